@@ -1,0 +1,424 @@
+"""The calls whose time and accuracy are tracked on one MI355X: gradient and training steps of the networks this
+framework is built for, and the kernel-level entry points that a program can call by themselves.
+
+Every case is a dict of plain values. `kind` names the path:
+  mlp     MoonwalkNet on a dense network: one gradient step (Moonwalk or backprop) or one training step in place
+  conv    ConvMoonwalkNet on a chain of 2-D convolutions: one gradient step
+  frag    ConvMoonwalkNet on a chain of 1-D convolutions with fragmental checkpointing: one gradient step
+  layer   one convolutional layer by itself: forward with sign mask, input cotangent, weight gradient
+  gemm    one fp32 product
+  steps   the stand-alone elementwise steps of one dense layer (sign packing, fragment index and compaction, ...)
+"""
+from __future__ import annotations
+
+import math
+
+import torch
+
+import paper_2402_14212_amd as mw
+
+
+# ------------------------------------------------------------------------------------------------ the cases
+def listed():
+    return [
+        # the smallest network of the tests: every launch is latency
+        dict(name="mlp_tiny", kind="mlp", d_first=64, d_last=64, grain=1, depth=4, batch=32, alpha=0.1, reseed=0,
+             scale_log2=0, method="moonwalk"),
+        # widths and a batch that no tile divides, as a user's own network has them
+        dict(name="mlp_ragged", kind="mlp", d_first=701, d_last=389, grain=1, depth=6, batch=100, alpha=0.3, reseed=2,
+             scale_log2=0, method="moonwalk"),
+        # the default benchmark: 64 square layers on a small batch, Phase III side by side on the second stream
+        dict(name="mlp_deep", kind="mlp", d_first=1024, d_last=1024, grain=1, depth=64, batch=256, alpha=0.1, reseed=4,
+             scale_log2=0, method="moonwalk"),
+        # ReLU layers: the fragment store is written and restored in the products' epilogues
+        dict(name="mlp_relu", kind="mlp", d_first=2048, d_last=2048, grain=1, depth=8, batch=512, alpha=0.0, reseed=0,
+             scale_log2=0, method="moonwalk"),
+        # the widest layers of the benchmark on a large batch: products that fill the chip
+        dict(name="mlp_wide", kind="mlp", d_first=4096, d_last=4096, grain=1, depth=6, batch=1024, alpha=0.1, reseed=4,
+             scale_log2=64, method="moonwalk"),
+        # the comparison method on a narrowing stack
+        dict(name="mlp_backprop", kind="mlp", d_first=2048, d_last=1024, grain=64, depth=16, batch=512, alpha=0.1, reseed=0,
+             scale_log2=0, method="backprop"),
+        # a training step in place: gradients applied layer by layer, right inverses brought up to date
+        dict(name="mlp_train", kind="mlp", d_first=1024, d_last=1024, grain=1, depth=12, batch=256, alpha=0.3, reseed=4,
+             scale_log2=0, method="train"),
+        # the paper's 2-D chain (3 x 3, stride 2, 128 channels) at a quarter of its batch and half its side
+        dict(name="conv_2d", kind="conv", batch=32, side=128, channels=128, depth=5, k=3, stride=2, pad=1, alpha=0.3, reseed=2),
+        # a kernel wider than padding + stride: the vijp sweeps over the anti-diagonals of the output grid
+        dict(name="conv_2d_k5", kind="conv", batch=8, side=64, channels=64, depth=3, k=5, stride=2, pad=1, alpha=0.3, reseed=2),
+        # the paper's 1-D chain with blocks of four positions
+        dict(name="conv_1d", kind="frag", batch=16, length=2048, channels=256, depth=3, k=3, block=4, alpha=0.3),
+        # one convolutional layer, each direction, called by itself on a small image batch
+        dict(name="layer_small", kind="layer", batch=6, side=29, c_in=96, c_out=64, k=3, stride=2, pad=1, alpha=0.2),
+        # the elementwise steps on tensors far larger than the caches
+        dict(name="steps_relu", kind="steps", rows=8192, d=4096, alpha=0.0),
+    ]
+
+
+def _log_uniform(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    """One more case of the ranges above; no dearer than the largest listed one."""
+    kind = rng.choice(["mlp", "mlp", "mlp", "conv", "frag", "layer", "gemm", "steps"])
+    if kind == "mlp":
+        method = rng.choice(["moonwalk", "moonwalk", "backprop", "train"])
+        d_first = _log_uniform(rng, 48, 3000)
+        grain = rng.choice([1, 1, 4, 32])
+        d_first = max(grain * 2, d_first // grain * grain)
+        d_last = d_first if rng.random() < 0.5 else max(grain, int(d_first * rng.uniform(0.5, 1.0)) // grain * grain)
+        alpha = rng.choice([0.1, 0.3, 0.5] if method == "train" else [0.0, 0.1, 0.3])
+        return dict(kind="mlp", d_first=d_first, d_last=d_last, grain=grain, depth=rng.randint(2, 9), batch=_log_uniform(rng, 17, 700),
+                    alpha=alpha, reseed=0 if alpha == 0.0 else rng.choice([2, 3, 4]), scale_log2=0, method=method)
+    if kind == "conv":
+        k = rng.choice([3, 3, 5])
+        return dict(kind="conv", batch=rng.randint(2, 12), side=rng.randint(32, 90), channels=rng.choice([32, 64, 96, 128]),
+                    depth=rng.randint(1, 3), k=k, stride=2, pad=1, alpha=rng.choice([0.2, 0.3, 0.5]), reseed=rng.choice([0, 2]))
+    if kind == "frag":
+        block = rng.choice([4, 8])
+        return dict(kind="frag", batch=rng.randint(2, 12), length=block * rng.randint(32, 200), channels=rng.choice([64, 96, 128, 224]),
+                    depth=rng.randint(1, 3), k=3, block=block, alpha=rng.choice([0.2, 0.3, 0.5]))
+    if kind == "layer":
+        c_out = rng.choice([32, 64, 96, 128])
+        return dict(kind="layer", batch=rng.randint(1, 24), side=rng.randint(9, 100), c_in=c_out + rng.choice([0, 32]), c_out=c_out,
+                    k=rng.choice([1, 3, 5]), stride=rng.choice([1, 2]), pad=rng.choice([0, 1]), alpha=0.2)
+    if kind == "gemm":
+        return dict(kind="gemm", op=rng.choice(["NT", "NN", "TN"]), m=_log_uniform(rng, 20, 4500), n=_log_uniform(rng, 20, 4500),
+                    inner=_log_uniform(rng, 20, 4500))
+    return dict(kind="steps", rows=_log_uniform(rng, 60, 8000), d=_log_uniform(rng, 60, 4000), alpha=rng.choice([0.0, 0.1, 0.3]))
+
+
+# ------------------------------------------------------------------------------------------------ inputs
+def _generator(seed):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(int(seed))
+    return gen
+
+
+def _randn(gen, *shape):
+    return torch.randn(*shape, device="cuda", dtype=torch.float32, generator=gen)
+
+
+def _widths(case):
+    """d_first .. d_last in equal steps, every width a multiple of `grain`, none larger than the one before."""
+    n, a, b, g = case["depth"], case["d_first"], case["d_last"], case["grain"]
+    return [max(g, int(round(a + (b - a) * i / n)) // g * g) for i in range(n + 1)]
+
+
+def _submersive_weights(gen, widths):
+    """Dense weights of full row rank with singular values around 0.7 .. 1.2: a Gaussian matrix pushed towards its
+    orthogonal polar factor (eight quintic steps)."""
+    out = []
+    for d_in, d_out in zip(widths[:-1], widths[1:]):
+        X = _randn(gen, d_out, d_in)
+        X = X / (math.sqrt(d_in) + math.sqrt(d_out))
+        for _ in range(8):
+            A = X @ X.t().contiguous()
+            X = 3.4445 * X + (-4.7750 * A + 2.0315 * (A @ A)) @ X
+        out.append(X.contiguous())
+    return out
+
+
+def _mlp_inputs(case, seed):
+    gen = _generator(seed)
+    widths = _widths(case)
+    Ws = _submersive_weights(gen, widths)
+    bs = [0.01 * _randn(gen, d) for d in widths[1:]]
+    x = _randn(gen, case["batch"], widths[0])
+    t = _randn(gen, case["batch"], widths[-1])
+    return Ws, bs, x, t
+
+
+TRAIN_LR = 0.05
+
+
+def _conv_side(n, case):
+    return (n + 2 * case["pad"] - case["k"]) // case["stride"] + 1
+
+
+def _conv_inputs(case, seed):
+    """The submersive recipe: N(0, 1 / fan-in) taps, the tap at (pad, pad) triangular over channels with diagonal U[0.8, 1.2]."""
+    gen = _generator(seed)
+    C, k, p = case["channels"], case["k"], case["pad"]
+    ws, bs, side = [], [], case["side"]
+    for _ in range(case["depth"]):
+        w = _randn(gen, k, k, C, C) / math.sqrt(k * k * C)
+        tap = torch.tril(w[p, p])
+        idx = torch.arange(C, device="cuda")
+        tap[idx, idx] = 0.8 + 0.4 * torch.rand(C, device="cuda", generator=gen)
+        w[p, p] = tap
+        ws.append(w.contiguous())
+        bs.append(0.01 * _randn(gen, C))
+        side = _conv_side(side, case)
+    x = _randn(gen, case["batch"], case["side"], case["side"], C)
+    t = _randn(gen, case["batch"], side, side, C)
+    return ws, bs, x, t
+
+
+def _frag_inputs(case, seed):
+    """The fragmental recipe: taps of half the usual gain, tap 0 triangular over channels with unit diagonal."""
+    gen = _generator(seed)
+    C, k, N = case["channels"], case["k"], case["length"]
+    ws, bs = [], []
+    for _ in range(case["depth"]):
+        w = 0.5 * _randn(gen, k, C, C) / math.sqrt(k * C)
+        tap = torch.tril(w[0])
+        idx = torch.arange(C, device="cuda")
+        tap[idx, idx] = 1.0
+        w[0] = tap
+        ws.append(w.contiguous())
+        bs.append(0.01 * _randn(gen, C))
+    return ws, bs, _randn(gen, case["batch"], N, C), _randn(gen, case["batch"], N, C)
+
+
+def _layer_inputs(case, seed):
+    gen = _generator(seed)
+    k, ci, co = case["k"], case["c_in"], case["c_out"]
+    side = _conv_side(case["side"], case)
+    x = _randn(gen, case["batch"], case["side"], case["side"], ci)
+    w = _randn(gen, k, k, ci, co) / math.sqrt(k * k * ci)
+    return x, w, 0.01 * _randn(gen, co), _randn(gen, case["batch"], side, side, co)
+
+
+def _gemm_inputs(case, seed):
+    gen = _generator(seed)
+    M, N, K = case["m"], case["n"], case["inner"]
+    A = _randn(gen, K, M) if case["op"] == "TN" else _randn(gen, M, K)
+    B = _randn(gen, N, K) if case["op"] == "NT" else _randn(gen, K, N)
+    return A, B
+
+
+def _steps_inputs(case, seed):
+    gen = _generator(seed)
+    r, d = case["rows"], case["d"]
+    return _randn(gen, r, d), 0.01 * _randn(gen, d), _randn(gen, r, d), _randn(gen, r, d), _randn(gen, r, d)
+
+
+def prepare(case, seed):
+    kind = case["kind"]
+    if kind == "mlp":
+        Ws, bs, x, t = _mlp_inputs(case, seed)
+        net = mw.MoonwalkNet(Ws, bs, [case["alpha"]] * case["depth"], case["batch"], reseed_interval=case["reseed"],
+                             loss_scale=2.0 ** case["scale_log2"],
+                             plan=mw.PLAN_BACKPROP if case["method"] == "backprop" else mw.PLAN_MOONWALK,
+                             phase3_overlap=True, refresh_bf16=case["method"] == "train")
+        return dict(case=case, net=net, x=x, t=t, Ws=Ws, bs=bs, grads=net.new_grads(),
+                    loss=torch.empty(1, dtype=torch.float32, device="cuda"),
+                    residual=torch.empty(1, dtype=torch.float32, device="cuda"))
+    if kind == "conv":
+        ws, bs, x, t = _conv_inputs(case, seed)
+        net = mw.ConvMoonwalkNet(ws, bs, [case["alpha"]] * case["depth"], case["batch"], case["side"], case["side"],
+                                 case["stride"], case["pad"], reseed_interval=case["reseed"], plan=mw.PLAN_MOONWALK)
+        return dict(case=case, net=net, x=x, t=t, grads=net.new_grads(), loss=torch.empty(1, dtype=torch.float32, device="cuda"))
+    if kind == "frag":
+        ws, bs, x, t = _frag_inputs(case, seed)
+        net = mw.ConvMoonwalkNet(ws, bs, [case["alpha"]] * case["depth"], case["batch"], 1, case["length"], 1,
+                                 (case["k"] - 1) // 2, kind=mw.CONV_FRAGMENTAL_1D, block=case["block"], plan=mw.PLAN_MOONWALK)
+        return dict(case=case, net=net, x=x, t=t, grads=net.new_grads(), loss=torch.empty(1, dtype=torch.float32, device="cuda"))
+    if kind == "layer":
+        x, w, b, ctz = _layer_inputs(case, seed)
+        return dict(case=case, x=x, w=w, b=b, ctz=ctz)
+    if kind == "gemm":
+        A, B = _gemm_inputs(case, seed)
+        out = torch.empty(case["m"], case["n"], dtype=torch.float32, device="cuda")
+        return dict(case=case, A=A, B=B, out=out)
+    z, bias, h, ct, t = _steps_inputs(case, seed)
+    return dict(case=case, z=z, bias=bias, h=h, ct=ct, t=t)
+
+
+def run(state):
+    case = state["case"]
+    kind = case["kind"]
+    if kind == "mlp":
+        net = state["net"]
+        if case["method"] == "train":
+            net.sgd_step(state["x"], state["t"], TRAIN_LR, refresh_iters=2, loss_out=state["loss"], residual=state["residual"])
+            return dict(W=state["Ws"], b=state["bs"], loss=state["loss"])
+        fn = net.backprop_grad if case["method"] == "backprop" else net.moonwalk_grad
+        r = fn(state["x"], state["t"], state["grads"], state["loss"])
+        return dict(grads=r.flat, loss=r.loss)
+    if kind in ("conv", "frag"):
+        r = state["net"].moonwalk_grad(state["x"], state["t"], state["grads"], state["loss"])
+        return dict(grads=r.flat, loss=r.loss)
+    if kind == "layer":
+        s, p, k = case["stride"], case["pad"], case["k"]
+        y, mask = mw.conv_forward(state["x"], state["w"], state["b"], s, p, p, alpha=case["alpha"], want_mask=True)
+        h = mw.conv_input_cotangent(state["ctz"], state["w"], (case["side"], case["side"]), s, p, p)
+        dw, db = mw.conv_weight_grad(state["x"], state["ctz"], k, k, s, p, p)
+        return dict(y=y, h=h, dw=dw, db=db)
+    if kind == "gemm":
+        op = {"NT": mw.GEMM_NT, "NN": mw.GEMM_NN, "TN": mw.GEMM_TN}[case["op"]]
+        return mw.gemm_f32(op, state["A"], state["B"], state["out"])
+    alpha = case["alpha"]
+    n = case["rows"] * case["d"]
+    x, mask = mw.bias_act_mask(state["z"], state["bias"], alpha)
+    h_L, loss = mw.loss_grad(x, state["t"], 1.0)
+    out = dict(x=x, h_L=h_L, loss=loss)
+    if alpha == 0.0:
+        offsets = mw.frag_offsets(mask, n)
+        frag, _ = mw.frag_compact(state["h"], mask, offsets)
+        out["frag"] = frag
+        x2, h_y = mw.vijp_epilogue(state["z"], state["ct"], alpha, mask, offsets, frag)
+    else:
+        x2, h_y = mw.vijp_epilogue(state["z"], state["ct"], alpha)
+    out.update(x_again=x2, h_y=h_y, ct_z=mw.rev_scale(state["h"], mask, alpha), db=mw.colsum_wide(state["ct"]))
+    return out
+
+
+# ------------------------------------------------------------------------------------------------ bytes and operations
+def work(case):
+    """What a pass cannot do without: inputs, weights and results once, the method's own products."""
+    kind = case["kind"]
+    if kind == "mlp":
+        w = _widths(case)
+        B = case["batch"]
+        prod = sum(a * b for a, b in zip(w[:-1], w[1:]))
+        io = 4 * (B * (w[0] + w[-1]) + 2 * prod + 2 * sum(w[1:]))   # x, t, W and the gradients (or the updated W)
+        if case["method"] == "backprop":
+            return {"bytes": io, "flops": 6 * B * prod - 2 * B * w[0] * w[1]}
+        io += 4 * prod                                               # the right inverses
+        flops = 10 * B * prod
+        if case["method"] == "train":
+            io += 4 * prod                                           # ... and written again
+            # two Schulz iterations of two products each, after two start products where the layer narrows
+            flops += sum((8 if a == b else 12) * b * b * a for a, b in zip(w[:-1], w[1:]))
+        return {"bytes": io, "flops": flops}
+    if kind == "conv":
+        C, k, B = case["channels"], case["k"], case["batch"]
+        reach = (k - 1 - case["pad"]) // case["stride"]
+        side, flops, params = case["side"], 0, 0
+        first = B * side * side * C
+        for _ in range(case["depth"]):
+            side = _conv_side(side, case)
+            rows = B * side * side
+            flops += 8 * rows * k * k * C * C + 2 * rows * C * C * (reach + 1) ** 2
+            params += k * k * C * C + C
+        return {"bytes": 4 * (2 * first + B * side * side * C + 2 * params), "flops": flops}   # x and h_0, t, w and dw
+    if kind == "frag":
+        C, k, rows = case["channels"], case["k"], case["batch"] * case["length"]
+        P = 2 * rows * k * C * C
+        flops = case["depth"] * (4 * P + P * (case["block"] - k + 1) // case["block"])
+        return {"bytes": 4 * (3 * rows * C + 2 * case["depth"] * (k * C * C + C)), "flops": flops}
+    if kind == "layer":
+        side = _conv_side(case["side"], case)
+        rows, pix = case["batch"] * side * side, case["batch"] * case["side"] ** 2
+        kk, ci, co = case["k"] ** 2, case["c_in"], case["c_out"]
+        return {"bytes": 4 * (2 * pix * ci + 2 * rows * co + 2 * kk * ci * co + 2 * co), "flops": 6 * rows * kk * ci * co}
+    if kind == "gemm":
+        M, N, K = case["m"], case["n"], case["inner"]
+        return {"bytes": 4 * (M * K + N * K + M * N), "flops": 2 * M * N * K}
+    n = case["rows"] * case["d"]
+    per = 8 + 12 + 8 + 16 + 4 + (8 if case["alpha"] == 0.0 else 0)
+    return {"bytes": per * n + 3 * n // 8, "flops": 10 * n}
+
+
+# ------------------------------------------------------------------------------------------------ tolerances
+def tolerance(case):
+    """Relative error (2-norm) between two correct fp32 implementations, about four times what was measured against
+    `exact`. A network's gradient changes by a finite step where a pre-activation next to zero takes the other sign (one
+    in about a million of them under fp32 rounding), and through the inverse Jacobians a rounding error grows by a
+    factor per layer between two re-seed points; single products and elementwise steps have neither."""
+    kind = case["kind"]
+    if kind == "mlp":
+        # measured: 2e-4 (alpha 0.1 over four layers), 6e-4 (ReLU) and 9e-4 (width 4096) from such signs; the updated
+        # weights of a training step 1.4e-6
+        # (a changed sign changes a whole row of a weight gradient by one sample's share)
+        return {"rel": 2e-5} if case["method"] == "train" else {"rel": 4e-3, "max": 1.0}
+    if kind == "conv":
+        # 4e-7 where no sign differs; one that does in the last layer (a few hundred positions) is 1e-4 of the whole
+        return {"rel": 2e-4, "max": 0.02}
+    if kind == "frag":
+        return {"rel": 5e-5}    # 6e-6 with blocks of four; the block recurrence multiplies a rounding error
+    if kind in ("layer", "gemm"):
+        return {"rel": 5e-6}    # 1.1e-6 over the longest sums
+    return {"rel": 1e-6}        # 2e-7
+
+
+# ------------------------------------------------------------------------------------------------ 64-bit results
+def _leaky(z, alpha):
+    return torch.where(z > 0, z, alpha * z)
+
+
+def _patches(x, k_h, k_w, s, p_h, p_w):
+    """Patch matrix [B, H', W', k_h k_w C] of a channels-last image."""
+    x = torch.nn.functional.pad(x, (0, 0, p_w, p_w, p_h, p_h))
+    Ho, Wo = (x.shape[1] - k_h) // s + 1, (x.shape[2] - k_w) // s + 1
+    return torch.cat([x[:, u:u + s * (Ho - 1) + 1:s, v:v + s * (Wo - 1) + 1:s, :] for u in range(k_h) for v in range(k_w)], dim=3)
+
+
+def _conv64(x, w, b, s, p_h, p_w):
+    k_h, k_w, ci, co = w.shape
+    P = _patches(x, k_h, k_w, s, p_h, p_w)
+    z = (P.reshape(-1, k_h * k_w * ci) @ w.reshape(-1, co)).reshape(P.shape[0], P.shape[1], P.shape[2], co)
+    return z if b is None else z + b
+
+
+def _flat_gradient(forward, ws, bs, x, t, batch):
+    """Gradient of J = 0.5 ||f(x) - t||^2 / B in 64 bits, laid out as the library does: per layer dW, db."""
+    ws = [w.double().requires_grad_() for w in ws]
+    bs = [b.double().requires_grad_() for b in bs]
+    loss = 0.5 * (forward(ws, bs, x.double()) - t.double()).square().sum() / batch
+    g = torch.autograd.grad(loss, [v for pair in zip(ws, bs) for v in pair])
+    return g, loss.detach().reshape(1)
+
+
+def exact(case, seed):
+    kind = case["kind"]
+    if kind == "mlp":
+        Ws, bs, x, t = _mlp_inputs(case, seed)
+        alpha = case["alpha"]
+
+        def forward(ws, bs_, v):
+            for w, b in zip(ws, bs_):
+                v = _leaky(v @ w.t() + b, alpha)
+            return v
+
+        g, loss = _flat_gradient(forward, Ws, bs, x, t, case["batch"])
+        if case["method"] == "train":
+            return dict(W=[w.double() - TRAIN_LR * d for w, d in zip(Ws, g[0::2])],
+                        b=[b.double() - TRAIN_LR * d for b, d in zip(bs, g[1::2])], loss=loss)
+        return dict(grads=torch.cat([v.reshape(-1) for v in g]), loss=loss)
+    if kind in ("conv", "frag"):
+        ws, bs, x, t = (_conv_inputs if kind == "conv" else _frag_inputs)(case, seed)
+        alpha = case["alpha"]
+        s, p_h, p_w = (case["stride"], case["pad"], case["pad"]) if kind == "conv" else (1, 0, (case["k"] - 1) // 2)
+        if kind == "frag":
+            ws, x, t = [w[None] for w in ws], x[:, None], t[:, None]
+
+        def forward(ws_, bs_, v):
+            for w, b in zip(ws_, bs_):
+                v = _leaky(_conv64(v, w, b, s, p_h, p_w), alpha)
+            return v
+
+        g, loss = _flat_gradient(forward, ws, bs, x, t, case["batch"])
+        return dict(grads=torch.cat([v.reshape(-1) for v in g]), loss=loss)
+    if kind == "layer":
+        x, w, b, ctz = _layer_inputs(case, seed)
+        x, w, b, ctz = x.double().requires_grad_(), w.double().requires_grad_(), b.double(), ctz.double()
+        z = _conv64(x, w, None, case["stride"], case["pad"], case["pad"])
+        h, dw = torch.autograd.grad(z, [x, w], ctz)
+        return dict(y=_leaky(z.detach() + b, case["alpha"]), h=h, dw=dw, db=ctz.sum((0, 1, 2)))
+    if kind == "gemm":
+        A, B = (v.double() for v in _gemm_inputs(case, seed))
+        return (A.t() if case["op"] == "TN" else A) @ (B.t() if case["op"] == "NT" else B)
+    z, bias, h, ct, t = (v.double() for v in _steps_inputs(case, seed))
+    alpha = case["alpha"]
+    zb = (z.float() + bias.float()).double()   # the sign is that of the 32-bit pre-activation
+    pos = zb > 0
+    x = torch.where(pos, zb, alpha * zb)
+    out = dict(x=x, h_L=(x - t) / case["rows"], loss=(0.5 * (x - t).square().sum() / case["rows"]).reshape(1))
+    pos2 = z > 0                               # the Phase-III step is given z as it is
+    if alpha == 0.0:
+        erased = h[~pos]
+        frag = torch.zeros(h.numel(), dtype=torch.float64, device="cuda")
+        frag[:erased.numel()] = erased
+        ct_kept = torch.where(pos, ct, torch.zeros_like(ct))
+        out["frag"] = frag
+        out.update(x_again=torch.where(pos, z, torch.zeros_like(z)), h_y=torch.where(pos, ct, h))
+    else:
+        ct_kept = ct
+        inv = float(torch.tensor(1.0) / torch.tensor(alpha))
+        out.update(x_again=torch.where(pos2, z, alpha * z), h_y=torch.where(pos2, ct, inv * ct))
+    out.update(ct_z=torch.where(pos, h, alpha * h), db=ct_kept.sum(0))
+    return out
