@@ -156,10 +156,10 @@ hipError_t dw_t(const ConvGeom& g, int n_img, const float* x, const float* ctz, 
   return launch_task<Cfg::NT>(t, stream);
 }
 
-// The tile for a product whose K runs over (tap, channel) with csel channels per tap: what pick_tile
+// The tile for a product whose K runs over (tap, channel) with csel channels per tap: what pick_tile_f32
 // says, unless that tile's K step would straddle taps; then the 64 x 64 tile, whose K step is 32.
 int gather_tile(int M, int N, int K, int csel_a, int csel_b) {
-  const int t = pick_tile(M, N, K);
+  const int t = pick_tile_f32(M, N, K);
   const int bk = t == TILE_64K2 ? 64 : (t == TILE_32K4 ? 128 : 32);
   return (csel_a % bk == 0 && csel_b % bk == 0) ? t : TILE_64;
 }

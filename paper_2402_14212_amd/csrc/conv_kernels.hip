@@ -328,8 +328,8 @@ hipError_t cv_tri_inverse(const float* T, int64_t ld, int n, float* Tinv, int32_
         const float* B = T + (int64_t)(o + m) * ld + o;
         float* X = Tinv + (int64_t)(o / 2) * n + n / 2;    // pair o / (2 m) gets rows [o / 2, o / 2 + m) of the quarter
         float* Low = Tinv + (int64_t)(o + m) * n + o;
-        e = gemm_plain(OP_NN, TILE_AUTO, m, m, m, 1.f, Dinv, n, B, ld, 0.f, X, n, nullptr, stream);
-        if (e == hipSuccess) e = gemm_plain(OP_NN, TILE_AUTO, m, m, m, -1.f, X, n, Ainv, n, 0.f, Low, n, nullptr, stream);
+        e = gemm_plain(OP_NN, pick_tile_f32(m, m, m), m, m, m, 1.f, Dinv, n, B, ld, 0.f, X, n, nullptr, stream);
+        if (e == hipSuccess) e = gemm_plain(OP_NN, pick_tile_f32(m, m, m), m, m, m, -1.f, X, n, Ainv, n, 0.f, Low, n, nullptr, stream);
       }
     }
     if (e != hipSuccess) return e;

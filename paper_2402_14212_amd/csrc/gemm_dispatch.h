@@ -5,36 +5,40 @@
 
 namespace mw {
 
-template <int LA, int LB, bool COLSUM, class Xf, class Epi>
+// Which tiles a launcher can be asked for (each one is a kernel): every tile (the kernel-level entry point takes fp32
+// tiles by name), those of pick_tile_f32, these and pick_tile's, those of weight gradients.
+enum TileSet { TILES_ALL, TILES_F32, TILES_REV, TILES_DW };
+
+template <int LA, int LB, bool COLSUM, TileSet SET, class Xf, class Epi>
 inline hipError_t dispatch_gemm(int tile, int M, int N, int K, const float* A, int64_t lda, const float* B,
                                 int64_t ldb, const Xf& xf, const Epi& epi, bool xf_vec_ok, float* colsum_out,
                                 float colsum_scale, hipStream_t stream, float colsum_beta = 0.f) {
-  if (tile == TILE_AUTO) tile = pick_tile(M, N, K);
+#define MW_LAUNCH_TILE(CFG)                                                                                            \
+  return launch_gemm<CFG, LA, LB, Xf, Epi, COLSUM>(M, N, K, A, lda, B, ldb, xf, epi, xf_vec_ok, colsum_out, colsum_scale, \
+                                                   stream, colsum_beta)
+  if (tile == TILE_AUTO) tile = LA == RCONTIG ? pick_tile_tn(M, N, K) : pick_tile(M, N, K);
   switch (tile) {
-    case TILE_128:
-      return launch_gemm<Tile128, LA, LB, Xf, Epi, COLSUM>(M, N, K, A, lda, B, ldb, xf, epi, xf_vec_ok, colsum_out,
-                                                          colsum_scale, stream, colsum_beta);
-    case TILE_64:
-      return launch_gemm<Tile64, LA, LB, Xf, Epi, COLSUM>(M, N, K, A, lda, B, ldb, xf, epi, xf_vec_ok, colsum_out,
-                                                         colsum_scale, stream, colsum_beta);
-    case TILE_32K4:
-      return launch_gemm<Tile32K4, LA, LB, Xf, Epi, COLSUM>(M, N, K, A, lda, B, ldb, xf, epi, xf_vec_ok, colsum_out,
-                                                           colsum_scale, stream, colsum_beta);
-    case TILE_32K8:
-      return launch_gemm<Tile32K8, LA, LB, Xf, Epi, COLSUM>(M, N, K, A, lda, B, ldb, xf, epi, xf_vec_ok, colsum_out,
-                                                           colsum_scale, stream, colsum_beta);
-    case TILE_64K2:
-      return launch_gemm<Tile64K2, LA, LB, Xf, Epi, COLSUM>(M, N, K, A, lda, B, ldb, xf, epi, xf_vec_ok, colsum_out,
-                                                           colsum_scale, stream, colsum_beta);
-    case TILE_128W8:
-      return launch_gemm<Tile128W8, LA, LB, Xf, Epi, COLSUM>(M, N, K, A, lda, B, ldb, xf, epi, xf_vec_ok, colsum_out,
-                                                           colsum_scale, stream, colsum_beta);
-    case TILE_64X128:
-      return launch_gemm<Tile64x128, LA, LB, Xf, Epi, COLSUM>(M, N, K, A, lda, B, ldb, xf, epi, xf_vec_ok, colsum_out,
-                                                           colsum_scale, stream, colsum_beta);
-    default:
-      return hipErrorInvalidValue;
+    case TILE_64: MW_LAUNCH_TILE(Tile64);
+    case TILE_128W8: MW_LAUNCH_TILE(Tile128W8);
+    case TILE_64X128: MW_LAUNCH_TILE(Tile64x128);
+    default: break;
   }
+  if constexpr (SET != TILES_F32) {
+    if (tile == TILE_S128) MW_LAUNCH_TILE(Split128);
+    if (tile == TILE_S64) MW_LAUNCH_TILE(Split64);
+  }
+  if constexpr (SET != TILES_DW) {
+    if (tile == TILE_32K4) MW_LAUNCH_TILE(Tile32K4);
+    if (tile == TILE_64K2) MW_LAUNCH_TILE(Tile64K2);
+  }
+  if constexpr (SET == TILES_ALL || SET == TILES_DW)
+    if (tile == TILE_128) MW_LAUNCH_TILE(Tile128);
+  if constexpr (LA == RCONTIG)
+    if (tile == TILE_S256) MW_LAUNCH_TILE(Split256);
+  if constexpr (SET == TILES_ALL)
+    if (tile == TILE_32K8) MW_LAUNCH_TILE(Tile32K8);
+#undef MW_LAUNCH_TILE
+  return hipErrorInvalidValue;
 }
 
 }  // namespace mw

@@ -8,12 +8,10 @@ template <bool RELU>
 static hipError_t vijp_dual_t(int tile, int M, int N, int K, const VijpArgs& a, hipStream_t stream) {
   EpiVijp<RELU> epi{a.bias, a.alpha, a.alpha > 0.f ? 1.0f / a.alpha : 0.f, a.mask, a.offsets, a.frag,
                     a.frag_base, a.frag_capacity, a.Xout, a.Hout, a.CTZ, a.mismatches};
-  if (tile == TILE_AUTO) tile = pick_tile(M, N, K);
+  if (tile == TILE_AUTO) tile = pick_tile_f32(M, N, K);
   switch (tile) {
-    case TILE_128: return launch_vijp_dual<Tile128, RELU>(M, N, K, a.X, a.W, a.Hin, a.P, epi, stream);
     case TILE_64: return launch_vijp_dual<Tile64, RELU>(M, N, K, a.X, a.W, a.Hin, a.P, epi, stream);
     case TILE_32K4: return launch_vijp_dual<Tile32K4, RELU>(M, N, K, a.X, a.W, a.Hin, a.P, epi, stream);
-    case TILE_32K8: return launch_vijp_dual<Tile32K8, RELU>(M, N, K, a.X, a.W, a.Hin, a.P, epi, stream);
     case TILE_64K2: return launch_vijp_dual<Tile64K2, RELU>(M, N, K, a.X, a.W, a.Hin, a.P, epi, stream);
     case TILE_128W8: return launch_vijp_dual<Tile128W8, RELU>(M, N, K, a.X, a.W, a.Hin, a.P, epi, stream);
     case TILE_64X128: return launch_vijp_dual<Tile64x128, RELU>(M, N, K, a.X, a.W, a.Hin, a.P, epi, stream);
@@ -53,21 +51,20 @@ static hipError_t pair_v(int tile_v, int tile_d, int M, int N, int K, const Vijp
     case TILE_128W8: return pair_d<Tile128W8, RELU>(tile_d, M, N, K, a, d, stream);
     case TILE_64X128: return pair_d<Tile64x128, RELU>(tile_d, M, N, K, a, d, stream);
     case TILE_64K2: return pair_d<Tile64K2, RELU>(tile_d, M, N, K, a, d, stream);
-    case TILE_128: return pair_d<Tile128, RELU>(tile_d, M, N, K, a, d, stream);
     case TILE_64: return pair_d<Tile64, RELU>(tile_d, M, N, K, a, d, stream);
     default: return pair_d<Tile32K4, RELU>(tile_d, M, N, K, a, d, stream);
   }
 }
 
 hipError_t gemm_phase3_pair(const VijpArgs* v, int M, int N, int K, const DwArgs* d, hipStream_t stream) {
-  const int tile_v = v ? pick_tile(M, N, K) : TILE_AUTO;
-  const int tile_d = d ? pick_tile_dw(d->M, d->N, d->K, tile_v, true) : TILE_AUTO;
+  const int tile_v = v ? pick_tile_f32(M, N, K) : TILE_AUTO;
+  const int tile_d = d ? pick_tile_dw_f32(d->M, d->N, tile_v, true) : TILE_AUTO;
   if (v && d && M > 0 && N > 0 && d->M > 0 && d->N > 0 && d->db) {
     const bool shapes_ok = extent_ok(M, K, K) && extent_ok(N, K, K) && extent_ok(M, N, N) &&
                            extent_ok(d->K, d->M, d->M) && extent_ok(d->K, d->N, d->N) && extent_ok(d->M, d->N, d->N);
     const bool vec = vijp_vec_ok(K, v->X, v->W, v->Hin, v->P) && operand_vec_ok(d->CTZ, d->M, d->M) &&
                      operand_vec_ok(d->X, d->N, d->N);
-    if (shapes_ok && vec && tile_v != TILE_32K8)
+    if (shapes_ok && vec)
       return v->alpha == 0.f ? pair_v<true>(tile_v, tile_d, M, N, K, *v, *d, stream)
                              : pair_v<false>(tile_v, tile_d, M, N, K, *v, *d, stream);
   }
@@ -88,7 +85,7 @@ bool phase3_group_ok(int M, int N, int K) {
   // layers whose Phase-I product takes the 32 x 32 tile with K split over four wavefronts (outputs too small to
   // fill the chip with larger tiles); pairs of whole 128-wide K tiles, so that the split falls on the same
   // boundaries and every set has an even number of 32-wide slices
-  return M > 0 && N > 0 && K > 0 && K % 256 == 0 && N % 32 == 0 && pick_tile(M, N, K) == TILE_32K4 && extent_ok(M, K, K) &&
+  return M > 0 && N > 0 && K > 0 && K % 256 == 0 && N % 32 == 0 && pick_tile_f32(M, N, K) == TILE_32K4 && extent_ok(M, K, K) &&
          extent_ok(N, K, K) && extent_ok(M, N, N);
 }
 
@@ -148,7 +145,7 @@ hipError_t gemm_phase3_group(int n_v, const VijpArgs* v, int M, int N, int K, in
   if (n_d > 0) {
     // the tile the weight gradient takes next to a layer kernel of the 32 x 32 K-split tile (the same product
     // launched with one layer gets the same tile, hence the same bits)
-    tile_d = pick_tile_dw(d[0].M, d[0].N, d[0].K, TILE_32K4, true);
+    tile_d = pick_tile_dw_f32(d[0].M, d[0].N, TILE_32K4, true);
     if (!extent_ok(d[0].K, d[0].M, d[0].M) || !extent_ok(d[0].K, d[0].N, d[0].N) || !extent_ok(d[0].M, d[0].N, d[0].N))
       return hipErrorInvalidValue;
     for (int g = 0; g < n_d; ++g) {
@@ -179,7 +176,10 @@ static hipError_t bp_pair_t(const BpLayerArgs& a, hipStream_t stream) {
 
 template <class CfgR>
 static hipError_t bp_pair_d(int tile_d, const BpLayerArgs& a, hipStream_t stream) {
-  if constexpr (CfgR::NT == 512) {
+  if constexpr (is_split<CfgR>()) {
+    if (tile_d == TILE_S128) return bp_pair_t<Split128, CfgR>(a, stream);
+    return bp_pair_t<Split64, CfgR>(a, stream);
+  } else if constexpr (CfgR::NT == 512) {
     return bp_pair_t<Tile64x128, CfgR>(a, stream);
   } else {
     if (tile_d == TILE_128) return bp_pair_t<Tile128, CfgR>(a, stream);
@@ -189,10 +189,10 @@ static hipError_t bp_pair_d(int tile_d, const BpLayerArgs& a, hipStream_t stream
 
 static hipError_t bp_pair_r(int tile_r, int tile_d, const BpLayerArgs& a, hipStream_t stream) {
   switch (tile_r) {
+    case TILE_S128: return bp_pair_d<Split128>(tile_d, a, stream);
+    case TILE_S64: return bp_pair_d<Split64>(tile_d, a, stream);
     case TILE_128W8: return bp_pair_d<Tile128W8>(tile_d, a, stream);
     case TILE_64X128: return bp_pair_d<Tile64x128>(tile_d, a, stream);
-    case TILE_64K2: return bp_pair_d<Tile64K2>(tile_d, a, stream);
-    case TILE_128: return bp_pair_d<Tile128>(tile_d, a, stream);
     case TILE_64: return bp_pair_d<Tile64>(tile_d, a, stream);
     default: return bp_pair_d<Tile32K4>(tile_d, a, stream);
   }
@@ -200,13 +200,13 @@ static hipError_t bp_pair_r(int tile_r, int tile_d, const BpLayerArgs& a, hipStr
 
 hipError_t gemm_bp_layer(const BpLayerArgs& a, hipStream_t stream) {
   const int tile_r = a.Hout ? pick_tile(a.batch, a.d_in, a.d_out) : TILE_AUTO;
-  const int tile_d = pick_tile_dw(a.d_out, a.d_in, a.batch, tile_r, false);
+  const int tile_d = bp_dw_tile(a.d_out, a.d_in, a.batch, tile_r);
   if (a.Hout && a.batch > 0 && a.d_in > 0 && a.d_out > 0) {
     const bool shapes_ok = extent_ok(a.batch, a.d_out, a.d_out) && extent_ok(a.batch, a.d_in, a.d_in) &&
                            extent_ok(a.d_out, a.d_in, a.d_in);
     const bool vec = operand_vec_ok(a.Hy, a.d_out, a.d_out) && aligned16(a.act) && operand_vec_ok(a.Xprev, a.d_in, a.d_in) &&
                      operand_vec_ok(a.W, a.d_in, a.d_in);
-    if (shapes_ok && vec && tile_r != TILE_32K8)
+    if (shapes_ok && vec && (tile_is_split(tile_r) == tile_is_split(tile_d)))
       return bp_pair_r(tile_r, tile_d, a, stream);
   }
   hipError_t e = gemm_dw_act(tile_d, a.d_out, a.d_in, a.batch, a.Hy, a.act, a.alpha, a.Xprev, a.scale, a.dW, a.db, stream);

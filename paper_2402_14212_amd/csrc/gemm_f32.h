@@ -73,9 +73,13 @@ __host__ __device__ constexpr int lds_stage_floats() {
 // for the split-K reduction (which reuses the same memory after the main loop).
 template <class Cfg, int LA, int LB, int NSETS>
 __host__ __device__ constexpr int lds_bytes() {
-  int pipe = 2 * lds_stage_floats<Cfg, LA, LB>();
-  int red = Cfg::WK > 1 ? Cfg::WK * Cfg::WM * Cfg::WN * (Cfg::NACC * 16 * NSETS + Cfg::WTM) * 64 : 0;
-  return 4 * (pipe > red ? pipe : red);
+  if constexpr (Cfg::PREC == 2) {
+    return Cfg::LDS_BYTES;   // gemm_split.h
+  } else {
+    int pipe = 2 * lds_stage_floats<Cfg, LA, LB>();
+    int red = Cfg::WK > 1 ? Cfg::WK * Cfg::WM * Cfg::WN * (Cfg::NACC * 16 * NSETS + Cfg::WTM) * 64 : 0;
+    return 4 * (pipe > red ? pipe : red);
+  }
 }
 
 // Workgroups are handed to the 8 XCDs round-robin by their linear id. Remap so that every XCD
@@ -123,6 +127,28 @@ struct Chunk {
   int nvalid;   // 0..4
 };
 
+// Which 4-element chunks of an operand tile (R rows x BK k) a thread moves: chunk i starts at (row(i), k(i)) of the
+// tile. KCONTIG chunks are four k of one row, RCONTIG chunks four rows at one k. KP > 1 (RCONTIG): chunks KP q ..
+// KP q + KP - 1 of a thread are the same rows at consecutive k, and a wavefront's eight-lane groups cover eight such
+// runs of k for eight row quads (128 bytes of memory at every k).
+template <int LAYOUT, int R, int BK, int NT, int KP>
+struct ChunkMap {
+  static __device__ __forceinline__ int row(int i) {
+    if (LAYOUT == KCONTIG) return ((int)threadIdx.x + i * NT) / (BK / 4);
+    if (KP == 1) return 4 * (((int)threadIdx.x + i * NT) % (R / 4));
+    const int f = (int)threadIdx.x + (i / KP) * NT;
+    return 4 * (((f & 63) >> 3) + 8 * ((f >> 6) / KGB));
+  }
+  static __device__ __forceinline__ int k(int i) {
+    if (LAYOUT == KCONTIG) return 4 * (((int)threadIdx.x + i * NT) % (BK / 4));
+    if (KP == 1) return ((int)threadIdx.x + i * NT) / (R / 4);
+    const int f = (int)threadIdx.x + (i / KP) * NT;
+    return ((f & 7) + 8 * ((f >> 6) % KGB)) * KP + i % KP;
+  }
+  static constexpr int KGB = KP > 1 ? BK / KP / 8 : 1;
+  static_assert(KP == 1 || (LAYOUT == RCONTIG && BK % (8 * KP) == 0 && R % 32 == 0), "runs of k in groups of eight, row quads too");
+};
+
 // ---------------------------------------------------------------------------------------------
 // Operand-A transforms. A transform has two halves so that the global loads of a tile stay in
 // flight while earlier tiles are multiplied: fetch() issues whatever extra loads it needs next
@@ -134,7 +160,9 @@ struct Chunk {
 struct ALinearDev {
   // Called once by the main loop before the first tile is requested (row0: the tile's first row of
   // the operand; n_rows, n_k: its extents), and once after every tile request, in tile order.
-  template <int LAYOUT, int R, int BK, int NT>
+  // KP: see ChunkMap.
+  static constexpr bool GATHERED = false;
+  template <int LAYOUT, int R, int BK, int NT, int KP = 1>
   __device__ __forceinline__ void prepare(int /*row0*/, int /*n_rows*/, int /*n_k*/) {}
   template <int LAYOUT, int BK>
   __device__ __forceinline__ void advance() {}

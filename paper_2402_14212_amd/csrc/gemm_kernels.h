@@ -6,6 +6,7 @@
 #pragma once
 
 #include "gemm_f32.h"
+#include "gemm_split.h"
 
 namespace mw {
 
@@ -384,6 +385,17 @@ struct GemmTask {
   __device__ __forceinline__ void run_tile(int tm_i, int tn_i, float* __restrict__ lds) const {
     const int m0 = tm_i * Cfg::BM, n0 = tn_i * Cfg::BN;
 
+    if constexpr (is_split<Cfg>()) {
+      typename Xf::Dev xd(xf, LA == KCONTIG ? M : K, LA == KCONTIG ? K : M, lda);
+      typename Epi::Dev ed(epi, M, N);
+      split_product<Cfg, LA, LB, VEC, COLSUM>(A, lda, B, ldb, M, N, K, m0, n0, lds, xd, ed, colsum_out, colsum_scale, colsum_beta);
+      ed.finish();
+    } else {
+      run_tile_f32(m0, n0, lds);
+    }
+  }
+
+  __device__ __forceinline__ void run_tile_f32(int m0, int n0, float* __restrict__ lds) const {
     f32x16 acc[1][Cfg::NACC];
     float asum[Cfg::WTM];
 #pragma unroll

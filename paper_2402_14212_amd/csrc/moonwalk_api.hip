@@ -24,34 +24,66 @@ hipError_t gemm_plain_nn(int tile, int M, int N, int K, float alpha, const float
 hipError_t gemm_plain_tn(int tile, int M, int N, int K, float alpha, const float* A, int64_t lda, const float* B,
                          int64_t ldb, float beta, float* C, int64_t ldc, const float* bias, hipStream_t stream);
 
-int pick_tile(int M, int N, int K) {
-  auto tiles = [](int m, int n, int tm, int tn) { return (int64_t)((m + tm - 1) / tm) * ((n + tn - 1) / tn); };
+static int64_t tiles_of(int m, int n, int tm, int tn) { return (int64_t)((m + tm - 1) / tm) * ((n + tn - 1) / tn); }
+
+// The split tile with the least time for `sets` outputs of M x N. One workgroup of each runs on a CU at a time, so
+// the time is the number of rounds of 256 workgroups times a round's length; relative lengths measured at K = 1024
+// .. 4096 (us a round at 8192 x 1024 x 1024): 256 x 128 69, 128 x 128 40, 64 x 64 12.5 (14.6 by itself).
+// For example 512 x 2048: 256 tiles of 64 x 64 in 26 us against 64 of 128 x 128 in 48.
+int pick_split_tile(int64_t sets, int M, int N, bool s256) {
+  struct { int tile, tm, tn; double cost; bool allowed; } const c[] = {
+      {TILE_S256, 256, 128, 1.7, s256}, {TILE_S128, 128, 128, 1.0, true}, {TILE_S64, 64, 64, 0.34, true}};
+  int best = TILE_S128;
+  double least = 1e300;
+  for (const auto& t : c) {
+    const double cost = (double)((sets * tiles_of(M, N, t.tm, t.tn) + 255) / 256) * t.cost;
+    if (t.allowed && cost < least) {
+      least = cost;
+      best = t.tile;
+    }
+  }
+  return best;
+}
+
+// The tile of a pre-activation product (Phase I, its recomputation in Phase III, backprop's forward). These stay on
+// fp32 instructions: the sign of a pre-activation selects a linear piece of the network, so one that lies next to zero
+// and is rounded another way changes gradients by a finite step (relative to 64 bits 2e-4 to 2e-3 on the same inputs,
+// from nothing but which signs differ), however exact the product.
+int pick_tile_f32(int M, int N, int K) {
   // Measured on MI355X (256 CUs) over the layer shapes of the five configurations: take the
   // largest tile that still gives every CU about two workgroups, with eight wavefronts per
   // workgroup; below that the 64x64 tile, whose eight-wavefront form splits K over two groups
   // (it pays when K is long); outputs too small even for that split K over the four wavefronts
   // of a 32x32 tile.
-  if (tiles(M, N, 128, 128) >= 512) return TILE_128W8;
-  if (tiles(M, N, 64, 128) >= 512) return TILE_64X128;
-  const int64_t t64 = tiles(M, N, 64, 64);
-  if (t64 >= 192) return K >= 1024 ? TILE_64K2 : TILE_64;
+  if (tiles_of(M, N, 128, 128) >= 512) return TILE_128W8;
+  if (tiles_of(M, N, 64, 128) >= 512) return TILE_64X128;
+  if (tiles_of(M, N, 64, 64) >= 192) return K >= 1024 ? TILE_64K2 : TILE_64;
   if (K >= 256) return TILE_32K4;
   return TILE_64;
 }
 
-// The weight-gradient tile next to a kernel of tile `partner` (TILE_AUTO: none); `phase3` says
-// whether that kernel is a Phase-III layer kernel or backprop's reverse product. Both tasks of a
-// launch need the same workgroup size, so the choice is made among the tiles with as many
-// wavefronts as the partner's; within those it follows what was measured for the pairs. It
-// depends on the shapes alone: launched together or apart, a product gets the same tile and
-// therefore the same bits.
-int pick_tile_dw(int M, int N, int K, int partner, bool phase3) {
-  (void)K;
-  const int64_t t128 = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
+// From 96 tiles of 64 x 64 the split ones are faster (us at K = 1024: 512 x 1024 14.6 against 21 on fp32 instructions);
+// smaller outputs are better spread over 32 x 32 fp32 tiles (256 x 1024: 11.1 against 14.6).
+bool split_pays(int64_t sets, int M, int N, int K) { return K >= SPLIT_MIN_K && sets * tiles_of(M, N, 64, 64) >= 96; }
+
+int pick_tile(int M, int N, int K) {
+  return split_pays(1, M, N, K) ? pick_split_tile(1, M, N, false) : pick_tile_f32(M, N, K);
+}
+
+int pick_tile_tn(int M, int N, int K) {
+  return split_pays(1, M, N, K) ? pick_split_tile(1, M, N, true) : pick_tile_f32(M, N, K);
+}
+
+int pick_tile_dw_f32(int M, int N, int partner, bool phase3) {
   // eight wavefronts: beside a layer kernel the 128x128 tile (few, long workgroups on both sides
   // share the CUs evenly), beside the single reverse product the 64x128 one
   if (tile_has_8_waves(partner)) return phase3 ? TILE_128W8 : TILE_64X128;
-  return t128 >= 512 ? TILE_128 : TILE_64;
+  return tiles_of(M, N, 128, 128) >= 512 ? TILE_128 : TILE_64;
+}
+
+int bp_dw_tile(int d_out, int d_in, int B, int partner) {
+  const bool split = partner == TILE_AUTO ? split_pays(1, d_out, d_in, B) : tile_is_split(partner);
+  return split ? pick_split_tile(1, d_out, d_in, false) : pick_tile_dw_f32(d_out, d_in, partner, false);
 }
 
 hipError_t gemm_plain(int op, int tile, int M, int N, int K, float alpha, const float* A, int64_t lda,
@@ -615,6 +647,9 @@ struct Step {
   const float* x;
   float* grads_out;
   float apply_lr;  // 0: gradients to grads_out; else W_i -= apply_lr dW_i, b_i -= apply_lr db_i in place
+  // Products on split operands. Not in a training step: its gradients become weights, whose every bit decides the
+  // signs of pre-activations next to zero in the next step (see pick_tile_f32).
+  bool split() const { return apply_lr == 0.f; }
 };
 
 // Forward through layers [lo, hi) from xin. Layers i >= mask_from also write their sign masks.
@@ -628,19 +663,20 @@ int forward_range(const Step& c, int lo, int hi, const float* xin, int mask_from
     Layer& l = h->layers[i];
     float* xout = l.xck ? l.xck : xbuf[i & 1];
     const bool want_mask = i >= mask_from;
+    const int tile = pick_tile_f32(B, l.d_out, l.d_in);  // (see there: the signs of the pre-activations)
     // mask slots are shared between segments: clear what this layer's packing will not overwrite
     if (want_mask && h->S > 0 && (((size_t)B * l.d_out) % 64) != 0)
       MW_LAUNCH(h, s, MW_KCLASS_EW, ew_fill_u32(reinterpret_cast<uint32_t*>(l.mask + l.mask_words - 1), 0u, 2, s));
     if (h->fuse) {
       if (want_mask && l.d_out % 32 == 0) {
-        MW_LAUNCH(h, s, MW_KCLASS_FWD, gemm_fwd_act(TILE_AUTO, B, l.d_out, l.d_in, xin, l.W, l.b, l.alpha, xout, l.mask, s, l.dbg_z));
+        MW_LAUNCH(h, s, MW_KCLASS_FWD, gemm_fwd_act(tile, B, l.d_out, l.d_in, xin, l.W, l.b, l.alpha, xout, l.mask, s, l.dbg_z));
       } else {
-        MW_LAUNCH(h, s, MW_KCLASS_FWD, gemm_fwd_act(TILE_AUTO, B, l.d_out, l.d_in, xin, l.W, l.b, l.alpha, xout, nullptr, s, l.dbg_z));
+        MW_LAUNCH(h, s, MW_KCLASS_FWD, gemm_fwd_act(tile, B, l.d_out, l.d_in, xin, l.W, l.b, l.alpha, xout, nullptr, s, l.dbg_z));
         if (want_mask) MW_LAUNCH(h, s, MW_KCLASS_EW, ew_mask_from_act(xout, (int64_t)B * l.d_out, l.mask, s));
       }
     } else {
       float* z = l.dbg_z ? l.dbg_z : h->zbuf;
-      MW_LAUNCH(h, s, MW_KCLASS_FWD, gemm_plain(OP_NT, TILE_AUTO, B, l.d_out, l.d_in, 1.f, xin, l.d_in, l.W, l.d_in, 0.f, z, l.d_out,
+      MW_LAUNCH(h, s, MW_KCLASS_FWD, gemm_plain(OP_NT, tile, B, l.d_out, l.d_in, 1.f, xin, l.d_in, l.W, l.d_in, 0.f, z, l.d_out,
                         l.b, s));
       MW_LAUNCH(h, s, MW_KCLASS_EW, ew_bias_act_mask(z, nullptr, B, l.d_out, l.alpha, xout, want_mask ? l.mask : nullptr, s));
     }
@@ -696,8 +732,9 @@ int reverse_range(const Step& c, int lo, int hi, float* h_top, float* h_bottom,
     const float* ctcur = h_top;
     for (int i = hi - 1; i >= lo; --i) {
       Layer& l = h->layers[i];
+      const int tile = c.split() ? pick_tile(B, l.d_in, l.d_out) : pick_tile_f32(B, l.d_in, l.d_out);
       if (i == lo) {
-        MW_LAUNCH(h, s, MW_KCLASS_REV, gemm_plain(OP_NN, TILE_AUTO, B, l.d_in, l.d_out, 1.f, ctcur, l.d_out, l.W, l.d_in, 0.f,
+        MW_LAUNCH(h, s, MW_KCLASS_REV, gemm_plain(OP_NN, tile, B, l.d_in, l.d_out, 1.f, ctcur, l.d_out, l.W, l.d_in, 0.f,
                                                   h_bottom, l.d_in, nullptr, s));
       } else {
         Layer& below = h->layers[i - 1];
@@ -705,7 +742,7 @@ int reverse_range(const Step& c, int lo, int hi, float* h_top, float* h_bottom,
         const bool relu = below.alpha == 0.f;
         RevArgs r{ctout, below.ckpt ? below.ckpt : below.dbg_h, below.mask, below.alpha, below.offsets, h->frag,
                   relu ? h->frag_bases + below.relu_slot : nullptr, h->frag_capacity, overflow};
-        MW_LAUNCH(h, s, MW_KCLASS_REV, gemm_rev_fused(TILE_AUTO, B, l.d_in, l.d_out, ctcur, l.W, r, s));
+        MW_LAUNCH(h, s, MW_KCLASS_REV, gemm_rev_fused(tile, B, l.d_in, l.d_out, ctcur, l.W, r, s));
         ctcur = ctout;
       }
       if (released) MW_TRY_RC(released(i));
@@ -779,9 +816,9 @@ int phase3_range(const Step& c, int lo, int hi, const float* xin, const float* h
         have_pending = true;
       } else {
         // same tiles as in the paired launches: the weight gradient's follows the next layer's kernel
-        const int partner = (i + 1 < hi) ? pick_tile(B, h->layers[i + 1].d_out, h->layers[i + 1].d_in) : TILE_AUTO;
+        const int partner = (i + 1 < hi) ? pick_tile_f32(B, h->layers[i + 1].d_out, h->layers[i + 1].d_in) : TILE_AUTO;
         MW_LAUNCH(h, s, MW_KCLASS_VIJP, gemm_vijp_dual(TILE_AUTO, B, l.d_out, l.d_in, a, s));
-        MW_LAUNCH(h, s, MW_KCLASS_DW, gemm_dw(pick_tile_dw(d.M, d.N, d.K, partner, true), d.M, d.N, d.K, d.CTZ, d.X, d.scale,
+        MW_LAUNCH(h, s, MW_KCLASS_DW, gemm_dw(pick_tile_dw_f32(d.M, d.N, partner, true), d.M, d.N, d.K, d.CTZ, d.X, d.scale,
                                               d.dW, d.db, s, d.beta));
       }
       xin = xout;
@@ -795,15 +832,15 @@ int phase3_range(const Step& c, int lo, int hi, const float* xin, const float* h
       float* xout = xbuf[i & 1];
       float* hout = l.dbg_h3 ? l.dbg_h3 : hbuf[i & 1];
       const bool relu = (l.alpha == 0.f);
-      MW_LAUNCH(h, s, MW_KCLASS_FWD, gemm_plain(OP_NT, TILE_AUTO, B, l.d_out, l.d_in, 1.f, xin, l.d_in, l.W, l.d_in, 0.f, h->zbuf, l.d_out,
+      MW_LAUNCH(h, s, MW_KCLASS_FWD, gemm_plain(OP_NT, pick_tile_f32(B, l.d_out, l.d_in), B, l.d_out, l.d_in, 1.f, xin, l.d_in, l.W, l.d_in, 0.f, h->zbuf, l.d_out,
                         l.b, s));
-      MW_LAUNCH(h, s, MW_KCLASS_FWD, gemm_plain(OP_NT, TILE_AUTO, B, l.d_out, l.d_in, 1.f, hin, l.d_in, l.P, l.d_in, 0.f, h->ctz, l.d_out,
+      MW_LAUNCH(h, s, MW_KCLASS_FWD, gemm_plain(OP_NT, pick_tile_f32(B, l.d_out, l.d_in), B, l.d_out, l.d_in, 1.f, hin, l.d_in, l.P, l.d_in, 0.f, h->ctz, l.d_out,
                         nullptr, s));
       MW_LAUNCH(h, s, MW_KCLASS_EW, ew_vijp_epilogue(h->zbuf, h->ctz, B, l.d_out, l.alpha, l.mask, l.offsets, h->frag,
                               relu ? h->frag_bases + l.relu_slot : nullptr, h->frag_capacity, xout, hout, mismatches,
                               s));
-      const int partner = (i + 1 < hi) ? pick_tile(B, h->layers[i + 1].d_out, h->layers[i + 1].d_in) : TILE_AUTO;
-      MW_LAUNCH(h, s, MW_KCLASS_DW, gemm_dw(pick_tile_dw(l.d_out, l.d_in, B, partner, true), l.d_out, l.d_in, B, h->ctz, xin, inv_scale,
+      const int partner = (i + 1 < hi) ? pick_tile_f32(B, h->layers[i + 1].d_out, h->layers[i + 1].d_in) : TILE_AUTO;
+      MW_LAUNCH(h, s, MW_KCLASS_DW, gemm_dw(pick_tile_dw_f32(l.d_out, l.d_in, partner, true), l.d_out, l.d_in, B, h->ctz, xin, inv_scale,
                                             c.grads_out + l.dW_off, nullptr, s));
       MW_LAUNCH(h, s, MW_KCLASS_EW, ew_colsum(h->ctz, B, l.d_out, inv_scale, c.grads_out + l.db_off, s));
       xin = xout;
@@ -1161,7 +1198,7 @@ int backprop_grad(mw_handle_t* h, const float* x, const float* target, float* gr
   const float* xin = x;
   for (int i = 0; i < L; ++i) {
     Layer& l = h->layers[i];
-    MW_LAUNCH(h, s, MW_KCLASS_FWD, gemm_fwd_act(TILE_AUTO, B, l.d_out, l.d_in, xin, l.W, l.b, l.alpha, l.act, nullptr, s));
+    MW_LAUNCH(h, s, MW_KCLASS_FWD, gemm_fwd_act(pick_tile_f32(B, l.d_out, l.d_in), B, l.d_out, l.d_in, xin, l.W, l.b, l.alpha, l.act, nullptr, s));
     xin = l.act;
   }
   float* hbuf[2] = {h->bp_ha, h->bp_hb};
@@ -1180,7 +1217,7 @@ int backprop_grad(mw_handle_t* h, const float* x, const float* target, float* gr
       MW_LAUNCH(h, s, MW_KCLASS_PHASE3, gemm_bp_layer(a, s));
     } else {
       const int tile_r = (i > 0) ? pick_tile(B, l.d_in, l.d_out) : TILE_AUTO;
-      MW_LAUNCH(h, s, MW_KCLASS_DW, gemm_dw_act(pick_tile_dw(l.d_out, l.d_in, B, tile_r, false), l.d_out, l.d_in, B, a.Hy, a.act, a.alpha,
+      MW_LAUNCH(h, s, MW_KCLASS_DW, gemm_dw_act(bp_dw_tile(l.d_out, l.d_in, B, tile_r), l.d_out, l.d_in, B, a.Hy, a.act, a.alpha,
                                                 a.Xprev, a.scale, a.dW, a.db, s));
       if (i > 0) MW_LAUNCH(h, s, MW_KCLASS_REV, gemm_rev_act(tile_r, B, l.d_in, l.d_out, a.Hy, a.act, a.alpha, a.W, a.Hout, s));
     }

@@ -9,16 +9,29 @@ namespace mw {
 
 // tile selectors (same values as MW_TILE_* in the public header)
 constexpr int TILE_AUTO = 0, TILE_128 = 1, TILE_64 = 2, TILE_32K4 = 3, TILE_32K8 = 4, TILE_64K2 = 5, TILE_128W8 = 6, TILE_64X128 = 7;
-// tiles whose workgroups have eight wavefronts (the others have four)
+// tiles of the products on split operands (gemm_split.h), chosen by the library only; eight wavefronts each (S64Q: four)
+constexpr int TILE_S256 = 16, TILE_S128 = 17, TILE_S64 = 18;
+inline bool tile_is_split(int tile) { return tile >= TILE_S256; }
+// least K of a product that takes split operands: below it the product is a few K tiles of launch and memory latency
+constexpr int SPLIT_MIN_K = 128;
+// fp32 tiles whose workgroups have eight wavefronts (the others have four)
 inline bool tile_has_8_waves(int tile) { return tile == TILE_32K8 || tile == TILE_64K2 || tile == TILE_128W8 || tile == TILE_64X128; }
 constexpr int OP_NT = 0, OP_NN = 1, OP_TN = 2;
 
-// Tile choice for an M x N x K product on a 256-CU device. Deterministic in (M, N, K) only, so
-// that phase I and phase III compute a layer's pre-activations with the same kernel shape.
+// Tile choice for an M x N x K product on a 256-CU device (NT or NN; TN). Deterministic in (M, N, K) only.
 int pick_tile(int M, int N, int K);
-// tile of a weight-gradient product launched beside a kernel of tile `partner` (TILE_AUTO: alone),
-// which is a Phase-III layer kernel (phase3) or backprop's reverse product
-int pick_tile_dw(int M, int N, int K, int partner, bool phase3);
+int pick_tile_tn(int M, int N, int K);
+// whether `sets` products of one shape take split operands, and if so the cheapest split tile (256 x 128: only if s256) for `sets` products of one shape
+bool split_pays(int64_t sets, int M, int N, int K);
+int pick_split_tile(int64_t sets, int M, int N, bool s256);
+// the same among the tiles on fp32 matrix instructions: every product that computes pre-activations takes it, so that
+// Phase I and Phase III get the same bits
+int pick_tile_f32(int M, int N, int K);
+// fp32 tile of a weight-gradient product launched beside a kernel of tile `partner` (TILE_AUTO: alone), which is a
+// Phase-III layer kernel (phase3) or backprop's reverse product
+int pick_tile_dw_f32(int M, int N, int partner, bool phase3);
+// tile of backprop's weight gradient beside the reverse product's (`partner`)
+int bp_dw_tile(int d_out, int d_in, int B, int partner);
 
 // ---- GEMM launchers (gemm_*.hip). All enqueue on `stream` and return the launch status. ----
 

@@ -110,7 +110,7 @@ hipError_t setup_right_inverse_group(int count, const float* const* W, int d_out
 
   for (int j = 0; j < count; ++j) {
     // G = W W^T
-    MW_TRY(gemm_plain_nt(TILE_AUTO, n, n, m, 1.f, W[j], m, W[j], m, 0.f, Gof(j), n, nullptr, stream));
+    MW_TRY(gemm_plain_nt(pick_tile_f32(n, n, m), n, n, m, 1.f, W[j], m, W[j], m, 0.f, Gof(j), n, nullptr, stream));
     // Y = W (right-hand side of the first solve, overwritten block row by block row)
     MW_TRY(ew_copy(W[j], Yof(j), (int64_t)n * m, stream));
   }
@@ -129,7 +129,7 @@ hipError_t setup_right_inverse_group(int count, const float* const* W, int d_out
       // column tile, so each workgroup reads only the rows it later writes.
       MW_TRY(gemm_plain_nt(TILE_64, below, bs, bs, 1.f, panel, n, Lk_inv, NB, 0.f, panel, n, nullptr, stream));
       // trailing block -= panel * panel^T
-      MW_TRY(gemm_plain_nt(TILE_AUTO, below, below, bs, -1.f, panel, n, panel, n, 1.f,
+      MW_TRY(gemm_plain_nt(pick_tile_f32(below, below, bs), below, below, bs, -1.f, panel, n, panel, n, 1.f,
                            G + (size_t)k1 * n + k1, n, nullptr, stream));
     }
   }
@@ -146,7 +146,7 @@ hipError_t setup_right_inverse_group(int count, const float* const* W, int d_out
       // Yk <- Lkk^{-1} Yk  (single row tile: in place is safe for the same reason as above)
       MW_TRY(gemm_plain_nn(TILE_64, bs, m, bs, 1.f, Lk_inv, NB, Yk, m, 0.f, Yk, m, nullptr, stream));
       if (below > 0)
-        MW_TRY(gemm_plain_nn(TILE_AUTO, below, m, bs, -1.f, G + (size_t)k1 * n + k0, n, Yk, m, 1.f,
+        MW_TRY(gemm_plain_nn(pick_tile_f32(below, m, bs), below, m, bs, -1.f, G + (size_t)k1 * n + k0, n, Yk, m, 1.f,
                              Y + (size_t)k1 * m, m, nullptr, stream));
     }
     // L^T P = Y, right-looking from the last block row upwards
@@ -159,7 +159,7 @@ hipError_t setup_right_inverse_group(int count, const float* const* W, int d_out
       MW_TRY(gemm_plain_tn(TILE_64, bs, m, bs, 1.f, Lk_inv, NB, Yk, m, 0.f, Pk, m, nullptr, stream));
       // rows above: Y[0:k0] -= L[k0:k1, 0:k0]^T Pk
       if (k0 > 0)
-        MW_TRY(gemm_plain_tn(TILE_AUTO, k0, m, bs, -1.f, G + (size_t)k0 * n, n, Pk, m, 1.f, Y, m, nullptr, stream));
+        MW_TRY(gemm_plain_tn(pick_tile_f32(k0, m, bs), k0, m, bs, -1.f, G + (size_t)k0 * n, n, Pk, m, 1.f, Y, m, nullptr, stream));
     }
   }
   return hipSuccess;
