@@ -18,16 +18,19 @@ template <int LA, int LB>
 hipError_t grouped_l(int n_sets, int M, int N, int K, float alpha, const float* const* A, int64_t lda,
                      const float* const* B, int64_t ldb, float beta, const float* const* D, float* const* C, int64_t ldc,
                      hipStream_t stream, float eye, bool bf16) {
-  // the tile one product of n_sets times the rows would take, among the tiles without a K split
   auto tiles = [&](int tm, int tn) { return (int64_t)n_sets * ceil_div(M, tm) * ceil_div(N, tn); };
-  if (bf16) {
+  if (bf16) {  // the tile one product of n_sets times the rows would take, among the tiles without a K split
     if (tiles(128, 128) >= 512) return grouped_t<Tile128W8B, LA, LB>(n_sets, M, N, K, alpha, A, lda, B, ldb, beta, D, C, ldc, stream, eye);
     if (tiles(64, 128) >= 512) return grouped_t<Tile64x128B, LA, LB>(n_sets, M, N, K, alpha, A, lda, B, ldb, beta, D, C, ldc, stream, eye);
     return grouped_t<Tile64B, LA, LB>(n_sets, M, N, K, alpha, A, lda, B, ldb, beta, D, C, ldc, stream, eye);
   }
-  if (tiles(128, 128) >= 512) return grouped_t<Tile128W8, LA, LB>(n_sets, M, N, K, alpha, A, lda, B, ldb, beta, D, C, ldc, stream, eye);
-  if (tiles(64, 128) >= 512) return grouped_t<Tile64x128, LA, LB>(n_sets, M, N, K, alpha, A, lda, B, ldb, beta, D, C, ldc, stream, eye);
-  return grouped_t<Tile64, LA, LB>(n_sets, M, N, K, alpha, A, lda, B, ldb, beta, D, C, ldc, stream, eye);
+  // us for twelve products of 1024 x 1024 x 1024: 66 on split operands, 156 with fp32 tiles
+  if (K < SPLIT_MIN_K) return grouped_t<Tile64, LA, LB>(n_sets, M, N, K, alpha, A, lda, B, ldb, beta, D, C, ldc, stream, eye);
+  switch (pick_split_tile(n_sets, M, N, true)) {
+    case TILE_S256: return grouped_t<Split256, LA, LB>(n_sets, M, N, K, alpha, A, lda, B, ldb, beta, D, C, ldc, stream, eye);
+    case TILE_S128: return grouped_t<Split128, LA, LB>(n_sets, M, N, K, alpha, A, lda, B, ldb, beta, D, C, ldc, stream, eye);
+    default: return grouped_t<Split64, LA, LB>(n_sets, M, N, K, alpha, A, lda, B, ldb, beta, D, C, ldc, stream, eye);
+  }
 }
 
 }  // namespace
