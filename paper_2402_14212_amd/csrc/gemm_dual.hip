@@ -8,7 +8,6 @@ template <bool RELU>
 static hipError_t vijp_dual_t(int tile, int M, int N, int K, const VijpArgs& a, hipStream_t stream) {
   EpiVijp<RELU> epi{a.bias, a.alpha, a.alpha > 0.f ? 1.0f / a.alpha : 0.f, a.mask, a.offsets, a.frag,
                     a.frag_base, a.frag_capacity, a.Xout, a.Hout, a.CTZ, a.mismatches};
-  if (tile == TILE_AUTO) tile = pick_tile_f32(M, N, K);
   switch (tile) {
     case TILE_64: return launch_vijp_dual<Tile64, RELU>(M, N, K, a.X, a.W, a.Hin, a.P, epi, stream);
     case TILE_32K4: return launch_vijp_dual<Tile32K4, RELU>(M, N, K, a.X, a.W, a.Hin, a.P, epi, stream);
@@ -56,10 +55,52 @@ static hipError_t pair_v(int tile_v, int tile_d, int M, int N, int K, const Vijp
   }
 }
 
-hipError_t gemm_phase3_pair(const VijpArgs* v, int M, int N, int K, const DwArgs* d, hipStream_t stream) {
-  const int tile_v = v ? pick_tile_f32(M, N, K) : TILE_AUTO;
-  const int tile_d = d ? pick_tile_dw_f32(d->M, d->N, tile_v, true) : TILE_AUTO;
-  if (v && d && M > 0 && N > 0 && d->M > 0 && d->N > 0 && d->db) {
+// A layer in two pieces: the pre-activation and its activation again (gemm_fwd_again, the tile and bits of Phase I),
+// and ct_z = h P^T with the cotangent of the layer's output, which needs the stored signs only. The second is a
+// product on split operands and shares its launch with the previous layer's weight gradient.
+template <class CfgV, bool RELU, class CfgD>
+static hipError_t apart_t(int M, int N, int K, const VijpArgs& a, const DwArgs& d, const EpiCotangent<RELU>& epi, hipStream_t stream) {
+  auto tv = make_gemm_task<CfgV, KCONTIG, KCONTIG, true, ANone, EpiCotangent<RELU>, false>(M, N, K, a.Hin, K, a.P, K, ANone{}, epi,
+                                                                                          nullptr, 0.f);
+  auto td = make_gemm_task<CfgD, RCONTIG, RCONTIG, true, ANone, EpiStore, true>(d.M, d.N, d.K, d.CTZ, d.M, d.X, d.N, ANone{},
+                                                                               EpiStore{d.dW, d.N, d.scale, d.beta, nullptr}, d.db, d.scale);
+  td.colsum_beta = d.beta;
+  return launch_task_pair<CfgV::NT>(tv, td, stream);
+}
+
+template <class CfgV, bool RELU>
+static hipError_t apart_d(int tile_d, int M, int N, int K, const VijpArgs& a, const DwArgs& d, const EpiCotangent<RELU>& epi,
+                          hipStream_t stream) {
+  if (tile_d == TILE_S256) return apart_t<CfgV, RELU, Split256>(M, N, K, a, d, epi, stream);
+  if (tile_d == TILE_S128) return apart_t<CfgV, RELU, Split128>(M, N, K, a, d, epi, stream);
+  return apart_t<CfgV, RELU, Split64>(M, N, K, a, d, epi, stream);
+}
+
+template <bool RELU>
+static hipError_t phase3_apart(int tile_v, int tile_d, const VijpArgs& a, int M, int N, int K, const DwArgs* d, hipStream_t stream) {
+  hipError_t e = gemm_fwd_again(pick_tile_f32(M, N, K), M, N, K, a.X, a.W, a.bias, a.alpha, a.Xout, a.mask, a.mismatches, stream);
+  if (e != hipSuccess) return e;
+  const EpiCotangent<RELU> epi{a.alpha > 0.f ? 1.0f / a.alpha : 0.f, a.mask, a.offsets, a.frag, a.frag_base, a.frag_capacity, a.Hout, a.CTZ};
+  if (d && tile_is_split(tile_d) && d->db && operand_vec_ok(a.Hin, K, K) && operand_vec_ok(a.P, K, K) &&
+      operand_vec_ok(d->CTZ, d->M, d->M) && operand_vec_ok(d->X, d->N, d->N) && extent_ok(M, K, K) && extent_ok(N, K, K) &&
+      extent_ok(M, N, N) && extent_ok(d->K, d->M, d->M) && extent_ok(d->K, d->N, d->N) && extent_ok(d->M, d->N, d->N)) {
+    if (tile_v == TILE_S128) return apart_d<Split128, RELU>(tile_d, M, N, K, a, *d, epi, stream);
+    if (tile_v == TILE_S64) return apart_d<Split64, RELU>(tile_d, M, N, K, a, *d, epi, stream);
+  }
+  e = tile_v == TILE_S128 ? launch_gemm<Split128, KCONTIG, KCONTIG, ANone, EpiCotangent<RELU>, false>(M, N, K, a.Hin, K, a.P, K, ANone{}, epi, true,
+                                                                                                     nullptr, 0.f, stream, 0.f)
+                          : launch_gemm<Split64, KCONTIG, KCONTIG, ANone, EpiCotangent<RELU>, false>(M, N, K, a.Hin, K, a.P, K, ANone{}, epi, true,
+                                                                                                    nullptr, 0.f, stream, 0.f);
+  if (e != hipSuccess || !d) return e;
+  return gemm_dw(tile_d, d->M, d->N, d->K, d->CTZ, d->X, d->scale, d->dW, d->db, stream, d->beta);
+}
+
+hipError_t gemm_phase3_pair(int tile_v, const VijpArgs* v, int M, int N, int K, const DwArgs* d, int tile_d, hipStream_t stream) {
+  if (v && tile_is_split(tile_v))
+    return v->alpha == 0.f ? phase3_apart<true>(tile_v, tile_d, *v, M, N, K, d, stream)
+                           : phase3_apart<false>(tile_v, tile_d, *v, M, N, K, d, stream);
+  if (v && d && !tile_is_split(tile_d) && tile_has_8_waves(tile_v) == tile_has_8_waves(tile_d) && M > 0 && N > 0 && d->M > 0 && d->N > 0 &&
+      d->db) {
     const bool shapes_ok = extent_ok(M, K, K) && extent_ok(N, K, K) && extent_ok(M, N, N) &&
                            extent_ok(d->K, d->M, d->M) && extent_ok(d->K, d->N, d->N) && extent_ok(d->M, d->N, d->N);
     const bool vec = vijp_vec_ok(K, v->X, v->W, v->Hin, v->P) && operand_vec_ok(d->CTZ, d->M, d->M) &&

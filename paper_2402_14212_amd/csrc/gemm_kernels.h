@@ -147,6 +147,130 @@ struct EpiFwdAct {
   };
 };
 
+// Phase III, the activation alone: z = acc + b as in Phase I (same tile, same bits), x = stored sign ? z : alpha z; every
+// recomputed sign is compared with the stored phase-I bit and differences are counted.
+struct EpiFwdAgain {
+  float* X;
+  const float* bias;
+  float alpha;
+  const uint32_t* mask32;
+  unsigned long long* mismatches;
+  struct Dev {
+    __amdgpu_buffer_rsrc_t rx, rbias, rmask;
+    float alpha;
+    bool bias;
+    unsigned long long* mismatches;
+    uint32_t mism;
+    __device__ __forceinline__ Dev(const EpiFwdAgain& p, int M, int N)
+        : alpha(p.alpha), bias(p.bias != nullptr), mismatches(p.mismatches), mism(0) {
+      rx = make_rsrc(p.X, extent_bytes(M, N, N));
+      rbias = make_rsrc(p.bias, p.bias ? (uint32_t)N * 4u : 0u);
+      rmask = make_rsrc(p.mask32, (uint32_t)(((int64_t)M * N + 63) / 64) * 8u);
+    }
+    __device__ __forceinline__ void finish() const {
+      if (mism) atomicAdd(mismatches, (unsigned long long)mism);
+    }
+    template <int CNT>
+    __device__ __forceinline__ void part(int M, int N, int row_base, int col, int g, int i0, const float (&v)[1][CNT]) {
+      const bool cv = col < N;
+      const float bv = buf_load_f32(rbias, (bias && cv) ? (uint32_t)col * 4u : OOB);
+      uint32_t e[CNT], word[CNT];
+#pragma unroll
+      for (int j = 0; j < CNT; ++j) {
+        const int row = row_base + acc_row(i0 + j, g);
+        const bool valid = cv && row < M;
+        e[j] = valid ? (uint32_t)row * (uint32_t)N + (uint32_t)col : OOB;
+        word[j] = buf_load_u32(rmask, valid ? (e[j] >> 5) * 4u : OOB);
+      }
+#pragma unroll
+      for (int j = 0; j < CNT; ++j) {
+        const bool valid = e[j] != OOB;
+        float z = v[0][j];
+        if (bias) z += bv;
+        const bool stored = (word[j] >> (e[j] & 31u)) & 1u;
+        if (valid && (z > 0.f) != stored) ++mism;
+        buf_store_f32(rx, valid ? e[j] * 4u : OOB, stored ? z : alpha * z);
+      }
+    }
+  };
+};
+
+// Phase III, the cotangents alone: acc = h_{i-1} P^T. The stored sign selects the slope to undo.
+//   leaky: h_y = m ? ct_z : ct_z * (1/alpha).
+//   ReLU : ct_z zeroed where erased; h_y restored from the fragment store (see EpiVijp).
+template <bool RELU>
+struct EpiCotangent {
+  float inv_alpha;
+  const uint64_t* mask;
+  const uint32_t* offsets;     // ReLU only
+  const float* frag;           // ReLU only: start of the whole store
+  const uint64_t* frag_base;   // ReLU only: device scalar, start of this layer in the store
+  uint64_t frag_capacity;
+  float* H;
+  float* CTZ;
+  struct Dev {
+    __amdgpu_buffer_rsrc_t rmask, roff, rfrag, rh, rc;
+    float inv_alpha;
+    __device__ __forceinline__ Dev(const EpiCotangent& p, int M, int N) : inv_alpha(p.inv_alpha) {
+      const uint32_t words = (uint32_t)(((int64_t)M * N + 63) / 64);
+      rmask = make_rsrc(p.mask, words * 8u);
+      roff = make_rsrc(p.offsets, RELU ? (words + 1u) * 4u : 0u);
+      uint64_t base = RELU ? *p.frag_base : 0ull;
+      uint64_t room = (RELU && base < p.frag_capacity) ? p.frag_capacity - base : 0ull;
+      if (room > 0x1FFFFFFFull) room = 0x1FFFFFFFull;
+      rfrag = make_rsrc(RELU ? p.frag + base : nullptr, (uint32_t)room * 4u);
+      rh = make_rsrc(p.H, extent_bytes(M, N, N));
+      rc = make_rsrc(p.CTZ, extent_bytes(M, N, N));
+    }
+    __device__ __forceinline__ void finish() const {}
+    template <int CNT>
+    __device__ __forceinline__ void part(int M, int N, int row_base, int col, int g, int i0, const float (&v)[1][CNT]) const {
+      const bool cv = col < N;
+      uint32_t e[CNT], lo[CNT], hi[CNT], rank0[CNT];
+#pragma unroll
+      for (int j = 0; j < CNT; ++j) {
+        const int row = row_base + acc_row(i0 + j, g);
+        const bool valid = cv && row < M;
+        e[j] = valid ? (uint32_t)row * (uint32_t)N + (uint32_t)col : OOB;
+        if (RELU) {
+          const uint32_t w = e[j] >> 6;
+          lo[j] = buf_load_u32(rmask, valid ? w * 8u : OOB);
+          hi[j] = buf_load_u32(rmask, valid ? w * 8u + 4u : OOB);
+          rank0[j] = buf_load_u32(roff, valid ? w * 4u : OOB);
+        } else {
+          lo[j] = buf_load_u32(rmask, valid ? (e[j] >> 5) * 4u : OOB);
+        }
+      }
+      float restored[CNT];
+      bool stored[CNT];
+#pragma unroll
+      for (int j = 0; j < CNT; ++j) {
+        if (RELU) {
+          const uint64_t w = ((uint64_t)hi[j] << 32) | lo[j];
+          const uint32_t sh = e[j] & 63u;
+          stored[j] = (w >> sh) & 1ull;
+          const uint32_t idx = rank0[j] + (uint32_t)__popcll(~w & ((1ull << sh) - 1ull));
+          restored[j] = buf_load_f32(rfrag, (e[j] != OOB && !stored[j]) ? idx * 4u : OOB);
+        } else {
+          stored[j] = (lo[j] >> (e[j] & 31u)) & 1u;
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < CNT; ++j) {
+        const uint32_t off = e[j] != OOB ? e[j] * 4u : OOB;
+        const float c = v[0][j];
+        if (RELU) {
+          buf_store_f32(rh, off, stored[j] ? c : restored[j]);
+          buf_store_f32(rc, off, stored[j] ? c : 0.f);
+        } else {
+          buf_store_f32(rh, off, stored[j] ? c : c * inv_alpha);
+          buf_store_f32(rc, off, c);
+        }
+      }
+    }
+  };
+};
+
 // Phase-III epilogue for one layer. v[0] = x_{i-1} W^T (pre-bias), v[1] = h_{i-1} P^T.
 //   leaky: m = (z > 0) recomputed; h_y = m ? ct_z : ct_z * (1/alpha).
 //   ReLU : m = stored bit; ct_z zeroed where erased; h_y restored from the fragment store at

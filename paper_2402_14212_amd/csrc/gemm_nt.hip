@@ -20,4 +20,10 @@ hipError_t gemm_fwd_act(int tile, int M, int N, int K, const float* X, const flo
   return dispatch_gemm<KCONTIG, KCONTIG, false, TILES_F32>(tile, M, N, K, X, K, W, K, ANone{}, epi, true, nullptr, 0.f, stream);
 }
 
+hipError_t gemm_fwd_again(int tile, int M, int N, int K, const float* X, const float* W, const float* bias, float alpha, float* Xout,
+                          const uint64_t* mask, unsigned long long* mismatches, hipStream_t stream) {
+  EpiFwdAgain epi{Xout, bias, alpha, reinterpret_cast<const uint32_t*>(mask), mismatches};
+  return dispatch_gemm<KCONTIG, KCONTIG, false, TILES_F32>(tile, M, N, K, X, K, W, K, ANone{}, epi, true, nullptr, 0.f, stream);
+}
+
 }  // namespace mw

@@ -74,11 +74,30 @@ int pick_tile_tn(int M, int N, int K) {
   return split_pays(1, M, N, K) ? pick_split_tile(1, M, N, true) : pick_tile_f32(M, N, K);
 }
 
+// Where one layer's 64 x 64 tiles fill the chip, the cotangent product of Phase III goes by itself on split operands
+// (us a layer with its weight gradient at 512 x 2048 x 2048: 42 for the activation and 60 for the rest, 117 in one
+// kernel; 1024 x 4096 x 4096: 267 and 240, 790). Smaller layers keep the one kernel for both products, whose launches
+// are fewer and can be grouped over stretches.
+int phase3_tile(int M, int N, int K, bool split) {
+  return split && K >= SPLIT_MIN_K && tiles_of(M, N, 64, 64) >= 192 ? pick_split_tile(1, M, N, false)
+                                                                   : pick_tile_f32(M, N, K);
+}
+
 int pick_tile_dw_f32(int M, int N, int partner, bool phase3) {
   // eight wavefronts: beside a layer kernel the 128x128 tile (few, long workgroups on both sides
   // share the CUs evenly), beside the single reverse product the 64x128 one
   if (tile_has_8_waves(partner)) return phase3 ? TILE_128W8 : TILE_64X128;
   return tiles_of(M, N, 128, 128) >= 512 ? TILE_128 : TILE_64;
+}
+
+// Split where the layer's own kernel is (one that runs in groups over stretches keeps the fp32 tile of those), and for
+// a first layer of few inputs beside a split kernel. It depends on the layers' shapes alone: launched together with the
+// next layer's kernel or apart, a product gets the same tile and therefore the same bits.
+int phase3_dw_tile(int B, int d_out, int d_in, int next_out, bool split) {
+  const int partner = next_out > 0 ? phase3_tile(B, next_out, d_out, split) : TILE_AUTO;
+  if (tile_is_split(phase3_tile(B, d_out, d_in, split)) || (d_in < SPLIT_MIN_K && tile_is_split(partner)))
+    return pick_split_tile(1, d_out, d_in, true);
+  return pick_tile_dw_f32(d_out, d_in, partner, true);
 }
 
 int bp_dw_tile(int d_out, int d_in, int B, int partner) {
@@ -790,9 +809,11 @@ int phase3_range(const Step& c, int lo, int hi, const float* xin, const float* h
     float* xrot[3] = {h->xa, h->xb, h->xc};
     float* crot[2] = {h->ctz, h->ctz2};
     DwArgs pending{};
+    int pending_tile = TILE_AUTO;
     bool have_pending = false;
     for (int i = lo; i < hi; ++i) {
       Layer& l = h->layers[i];
+      const int tile_d = phase3_dw_tile(B, l.d_out, l.d_in, i + 1 < h->L ? h->layers[i + 1].d_out : 0, c.split());
       if (i > lo && h->layers[i - 1].ckpt) hin = h->layers[i - 1].ckpt;  // re-seed
       float* xout = xrot[i % 3];
       float* ctz = crot[i & 1];
@@ -811,20 +832,18 @@ int phase3_range(const Step& c, int lo, int hi, const float* xin, const float* h
         d.db = c.grads_out + l.db_off;
       }
       if (paired) {
-        MW_LAUNCH(h, s, MW_KCLASS_PHASE3, gemm_phase3_pair(&a, B, l.d_out, l.d_in, have_pending ? &pending : nullptr, s));
+        MW_LAUNCH(h, s, MW_KCLASS_PHASE3, gemm_phase3_pair(phase3_tile(B, l.d_out, l.d_in, c.split()), &a, B, l.d_out, l.d_in, have_pending ? &pending : nullptr, pending_tile, s));
         pending = d;
+        pending_tile = tile_d;
         have_pending = true;
       } else {
-        // same tiles as in the paired launches: the weight gradient's follows the next layer's kernel
-        const int partner = (i + 1 < hi) ? pick_tile_f32(B, h->layers[i + 1].d_out, h->layers[i + 1].d_in) : TILE_AUTO;
-        MW_LAUNCH(h, s, MW_KCLASS_VIJP, gemm_vijp_dual(TILE_AUTO, B, l.d_out, l.d_in, a, s));
-        MW_LAUNCH(h, s, MW_KCLASS_DW, gemm_dw(pick_tile_dw_f32(d.M, d.N, partner, true), d.M, d.N, d.K, d.CTZ, d.X, d.scale,
-                                              d.dW, d.db, s, d.beta));
+        MW_LAUNCH(h, s, MW_KCLASS_VIJP, gemm_phase3_pair(phase3_tile(B, l.d_out, l.d_in, c.split()), &a, B, l.d_out, l.d_in, nullptr, TILE_AUTO, s));
+        MW_LAUNCH(h, s, MW_KCLASS_DW, gemm_dw(tile_d, d.M, d.N, d.K, d.CTZ, d.X, d.scale, d.dW, d.db, s, d.beta));
       }
       xin = xout;
       hin = hout;
     }
-    if (have_pending) MW_LAUNCH(h, s, MW_KCLASS_PHASE3, gemm_phase3_pair(nullptr, 0, 0, 0, &pending, s));
+    if (have_pending) MW_LAUNCH(h, s, MW_KCLASS_PHASE3, gemm_phase3_pair(TILE_AUTO, nullptr, 0, 0, 0, &pending, pending_tile, s));
   } else {
     for (int i = lo; i < hi; ++i) {
       Layer& l = h->layers[i];
@@ -832,15 +851,15 @@ int phase3_range(const Step& c, int lo, int hi, const float* xin, const float* h
       float* xout = xbuf[i & 1];
       float* hout = l.dbg_h3 ? l.dbg_h3 : hbuf[i & 1];
       const bool relu = (l.alpha == 0.f);
-      MW_LAUNCH(h, s, MW_KCLASS_FWD, gemm_plain(OP_NT, pick_tile_f32(B, l.d_out, l.d_in), B, l.d_out, l.d_in, 1.f, xin, l.d_in, l.W, l.d_in, 0.f, h->zbuf, l.d_out,
-                        l.b, s));
-      MW_LAUNCH(h, s, MW_KCLASS_FWD, gemm_plain(OP_NT, pick_tile_f32(B, l.d_out, l.d_in), B, l.d_out, l.d_in, 1.f, hin, l.d_in, l.P, l.d_in, 0.f, h->ctz, l.d_out,
-                        nullptr, s));
+      MW_LAUNCH(h, s, MW_KCLASS_FWD, gemm_plain(OP_NT, pick_tile_f32(B, l.d_out, l.d_in), B, l.d_out, l.d_in, 1.f, xin, l.d_in, l.W,
+                                                l.d_in, 0.f, h->zbuf, l.d_out, l.b, s));
+      MW_LAUNCH(h, s, MW_KCLASS_FWD, gemm_plain(OP_NT, phase3_tile(B, l.d_out, l.d_in, c.split()), B, l.d_out, l.d_in, 1.f, hin, l.d_in,
+                                                l.P, l.d_in, 0.f, h->ctz, l.d_out, nullptr, s));
       MW_LAUNCH(h, s, MW_KCLASS_EW, ew_vijp_epilogue(h->zbuf, h->ctz, B, l.d_out, l.alpha, l.mask, l.offsets, h->frag,
                               relu ? h->frag_bases + l.relu_slot : nullptr, h->frag_capacity, xout, hout, mismatches,
                               s));
-      const int partner = (i + 1 < hi) ? pick_tile_f32(B, h->layers[i + 1].d_out, h->layers[i + 1].d_in) : TILE_AUTO;
-      MW_LAUNCH(h, s, MW_KCLASS_DW, gemm_dw(pick_tile_dw_f32(l.d_out, l.d_in, partner, true), l.d_out, l.d_in, B, h->ctz, xin, inv_scale,
+      const int tile_d = phase3_dw_tile(B, l.d_out, l.d_in, i + 1 < h->L ? h->layers[i + 1].d_out : 0, c.split());
+      MW_LAUNCH(h, s, MW_KCLASS_DW, gemm_dw(tile_d, l.d_out, l.d_in, B, h->ctz, xin, inv_scale,
                                             c.grads_out + l.dW_off, nullptr, s));
       MW_LAUNCH(h, s, MW_KCLASS_EW, ew_colsum(h->ctz, B, l.d_out, inv_scale, c.grads_out + l.db_off, s));
       xin = xout;

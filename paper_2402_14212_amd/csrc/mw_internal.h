@@ -27,6 +27,12 @@ int pick_split_tile(int64_t sets, int M, int N, bool s256);
 // the same among the tiles on fp32 matrix instructions: every product that computes pre-activations takes it, so that
 // Phase I and Phase III get the same bits
 int pick_tile_f32(int M, int N, int K);
+// tile of a layer's kernel in Phase III: a split tile (of the cotangent product; the activation is then recomputed by
+// a launch of its own; only if `split`), or pick_tile_f32's for both products in one kernel
+int phase3_tile(int M, int N, int K, bool split);
+// tile of a layer's weight gradient in Phase III; next_out: width of the layer after the next boundary (0: last
+// layer), whose kernel shares the launch
+int phase3_dw_tile(int B, int d_out, int d_in, int next_out, bool split);
 // fp32 tile of a weight-gradient product launched beside a kernel of tile `partner` (TILE_AUTO: alone), which is a
 // Phase-III layer kernel (phase3) or backprop's reverse product
 int pick_tile_dw_f32(int M, int N, int partner, bool phase3);
@@ -52,6 +58,10 @@ hipError_t gemm_plain(int op, int tile, int M, int N, int K, float alpha, const 
 // then requires N % 32 == 0. Zkeep (may be NULL; a debugging aid) receives the pre-activations.
 hipError_t gemm_fwd_act(int tile, int M, int N, int K, const float* X, const float* W, const float* bias,
                         float alpha, float* Xout, uint64_t* mask, hipStream_t stream, float* Zkeep = nullptr);
+
+// Phase III, the activation alone: Xout = act(X W^T + bias) with the stored signs, the recomputed ones checked against them
+hipError_t gemm_fwd_again(int tile, int M, int N, int K, const float* X, const float* W, const float* bias, float alpha, float* Xout,
+                          const uint64_t* mask, unsigned long long* mismatches, hipStream_t stream);
 
 // Phase-II product with the NEXT step's slope folded into the epilogue:
 //   h = CTin[M][K] W[K][N];  CT = h .* slope(mask, alpha)  (mask/alpha of the layer whose OUTPUT h is);
@@ -111,7 +121,8 @@ struct DwArgs {
   float* db;            // [M] or NULL
   float beta = 0.f;     // dW = scale * product + beta * dW (same for db): 1 applies an update in place
 };
-hipError_t gemm_phase3_pair(const VijpArgs* v, int M, int N, int K, const DwArgs* d, hipStream_t stream);
+// tile_v, tile_d: phase3_tile's and phase3_dw_tile's.
+hipError_t gemm_phase3_pair(int tile_v, const VijpArgs* v, int M, int N, int K, const DwArgs* d, int tile_d, hipStream_t stream);
 
 // Phase III for several independent stretches of the network in one launch: n_v layer kernels of one shape
 // (M x N x K each, the same alpha) and n_d weight-gradient products of one shape (the same scale and beta; a

@@ -12,6 +12,11 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import moonwalk_oracle as O
+from workloads import make_mlp
+
+from parity import check_moonwalk
+
 pytestmark = pytest.mark.gpu
 
 NT, NN, TN = 0, 1, 2
@@ -129,3 +134,25 @@ def test_no_less_precise_than_fp32_instructions(mw, op, K):
     split, f32 = (np.linalg.norm(product(mw, op, A, B, tile=t) - ref) / np.linalg.norm(ref) for t in (0, mw.TILE_64))
     print("K=%d normwise error: split %.3g, fp32 instructions %.3g" % (K, split, f32), flush=True)
     assert split <= f32
+
+
+@pytest.mark.parametrize("widths,alphas", [
+    ((1152, 1024, 1024, 192), (0.3, 0.3, 0.3)),     # 64 x 64 tiles; the last layer is too small for split operands
+    ((1029, 1027, 1025), (0.3, 0.3)),               # element-wise loads: every product in a launch of its own
+    ((96, 96), (0.3,)),                             # all of it below
+    ((1088, 1056, 1024), (0.0, 0.0)),               # the fragment store restored in the cotangent's launch
+    ((2176, 2112), (0.3,)),                         # 128 x 128 tiles
+])
+def test_phase3_in_two_launches(mw, widths, alphas):
+    """The activation and the cotangent of a layer in launches of their own: against the oracle on the same signs, and
+    with the same bits as the unfused path."""
+    wl = make_mlp(list(widths), 776, list(alphas), seed=3, reseed_interval=0, name="split")
+    nets = [mw.MoonwalkNet.from_workload(wl, fuse=f) for f in (True, False)]
+    res = [net.moonwalk_grad(net.x, net.t) for net in nets]
+    torch.cuda.synchronize()
+    check_moonwalk(nets[0], wl, res[0])
+    for i in range(wl.depth):
+        assert torch.equal(res[0].dW[i], res[1].dW[i]), i
+        assert O.normwise_rel_err(res[0].db[i].cpu().numpy(), res[1].db[i].cpu().numpy()) < 1e-5
+    for net in nets:
+        net.close()
