@@ -94,16 +94,18 @@ struct AConvPatch {
       ox = rem - oy * (uint32_t)g.Wo;
     }
 
-    template <int LAYOUT, int R, int BK, int NT>
+    static constexpr bool GATHERED = true;
+
+    template <int LAYOUT, int R, int BK, int NT, int KP = 1>
     __device__ __forceinline__ void prepare(int row0, int n_rows, int n_k) {
+      using Map = ChunkMap<LAYOUT, R, BK, NT, KP>;
       constexpr int NV = R * BK / 4 / NT;
       static_assert(NV <= MAX_CHUNKS, "tile shape has more chunks per thread than the gather keeps state for");
       k_left = n_k;
       if (LAYOUT == KCONTIG) {
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
-          const int f = (int)threadIdx.x + i * NT;
-          const int row = row0 + f / (BK / 4), kk = 4 * (f % (BK / 4));
+          const int row = row0 + Map::row(i), kk = Map::k(i);
           uint32_t b, oy, ox;
           split_row((uint32_t)(row + row_off), b, oy, ox);
           fterm[i] = row_term(b, oy, ox) + (uint32_t)kk;
@@ -115,11 +117,10 @@ struct AConvPatch {
       } else {
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
-          const int f = (int)threadIdx.x + i * NT;
-          const int col = row0 + 4 * (f % (R / 4));
+          const int col = row0 + Map::row(i);
           const uint32_t tap = g.d_csel.div((uint32_t)col), c = (uint32_t)col - tap * (uint32_t)g.Csel;
           const uint32_t ty = g.d_kw.div(tap), tx = tap - ty * (uint32_t)g.kw;
-          rr[i] = f / (R / 4);
+          rr[i] = Map::k(i);
           // the displacement of rr rows: whole images, whole output rows, columns
           uint32_t db, dyy, dxx;
           split_row((uint32_t)rr[i], db, dyy, dxx);
@@ -159,6 +160,40 @@ struct AConvPatch {
             ++b0;
           }
         }
+        tterm = row_term(b0, oy0, ox0);
+      }
+    }
+
+    // For one tile request after prepare: move to a K tile that is not in the padding. Columns along K: the tap that
+    // reads the output position itself, or, on a diagonal (whose last tap is left out), the one before the last. Rows along K: the middle of the first
+    // image's output grid (rows beyond the images read nothing: they lie outside the buffer).
+    template <int LAYOUT, int BK>
+    __device__ __forceinline__ void seek_sample() {
+      if (LAYOUT == KCONTIG) {
+        ky = g.py < 0 ? 0 : (g.py < g.kh ? g.py : g.kh - 1);
+        kx = g.px < 0 ? 0 : (g.px < g.kw ? g.px : g.kw - 1);
+        if (g.xdiag) {
+          ky = g.kh - 1;
+          kx = g.kw > 1 ? g.kw - 2 : 0;
+        }
+        tterm = (uint32_t)g.c0 + (uint32_t)((ky * g.W + kx) * g.C);
+      } else {
+        oy0 = (uint32_t)g.Ho / 2;
+        ox0 = (uint32_t)g.Wo / 2;
+        tterm = row_term(b0, oy0, ox0);
+        const int k = k_left;
+        k_left = BK;
+        ky = k;   // (not used with rows along K: keeps the count for unseek)
+      }
+    }
+    template <int LAYOUT>
+    __device__ __forceinline__ void unseek() {
+      if (LAYOUT == KCONTIG) {
+        ky = 0; kx = 0; cb = 0;
+        tterm = (uint32_t)g.c0;
+      } else {
+        k_left = ky;
+        split_row((uint32_t)row_off, b0, oy0, ox0);
         tterm = row_term(b0, oy0, ox0);
       }
     }
@@ -272,26 +307,14 @@ struct SplitKTnTask {
     const int m0 = (tile % tiles_m) * Cfg::BM, n0 = (tile / tiles_m) * Cfg::BN;
     const int k_lo = slice * k_per;
     const int k_n = (K - k_lo) < k_per ? (K - k_lo) : k_per;
-
-    f32x16 acc[1][Cfg::NACC];
-    float asum[Cfg::WTM];
-#pragma unroll
-    for (int a = 0; a < Cfg::NACC; ++a)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[0][a][i] = 0.f;
-#pragma unroll
-    for (int t = 0; t < Cfg::WTM; ++t) asum[t] = 0.f;
-    {
-      typename Xf::Dev xd(xf, k_n, M, lda);
-      const float* a = A;
-      if constexpr (GATHER) xd.row_off += k_lo;
-      else a += (int64_t)k_lo * lda;
-      gemm_mainloop<Cfg, RCONTIG, RCONTIG, true, false>(a, lda, B + (int64_t)k_lo * ldb, ldb, M, N, k_n, m0, n0, lds, xd,
-                                                        acc[0], asum);
-    }
+    typename Xf::Dev xd(xf, k_n, M, lda);
+    const float* a = A;
+    if constexpr (GATHER) xd.row_off += k_lo;
+    else a += (int64_t)k_lo * lda;
     EpiStore es{part + (int64_t)slice * M * N, N, 1.f, 0.f, nullptr};
     EpiStore::Dev ed(es, M, N);
-    reduce_and_finish<Cfg, 1>(lds, M, N, m0, n0, acc, asum, ed);
+    split_product<Cfg, RCONTIG, RCONTIG, true, false>(a, lda, B + (int64_t)k_lo * ldb, ldb, M, N, k_n, m0, n0, lds, xd, ed, nullptr,
+                                                      0.f, 0.f);
   }
 };
 
@@ -422,6 +445,17 @@ struct ConvRevTask {
     int tm_i, tn_i;
     tile_coords(b, rc.tiles_m, tiles_n, tm_i, tn_i);
     const int m0 = tm_i * Cfg::BM, n0 = tn_i * Cfg::BN;
+    if constexpr (is_split<Cfg>()) {
+      AConvPatch::Dev dg(rc.g, rc.M, rc.K, 0);
+      EpiConvRev::Dev ed(epi, rc);
+      split_product<Cfg, KCONTIG, RCONTIG, true, false>(CT, 0, Wrev + rc.w_off, N, rc.M, N, rc.K, m0, n0, lds, dg, ed, nullptr, 0.f,
+                                                        0.f);
+    } else {
+      run_f32(rc, m0, n0, lds);
+    }
+  }
+
+  __device__ __forceinline__ void run_f32(const RevClass& rc, int m0, int n0, float* __restrict__ lds) const {
     f32x16 acc[1][Cfg::NACC];
     float asum[Cfg::WTM];
 #pragma unroll

@@ -129,18 +129,20 @@ struct DwPlan {
 
 DwPlan plan_dw(int K1, int Cout, int64_t rows) {
   DwPlan p;
-  int bm, bn;
-  if (K1 >= 128 && Cout >= 128) { p.tile = TILE_128W8; bm = 128; bn = 128; }
-  else if (Cout >= 128) { p.tile = TILE_64X128; bm = 64; bn = 128; }
-  else { p.tile = TILE_64; bm = 64; bn = 64; }
-  const int64_t tiles = (int64_t)ceil_div(K1, bm) * ceil_div(Cout, bn);
-  // four workgroups per CU when the rows allow it, never a few more than that (they would run on
-  // their own after all the others), and at least eight K tiles per slice
-  int64_t want = tiles >= 1024 ? 1 : 1024 / tiles;
+  // 128 x 128 where that fills the chip with slices of 256 rows (us for 3264 rows, 288 x 96: 128 x 128 16.0 in 39
+  // workgroups, 64 x 64 on fp32 instructions 11.1)
+  const int64_t tiles128 = (int64_t)ceil_div(K1, 128) * ceil_div(Cout, 128);
+  const int t = (K1 > 64 && Cout > 64 && rows * tiles128 >= 256 * 256) ? 128 : 64;
+  p.tile = t == 128 ? TILE_S128 : TILE_S64;
+  const int64_t tiles = (int64_t)ceil_div(K1, t) * ceil_div(Cout, t);
+  // one round of workgroups (two of the small tile) when the rows allow it, never a few more than that (they would
+  // run on their own after all the others), and at least 256 rows per slice
+  const int64_t room = t == 128 ? 256 : 512;
+  int64_t want = tiles >= room ? 1 : room / tiles;
   if (want > CONV_DW_MAX_SLICES) want = CONV_DW_MAX_SLICES;
   int64_t k_per = (rows + want - 1) / want;
   if (k_per < 256) k_per = 256;
-  k_per = (k_per + 31) / 32 * 32;
+  k_per = (k_per + 63) / 64 * 64;
   p.k_per = (int)k_per;
   p.slices = (int)((rows + k_per - 1) / k_per);
   if (p.slices < 1) p.slices = 1;
@@ -156,12 +158,27 @@ hipError_t dw_t(const ConvGeom& g, int n_img, const float* x, const float* ctz, 
   return launch_task<Cfg::NT>(t, stream);
 }
 
-// The tile for a product whose K runs over (tap, channel) with csel channels per tap: what pick_tile_f32
-// says, unless that tile's K step would straddle taps; then the 64 x 64 tile, whose K step is 32.
-int gather_tile(int M, int N, int K, int csel_a, int csel_b) {
+// The fp32 tile for a product whose K runs over (tap, channel) with csel channels per tap (a multiple of 32; csel_b: of
+// the layer's second product): what pick_tile_f32 says, unless that tile's K step would straddle taps; then the 64 x 64
+// tile, whose K step is 32. Pre-activations take it always (see pick_tile_f32).
+int gather_tile_f32(int M, int N, int K, int csel_a, int csel_b) {
   const int t = pick_tile_f32(M, N, K);
   const int bk = t == TILE_64K2 ? 64 : (t == TILE_32K4 ? 128 : 32);
   return (csel_a % bk == 0 && csel_b % bk == 0) ? t : TILE_64;
+}
+
+// The same for products that may take split operands, `sets` of them with k_sum of K altogether. They pay from 256 of K
+// on (us at 13 ... 30 thousand rows of each of the four classes of a stride-2 input cotangent, 64 channels: 3 x 3, K
+// 144 on average, 59 against 39 with fp32 tiles; 5 x 5, K 400, 100 against 155), because a split tile starts with a
+// sample and ends with an exchange between its K groups.
+int gather_tile(int M, int N, int K, int csel, int sets, int k_sum) {
+  if (k_sum / sets < 256) return gather_tile_f32(M, N, K, csel, csel);
+  if (!split_pays(sets, M, N, K)) return gather_tile_f32(M, N, K, csel, csel);
+  const int t = pick_split_tile(sets, M, N, false);
+  if (t != TILE_S64 || csel % Split64::BK == 0) return t;
+  // channels that are no multiple of 64: four wavefronts and a K tile of 32 (us for 3264 rows of 96 channels, 102
+  // tiles: 15.2 against 13.2 with fp32 tiles; 40560 rows of 32, 634 tiles: 50 against 95)
+  return sets * ceil_div(M, 64) * ceil_div(N, 64) >= 256 ? TILE_S64Q : gather_tile_f32(M, N, K, csel, csel);
 }
 
 }  // namespace
@@ -182,7 +199,7 @@ hipError_t conv_fwd_act(const ConvGeom& g, int n_img, const float* x, const floa
                         float* xout, uint32_t* mask32, hipStream_t stream) {
   if (n_img <= 0) return hipSuccess;
   const int M = n_img * g.Ho * g.Wo, K1 = g.taps() * g.C;
-  switch (gather_tile(M, Cout, K1, g.C, Cout)) {
+  switch (gather_tile_f32(M, Cout, K1, g.C, Cout)) {
     case TILE_128W8: return fwd_m<Tile128W8>(g, n_img, x, w, b, alpha, Cout, xout, mask32, stream);
     case TILE_64X128: return fwd_m<Tile64x128>(g, n_img, x, w, b, alpha, Cout, xout, mask32, stream);
     case TILE_64K2: return fwd_m<Tile64K2>(g, n_img, x, w, b, alpha, Cout, xout, mask32, stream);
@@ -199,7 +216,7 @@ hipError_t conv_vijp_given(const ConvGeom& g, int n_img, const float* x, const f
   EpiVijpGiven epi{EpiVijp<false>{b, alpha, 1.0f / alpha, reinterpret_cast<const uint64_t*>(mask32), nullptr, nullptr, nullptr, 0,
                                   xout, hout, nullptr, mismatches},
                    ctz};
-  switch (gather_tile(M, Cout, K1, g.C, Cout)) {  // the tile of conv_fwd_act: the recomputed signs must match bit for bit
+  switch (gather_tile_f32(M, Cout, K1, g.C, Cout)) {  // the tile of conv_fwd_act: the recomputed signs must match bit for bit
     case TILE_128W8: return fwd_given_t<Tile128W8>(g, n_img, x, w, Cout, epi, stream);
     case TILE_64X128: return fwd_given_t<Tile64x128>(g, n_img, x, w, Cout, epi, stream);
     case TILE_64K2: return fwd_given_t<Tile64K2>(g, n_img, x, w, Cout, epi, stream);
@@ -216,7 +233,7 @@ hipError_t conv_vijp_layer(const ConvGeom& g, int n_img, const float* x, const f
   // the leaky path of the epilogue reads the mask as 32-bit words, so a 4-byte aligned start is enough
   EpiVijp<false> epi{b, alpha, 1.0f / alpha, reinterpret_cast<const uint64_t*>(mask32), nullptr, nullptr, nullptr, 0,
                      xout, hout, ctz, mismatches};
-  switch (gather_tile(M, Cout, K1, g.C, Cout)) {  // the tile of conv_fwd_act: the recomputed signs must match bit for bit
+  switch (gather_tile_f32(M, Cout, K1, g.C, Cout)) {  // the tile of conv_fwd_act: the recomputed signs must match bit for bit
     case TILE_128W8: return vijp_t<Tile128W8>(g, n_img, x, w, Cout, hin, hin_as_read, Tinv, epi, stream);
     case TILE_64X128: return vijp_t<Tile64x128>(g, n_img, x, w, Cout, hin, hin_as_read, Tinv, epi, stream);
     case TILE_64K2: return vijp_t<Tile64K2>(g, n_img, x, w, Cout, hin, hin_as_read, Tinv, epi, stream);
@@ -239,10 +256,12 @@ hipError_t sub_solve_t(const ConvGeom& g, int n_img, int Cout, const float* hin,
 hipError_t conv_sub_solve(const ConvGeom& g, int n_img, int Cout, const float* hin, const float* Tinv, float* ct, hipStream_t stream) {
   if (n_img <= 0) return hipSuccess;
   const int M = n_img * g.Ho * g.Wo;
-  switch (gather_tile(M, Cout, Cout, Cout, Cout)) {
+  switch (gather_tile(M, Cout, Cout, Cout, 1, Cout)) {
     case TILE_128W8: return sub_solve_t<Tile128W8>(g, n_img, Cout, hin, Tinv, ct, stream);
     case TILE_64X128: return sub_solve_t<Tile64x128>(g, n_img, Cout, hin, Tinv, ct, stream);
-    case TILE_64K2: return sub_solve_t<Tile64K2>(g, n_img, Cout, hin, Tinv, ct, stream);
+    case TILE_S128: return sub_solve_t<Split128>(g, n_img, Cout, hin, Tinv, ct, stream);
+    case TILE_S64: return sub_solve_t<Split64>(g, n_img, Cout, hin, Tinv, ct, stream);
+    case TILE_S64Q: return sub_solve_t<Split64Q>(g, n_img, Cout, hin, Tinv, ct, stream);
     case TILE_32K4: return sub_solve_t<Tile32K4>(g, n_img, Cout, hin, Tinv, ct, stream);
     default: return sub_solve_t<Tile64>(g, n_img, Cout, hin, Tinv, ct, stream);
   }
@@ -283,10 +302,16 @@ hipError_t conv_vijp_sweep(int Ho, int Wo, int Cout, int n_img, int reach, float
     const int i0 = d - (Wo - 1) > 0 ? d - (Wo - 1) : 0, i1 = d < Ho - 1 ? d : Ho - 1;
     const int M = n_img * (i1 - i0 + 1);
     hipError_t e;
-    switch (gather_tile(M, Cout, K, Cout, Cout)) {
+    // a diagonal is one round of few workgroups: the shorter chain of the split 64 x 64 tile counts (us a diagonal of
+    // eight 32 x 32 images, K = 192: 6.5 against 7.1)
+    int tile = gather_tile(M, Cout, K, Cout, 1, K);
+    if (tile == TILE_64 && K >= SPLIT_MIN_K && Cout % Split64::BK == 0) tile = TILE_S64;
+    switch (tile) {
       case TILE_128W8: e = sweep_t<Tile128W8>(Ho, Wo, Cout, n_img, d, reach, ct, Asweep, stream); break;
       case TILE_64X128: e = sweep_t<Tile64x128>(Ho, Wo, Cout, n_img, d, reach, ct, Asweep, stream); break;
-      case TILE_64K2: e = sweep_t<Tile64K2>(Ho, Wo, Cout, n_img, d, reach, ct, Asweep, stream); break;
+      case TILE_S128: e = sweep_t<Split128>(Ho, Wo, Cout, n_img, d, reach, ct, Asweep, stream); break;
+      case TILE_S64: e = sweep_t<Split64>(Ho, Wo, Cout, n_img, d, reach, ct, Asweep, stream); break;
+      case TILE_S64Q: e = sweep_t<Split64Q>(Ho, Wo, Cout, n_img, d, reach, ct, Asweep, stream); break;
       case TILE_32K4: e = sweep_t<Tile32K4>(Ho, Wo, Cout, n_img, d, reach, ct, Asweep, stream); break;
       default: e = sweep_t<Tile64>(Ho, Wo, Cout, n_img, d, reach, ct, Asweep, stream); break;
     }
@@ -306,10 +331,12 @@ hipError_t conv_input_cotangent(const ConvGeom& g, int n_img, int Cout, const fl
   // the tile for the largest class: about a quarter of the input pixels, all taps of that class
   const int M = n_img * ((g.H + g.s - 1) / g.s) * ((g.W + g.s - 1) / g.s);
   const int K = class_taps(g.kh, g.s, 0) * class_taps(g.kw, g.s, 0) * Cout;
-  switch (gather_tile(M, g.C, K, Cout, Cout)) {
+  switch (gather_tile(M, g.C, K, Cout, g.s * g.s, g.taps() * Cout)) {
     case TILE_128W8: return rev_t<Tile128W8>(g, n_img, Cout, ctz, wrev, epi, stream);
     case TILE_64X128: return rev_t<Tile64x128>(g, n_img, Cout, ctz, wrev, epi, stream);
-    case TILE_64K2: return rev_t<Tile64K2>(g, n_img, Cout, ctz, wrev, epi, stream);
+    case TILE_S128: return rev_t<Split128>(g, n_img, Cout, ctz, wrev, epi, stream);
+    case TILE_S64: return rev_t<Split64>(g, n_img, Cout, ctz, wrev, epi, stream);
+    case TILE_S64Q: return rev_t<Split64Q>(g, n_img, Cout, ctz, wrev, epi, stream);
     case TILE_32K4: return rev_t<Tile32K4>(g, n_img, Cout, ctz, wrev, epi, stream);
     default: return rev_t<Tile64>(g, n_img, Cout, ctz, wrev, epi, stream);
   }
@@ -331,12 +358,8 @@ hipError_t conv_dw(const ConvGeom& g, int n_img, const float* x, const float* ct
   if (n_img <= 0) return hipSuccess;
   const int K1 = g.taps() * g.C;
   const DwPlan p = plan_dw(K1, Cout, (int64_t)n_img * g.Ho * g.Wo);
-  hipError_t e;
-  switch (p.tile) {
-    case TILE_128W8: e = dw_t<Tile128W8>(g, n_img, x, ctz, Cout, p, part, stream); break;
-    case TILE_64X128: e = dw_t<Tile64x128>(g, n_img, x, ctz, Cout, p, part, stream); break;
-    default: e = dw_t<Tile64>(g, n_img, x, ctz, Cout, p, part, stream); break;
-  }
+  const hipError_t e = p.tile == TILE_S128 ? dw_t<Split128>(g, n_img, x, ctz, Cout, p, part, stream)
+                                           : dw_t<Split64>(g, n_img, x, ctz, Cout, p, part, stream);
   if (e != hipSuccess) return e;
   return ew_reduce_slices(part, p.slices, (int64_t)K1 * Cout, scale, beta, dW, stream);
 }

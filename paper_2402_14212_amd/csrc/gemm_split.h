@@ -64,6 +64,8 @@ using Split256 = SplitCfg<2, 2, 4, 2, 1, 2>;  // 256 x 128, K tile 32
 using Split128 = SplitCfg<2, 2, 2, 2, 2, 1>;  // 128 x 128, K tile 32, K split over two groups of four wavefronts
 using Split64 = SplitCfg<1, 1, 2, 2, 2, 2>;   //  64 x  64, K tile 64, likewise
 
+using Split64Q = SplitCfg<1, 1, 2, 2, 1, 2>;  // 64 x 64, K tile 32, four wavefronts: gathers of 32 channels and odd multiples
+
 template <class Cfg>
 constexpr bool is_split() { return Cfg::PREC == 2; }
 

@@ -10,7 +10,7 @@ namespace mw {
 // tile selectors (same values as MW_TILE_* in the public header)
 constexpr int TILE_AUTO = 0, TILE_128 = 1, TILE_64 = 2, TILE_32K4 = 3, TILE_32K8 = 4, TILE_64K2 = 5, TILE_128W8 = 6, TILE_64X128 = 7;
 // tiles of the products on split operands (gemm_split.h), chosen by the library only; eight wavefronts each (S64Q: four)
-constexpr int TILE_S256 = 16, TILE_S128 = 17, TILE_S64 = 18;
+constexpr int TILE_S256 = 16, TILE_S128 = 17, TILE_S64 = 18, TILE_S64Q = 19;
 inline bool tile_is_split(int tile) { return tile >= TILE_S256; }
 // least K of a product that takes split operands: below it the product is a few K tiles of launch and memory latency
 constexpr int SPLIT_MIN_K = 128;
