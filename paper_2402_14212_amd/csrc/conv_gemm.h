@@ -165,8 +165,9 @@ struct AConvPatch {
     }
 
     // For one tile request after prepare: move to a K tile that is not in the padding. Columns along K: the tap that
-    // reads the output position itself, or, on a diagonal (whose last tap is left out), the one before the last. Rows along K: the middle of the first
-    // image's output grid (rows beyond the images read nothing: they lie outside the buffer).
+    // reads the output position itself, or, on a diagonal (whose last tap is left out), the one before the last. Rows
+    // along K: the middle of the first image's output grid (rows beyond the images read nothing: they lie outside the
+    // buffer).
     template <int LAYOUT, int BK>
     __device__ __forceinline__ void seek_sample() {
       if (LAYOUT == KCONTIG) {
@@ -183,7 +184,7 @@ struct AConvPatch {
         tterm = row_term(b0, oy0, ox0);
         const int k = k_left;
         k_left = BK;
-        ky = k;   // (not used with rows along K: keeps the count for unseek)
+        ky = k;   // (ky has no use with rows along K: it keeps the count for unseek)
       }
     }
     template <int LAYOUT>

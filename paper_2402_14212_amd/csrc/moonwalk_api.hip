@@ -1059,13 +1059,14 @@ int refresh_one_layer(mw_handle* h, Layer& l, int iters, float* residual_out, hi
     if (cur != l.P) MW_HIP(ew_copy(l.P, cur, (int64_t)n * m, s));
   } else {
     MW_HIP(gemm_plain(OP_NT, TILE_AUTO, n, n, m, 1.f, l.P, m, l.P, m, 0.f, S, n, nullptr, s));
-    MW_HIP(gemm_plain(OP_NN, TILE_AUTO, n, m, n, 1.f, S, n, l.W, m, 0.f, cur, m, nullptr, s));
+    MW_HIP(gemm_plain(OP_NN, pick_tile_f32(n, m, n), n, m, n, 1.f, S, n, l.W, m, 0.f, cur, m, nullptr, s));
   }
   for (int it = 0; it < iters; ++it) {
     MW_HIP(gemm_plain(OP_NT, TILE_AUTO, n, n, m, 1.f, cur, m, l.W, m, 0.f, S, n, nullptr, s));
     if (residual_out && it == iters - 1) MW_HIP(ew_identity_residual(S, n, h->loss_scratch, residual_out, s));
     MW_HIP(ew_copy(cur, other, (int64_t)n * m, s));
-    MW_HIP(gemm_plain(OP_NN, TILE_AUTO, n, m, n, -1.f, S, n, cur, m, 2.f, other, m, nullptr, s));
+    // (fp32 instructions: S is next to the identity, see gemm_grouped)
+    MW_HIP(gemm_plain(OP_NN, pick_tile_f32(n, m, n), n, m, n, -1.f, S, n, cur, m, 2.f, other, m, nullptr, s));
     float* t = cur;
     cur = other;
     other = t;
