@@ -94,8 +94,6 @@ struct AConvPatch {
       ox = rem - oy * (uint32_t)g.Wo;
     }
 
-    static constexpr bool GATHERED = true;
-
     template <int LAYOUT, int R, int BK, int NT, int KP = 1>
     __device__ __forceinline__ void prepare(int row0, int n_rows, int n_k) {
       using Map = ChunkMap<LAYOUT, R, BK, NT, KP>;
@@ -160,41 +158,6 @@ struct AConvPatch {
             ++b0;
           }
         }
-        tterm = row_term(b0, oy0, ox0);
-      }
-    }
-
-    // For one tile request after prepare: move to a K tile that is not in the padding. Columns along K: the tap that
-    // reads the output position itself, or, on a diagonal (whose last tap is left out), the one before the last. Rows
-    // along K: the middle of the first image's output grid (rows beyond the images read nothing: they lie outside the
-    // buffer).
-    template <int LAYOUT, int BK>
-    __device__ __forceinline__ void seek_sample() {
-      if (LAYOUT == KCONTIG) {
-        ky = g.py < 0 ? 0 : (g.py < g.kh ? g.py : g.kh - 1);
-        kx = g.px < 0 ? 0 : (g.px < g.kw ? g.px : g.kw - 1);
-        if (g.xdiag) {
-          ky = g.kh - 1;
-          kx = g.kw > 1 ? g.kw - 2 : 0;
-        }
-        tterm = (uint32_t)g.c0 + (uint32_t)((ky * g.W + kx) * g.C);
-      } else {
-        oy0 = (uint32_t)g.Ho / 2;
-        ox0 = (uint32_t)g.Wo / 2;
-        tterm = row_term(b0, oy0, ox0);
-        const int k = k_left;
-        k_left = BK;
-        ky = k;   // (ky has no use with rows along K: it keeps the count for unseek)
-      }
-    }
-    template <int LAYOUT>
-    __device__ __forceinline__ void unseek() {
-      if (LAYOUT == KCONTIG) {
-        ky = 0; kx = 0; cb = 0;
-        tterm = (uint32_t)g.c0;
-      } else {
-        k_left = ky;
-        split_row((uint32_t)row_off, b0, oy0, ox0);
         tterm = row_term(b0, oy0, ox0);
       }
     }

@@ -161,7 +161,6 @@ struct ALinearDev {
   // Called once by the main loop before the first tile is requested (row0: the tile's first row of
   // the operand; n_rows, n_k: its extents), and once after every tile request, in tile order.
   // KP: see ChunkMap.
-  static constexpr bool GATHERED = false;
   template <int LAYOUT, int R, int BK, int NT, int KP = 1>
   __device__ __forceinline__ void prepare(int /*row0*/, int /*n_rows*/, int /*n_k*/) {}
   template <int LAYOUT, int BK>
