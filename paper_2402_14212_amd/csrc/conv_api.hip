@@ -233,8 +233,9 @@ int frag_rebuild(mw_conv_handle* h, const ConvLayer& l, const float* hin, float*
     float* ct = ctz + r0 * ld_ct;
     const float* hi = hin + r0 * ld_h;
     if (nfrag > 0) CV_HIP(cv_copy_rows(l.frag + r0 * nfrag, nfrag, ct, ld_ct, R, nfrag, s));
-    // (fp32 tiles: a chain of short launches gains nothing from split ones, 1434 against 1437 us a step with three
-    // layers of 8192 blocks of four positions, 256 channels)
+    // (fp32 tiles: the recurrence carries every rounding on to the later positions, and its short launches gain little from
+    // split ones: 1461 and 1460 us a gradient with three layers of 8192 blocks of four positions, 256 channels, 5412 and
+    // 5184 with 32768 blocks)
     for (int j = l.k - 1; j < l.block; ++j) {
       CV_HIP(gemm_plain(OP_NT, pick_tile_f32((int)R, l.Cout, l.Cout), (int)R, l.Cout, l.Cout, 1.f,
                         hi + (int64_t)(j - l.p) * l.Cin, ld_h, l.Tinv, l.Cout, 0.f, ct + (int64_t)j * l.Cout, ld_ct, nullptr, s));

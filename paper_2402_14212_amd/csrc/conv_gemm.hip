@@ -168,17 +168,19 @@ int gather_tile_f32(int M, int N, int K, int csel_a, int csel_b) {
 }
 
 // The same for products that may take split operands, `sets` of them with k_sum of K altogether. They pay from 256 of K
-// on (us at 13 ... 30 thousand rows of each of the four classes of a stride-2 input cotangent, 64 channels: 3 x 3, K
-// 144 on average, 59 against 39 with fp32 tiles; 5 x 5, K 400, 100 against 155), because a split tile starts with a
-// sample and ends with an exchange between its K groups.
+// on (an input cotangent of stride 2 and 128 channels, 3 x 3: 144 of K on average with 64 channels, 288 with 128), and
+// at fewer tiles than a plain product (split_pays), because an fp32 tile with K split would straddle taps. us with fp32
+// tiles and split, input cotangents: 131072 rows of 128 channels, 3 x 3, stride 2 389 and 366, 8192 rows 33 and 36, 2048
+// rows 19.5 and 18.5; 1800 rows of 64 channels, 5 x 5, stride 2 (128 tiles) 23.6 and 18.1, 16820 rows 51.9 and 53.7;
+// 25392 rows of 96 to 128 channels, 5 x 5 183 and 119. Several rounds of 64 x 64 tiles, and channels that are no
+// multiple of 64, take four wavefronts and a K tile of 32, three workgroups to a CU (240000 rows of 64 channels: 173
+// against 207, fp32 320; 40368 rows of 32 channels, 5 x 5: 54, fp32 91).
 int gather_tile(int M, int N, int K, int csel, int sets, int k_sum) {
-  if (k_sum / sets < 256) return gather_tile_f32(M, N, K, csel, csel);
-  if (!split_pays(sets, M, N, K)) return gather_tile_f32(M, N, K, csel, csel);
-  const int t = pick_split_tile(sets, M, N, false);
-  if (t != TILE_S64 || csel % Split64::BK == 0) return t;
-  // channels that are no multiple of 64: four wavefronts and a K tile of 32 (us for 3264 rows of 96 channels, 102
-  // tiles: 15.2 against 13.2 with fp32 tiles; 40560 rows of 32, 634 tiles: 50 against 95)
-  return sets * ceil_div(M, 64) * ceil_div(N, 64) >= 256 ? TILE_S64Q : gather_tile_f32(M, N, K, csel, csel);
+  const int64_t t64 = (int64_t)sets * ceil_div(M, 64) * ceil_div(N, 64);
+  if (k_sum / sets < 256 || t64 < 96) return gather_tile_f32(M, N, K, csel, csel);
+  if (N > 64 && pick_split_tile(sets, M, N, false) == TILE_S128) return TILE_S128;
+  if (t64 <= 256 && csel % Split64::BK == 0) return TILE_S64;
+  return t64 >= 256 ? TILE_S64Q : gather_tile_f32(M, N, K, csel, csel);
 }
 
 }  // namespace
@@ -305,7 +307,7 @@ hipError_t conv_vijp_sweep(int Ho, int Wo, int Cout, int n_img, int reach, float
     // a diagonal is one round of few workgroups: the shorter chain of the split 64 x 64 tile counts (us a diagonal of
     // eight 32 x 32 images, K = 192: 6.5 against 7.1)
     int tile = gather_tile(M, Cout, K, Cout, 1, K);
-    if (tile == TILE_64 && K >= SPLIT_MIN_K && Cout % Split64::BK == 0) tile = TILE_S64;
+    if (tile == TILE_64 && K >= 128 && Cout % Split64::BK == 0) tile = TILE_S64;
     switch (tile) {
       case TILE_128W8: e = sweep_t<Tile128W8>(Ho, Wo, Cout, n_img, d, reach, ct, Asweep, stream); break;
       case TILE_64X128: e = sweep_t<Tile64x128>(Ho, Wo, Cout, n_img, d, reach, ct, Asweep, stream); break;

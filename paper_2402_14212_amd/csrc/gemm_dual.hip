@@ -234,6 +234,7 @@ static hipError_t bp_pair_r(int tile_r, int tile_d, const BpLayerArgs& a, hipStr
     case TILE_S64: return bp_pair_d<Split64>(tile_d, a, stream);
     case TILE_128W8: return bp_pair_d<Tile128W8>(tile_d, a, stream);
     case TILE_64X128: return bp_pair_d<Tile64x128>(tile_d, a, stream);
+    case TILE_64K2: return bp_pair_d<Tile64K2>(tile_d, a, stream);
     case TILE_64: return bp_pair_d<Tile64>(tile_d, a, stream);
     default: return bp_pair_d<Tile32K4>(tile_d, a, stream);
   }

@@ -24,16 +24,12 @@ hipError_t grouped_l(int n_sets, int M, int N, int K, float alpha, const float* 
     if (tiles(64, 128) >= 512) return grouped_t<Tile64x128B, LA, LB>(n_sets, M, N, K, alpha, A, lda, B, ldb, beta, D, C, ldc, stream, eye);
     return grouped_t<Tile64B, LA, LB>(n_sets, M, N, K, alpha, A, lda, B, ldb, beta, D, C, ldc, stream, eye);
   }
-  // Split operands for P W^T only (us for twelve products of 1024 x 1024 x 1024: 66, with fp32 tiles 156). The left
-  // operand of the NN products is next to the identity: a row's first values are a millionth of the one on the
-  // diagonal, so that split tiles would be repeated with fp32 instructions (64 fp32 refreshes of 1024 x 1024 5.1 ms
-  // instead of 4.4).
-  if constexpr (LB == KCONTIG) {
-    if (K >= SPLIT_MIN_K) switch (pick_split_tile(n_sets, M, N, true)) {
-      case TILE_S256: return grouped_t<Split256, LA, LB>(n_sets, M, N, K, alpha, A, lda, B, ldb, beta, D, C, ldc, stream, eye);
-      case TILE_S128: return grouped_t<Split128, LA, LB>(n_sets, M, N, K, alpha, A, lda, B, ldb, beta, D, C, ldc, stream, eye);
-      default: return grouped_t<Split64, LA, LB>(n_sets, M, N, K, alpha, A, lda, B, ldb, beta, D, C, ldc, stream, eye);
-    }
+  // Split operands by the rule of single products (us for eight products of 1024 x 1024 x 1024, P W^T: 99, with fp32 tiles
+  // 149; 64 fp32 refreshes of 1024 x 1024 in all 3.1 ms, with fp32 tiles for both products 4.4, for the NN ones 3.7).
+  if (split_pays(n_sets, M, N, K)) switch (pick_split_tile(n_sets, M, N, true)) {
+    case TILE_S256: return grouped_t<Split256, LA, LB>(n_sets, M, N, K, alpha, A, lda, B, ldb, beta, D, C, ldc, stream, eye);
+    case TILE_S128: return grouped_t<Split128, LA, LB>(n_sets, M, N, K, alpha, A, lda, B, ldb, beta, D, C, ldc, stream, eye);
+    default: return grouped_t<Split64, LA, LB>(n_sets, M, N, K, alpha, A, lda, B, ldb, beta, D, C, ldc, stream, eye);
   }
   if (tiles(128, 128) >= 512) return grouped_t<Tile128W8, LA, LB>(n_sets, M, N, K, alpha, A, lda, B, ldb, beta, D, C, ldc, stream, eye);
   if (tiles(64, 128) >= 512) return grouped_t<Tile64x128, LA, LB>(n_sets, M, N, K, alpha, A, lda, B, ldb, beta, D, C, ldc, stream, eye);

@@ -28,11 +28,11 @@ static int64_t tiles_of(int m, int n, int tm, int tn) { return (int64_t)((m + tm
 
 // The split tile with the least time for `sets` outputs of M x N. One workgroup of each runs on a CU at a time, so
 // the time is the number of rounds of 256 workgroups times a round's length; relative lengths measured at K = 1024
-// .. 4096 (us a round at 8192 x 1024 x 1024): 256 x 128 69, 128 x 128 40, 64 x 64 12.5 (14.6 by itself).
-// For example 512 x 2048: 256 tiles of 64 x 64 in 26 us against 64 of 128 x 128 in 48.
+// (us a round): 256 x 128 94, 128 x 128 50, 64 x 64 26 (21 alone). For example 512 x 2048 x 2048: 256 tiles of 64 x 64
+// in 42 us against 64 of 128 x 128 in 71; 2048 x 2048 x 2048: 150 us against 94.
 int pick_split_tile(int64_t sets, int M, int N, bool s256) {
   struct { int tile, tm, tn; double cost; bool allowed; } const c[] = {
-      {TILE_S256, 256, 128, 1.7, s256}, {TILE_S128, 128, 128, 1.0, true}, {TILE_S64, 64, 64, 0.34, true}};
+      {TILE_S256, 256, 128, 1.88, s256}, {TILE_S128, 128, 128, 1.0, true}, {TILE_S64, 64, 64, 0.52, true}};
   int best = TILE_S128;
   double least = 1e300;
   for (const auto& t : c) {
@@ -62,9 +62,16 @@ int pick_tile_f32(int M, int N, int K) {
   return TILE_64;
 }
 
-// From 96 tiles of 64 x 64 the split ones are faster (us at K = 1024: 512 x 1024 14.6 against 21 on fp32 instructions);
-// smaller outputs are better spread over 32 x 32 fp32 tiles (256 x 1024: 11.1 against 14.6).
-bool split_pays(int64_t sets, int M, int N, int K) { return K >= SPLIT_MIN_K && sets * tiles_of(M, N, 64, 64) >= 96; }
+// Split operands where they are faster than the fp32 tile of the same product, measured over NT, NN and TN (us, fp32
+// against split): from half a round of 128 x 128 tiles (132 of them, 1408 x 1536: K = 256 17.8 and 15.4, 1024 57 and
+// 41; 128 of them, 1024 x 2048: K = 256 14.3 and 16.0, 1024 44.1 and 44.2, 2048 74.5 and 70.2; two rounds, 2176 x
+// 2176: K = 128 18.6 and 20.5, 512 53 and 47), and where 64 x 64 tiles make one round that is nearly full (1024 x 1024: K = 512 14.5
+// and 11.7, 1024 23.8 and 22.5; 512 x 2048 x 2048 46 and 42). Fewer are better spread over 32 x 32 fp32 tiles (512 x 1024 x 1024:
+// 16.4 and 20.1), more 64 x 64 tiles are a second round.
+bool split_pays(int64_t sets, int M, int N, int K) {
+  const int64_t t64 = sets * tiles_of(M, N, 64, 64), t128 = sets * tiles_of(M, N, 128, 128);
+  return (K >= SPLIT_MIN_K && t128 > (K >= 1024 ? 127 : 128)) || (K >= 512 && t64 >= 192 && t64 <= 256);
+}
 
 int pick_tile(int M, int N, int K) {
   return split_pays(1, M, N, K) ? pick_split_tile(1, M, N, false) : pick_tile_f32(M, N, K);
@@ -74,13 +81,12 @@ int pick_tile_tn(int M, int N, int K) {
   return split_pays(1, M, N, K) ? pick_split_tile(1, M, N, true) : pick_tile_f32(M, N, K);
 }
 
-// Where one layer's 64 x 64 tiles fill the chip, the cotangent product of Phase III goes by itself on split operands
-// (us a layer with its weight gradient at 512 x 2048 x 2048: 42 for the activation and 60 for the rest, 117 in one
-// kernel; 1024 x 4096 x 4096: 267 and 240, 790). Smaller layers keep the one kernel for both products, whose launches
-// are fewer and can be grouped over stretches.
+// Where the cotangent product of Phase III takes split operands, it goes by itself (whole gradients, us, in one fp32
+// kernel and apart: eight layers of 1024 x 1024 x 1024 1146 and 819 to 862; six of 4096 x 4096, batch 1024, 7770 and
+// 6330 to 6700; eight of 2048 x 2048, batch 512, 1500 and 1430 to 1530, by how far the card clocks down).
+// Smaller layers keep the one kernel for both products, whose launches are fewer and can be grouped over stretches.
 int phase3_tile(int M, int N, int K, bool split) {
-  return split && K >= SPLIT_MIN_K && tiles_of(M, N, 64, 64) >= 192 ? pick_split_tile(1, M, N, false)
-                                                                   : pick_tile_f32(M, N, K);
+  return split && split_pays(1, M, N, K) ? pick_split_tile(1, M, N, false) : pick_tile_f32(M, N, K);
 }
 
 int pick_tile_dw_f32(int M, int N, int partner, bool phase3) {
@@ -1059,14 +1065,13 @@ int refresh_one_layer(mw_handle* h, Layer& l, int iters, float* residual_out, hi
     if (cur != l.P) MW_HIP(ew_copy(l.P, cur, (int64_t)n * m, s));
   } else {
     MW_HIP(gemm_plain(OP_NT, TILE_AUTO, n, n, m, 1.f, l.P, m, l.P, m, 0.f, S, n, nullptr, s));
-    MW_HIP(gemm_plain(OP_NN, pick_tile_f32(n, m, n), n, m, n, 1.f, S, n, l.W, m, 0.f, cur, m, nullptr, s));
+    MW_HIP(gemm_plain(OP_NN, TILE_AUTO, n, m, n, 1.f, S, n, l.W, m, 0.f, cur, m, nullptr, s));
   }
   for (int it = 0; it < iters; ++it) {
     MW_HIP(gemm_plain(OP_NT, TILE_AUTO, n, n, m, 1.f, cur, m, l.W, m, 0.f, S, n, nullptr, s));
     if (residual_out && it == iters - 1) MW_HIP(ew_identity_residual(S, n, h->loss_scratch, residual_out, s));
     MW_HIP(ew_copy(cur, other, (int64_t)n * m, s));
-    // (fp32 instructions: S is next to the identity, see gemm_grouped)
-    MW_HIP(gemm_plain(OP_NN, pick_tile_f32(n, m, n), n, m, n, -1.f, S, n, cur, m, 2.f, other, m, nullptr, s));
+    MW_HIP(gemm_plain(OP_NN, TILE_AUTO, n, m, n, -1.f, S, n, cur, m, 2.f, other, m, nullptr, s));
     float* t = cur;
     cur = other;
     other = t;

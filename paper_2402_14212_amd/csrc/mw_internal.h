@@ -13,7 +13,7 @@ constexpr int TILE_AUTO = 0, TILE_128 = 1, TILE_64 = 2, TILE_32K4 = 3, TILE_32K8
 constexpr int TILE_S256 = 16, TILE_S128 = 17, TILE_S64 = 18, TILE_S64Q = 19;
 inline bool tile_is_split(int tile) { return tile >= TILE_S256; }
 // least K of a product that takes split operands: below it the product is a few K tiles of launch and memory latency
-constexpr int SPLIT_MIN_K = 128;
+constexpr int SPLIT_MIN_K = 256;
 // fp32 tiles whose workgroups have eight wavefronts (the others have four)
 inline bool tile_has_8_waves(int tile) { return tile == TILE_32K8 || tile == TILE_64K2 || tile == TILE_128W8 || tile == TILE_64X128; }
 constexpr int OP_NT = 0, OP_NN = 1, OP_TN = 2;
@@ -21,7 +21,7 @@ constexpr int OP_NT = 0, OP_NN = 1, OP_TN = 2;
 // Tile choice for an M x N x K product on a 256-CU device (NT or NN; TN). Deterministic in (M, N, K) only.
 int pick_tile(int M, int N, int K);
 int pick_tile_tn(int M, int N, int K);
-// whether `sets` products of one shape take split operands, and if so the cheapest split tile (256 x 128: only if s256) for `sets` products of one shape
+// whether `sets` products of one shape take split operands, and if so their cheapest split tile (256 x 128: only if s256)
 bool split_pays(int64_t sets, int M, int N, int K);
 int pick_split_tile(int64_t sets, int M, int N, bool s256);
 // the same among the tiles on fp32 matrix instructions: every product that computes pre-activations takes it, so that

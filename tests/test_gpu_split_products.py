@@ -55,24 +55,29 @@ def operands(seed, M, N, K):
     return rng, rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32)
 
 
+# one size for each split tile: 64 x 64, 128 x 128 and (TN) 256 x 128
+SIZES = [(NT, 900, 1020, 520), (NT, 1436, 1500, 264), (NN, 900, 1020, 520), (NN, 1436, 1500, 264),
+         (TN, 900, 1020, 520), (TN, 1436, 1500, 264), (TN, 2290, 2300, 260)]
+
+
 @pytest.mark.parametrize("op", [NT, NN, TN])
 @pytest.mark.parametrize("M,N,K,pad", [
-    (640, 640, 128, 0),      # 100 tiles of 64 x 64: the least grid and the least K that take split operands
-    (700, 612, 160, 0),      # remainders of rows and of a K tile
-    (637, 705, 131, 0),      # odd everything: element-wise loads
-    (1280, 2052, 192, 1),    # 128 x 128 tiles, an unaligned leading dimension
-    (2049, 2304, 256, 0),    # one row more than the tiles
-    (4096, 4100, 136, 0),    # TN: 256 x 128 tiles
+    (832, 960, 512, 0),      # 195 tiles of 64 x 64 and the least K that takes them
+    (961, 1021, 517, 0),     # odd everything: element-wise loads, remainders of rows and of a K tile
+    (1408, 1536, 256, 0),    # 132 tiles of 128 x 128 and the least K of those
+    (1501, 1433, 259, 0),    # odd
+    (1500, 1412, 300, 1),    # an unaligned leading dimension
+    (1024, 2048, 1024, 0),   # 128 tiles: from this K on
+    (2177, 2304, 256, 0),    # one row more than the tiles; TN: 256 x 128 tiles
 ])
 def test_tile_edges(mw, op, M, N, K, pad):
     _, A, B = operands(M + K, M, N, K)
     check(mw, op, A, B, pad)
 
 
-@pytest.mark.parametrize("op", [NT, NN, TN])
+@pytest.mark.parametrize("op,M,N,K", SIZES)
 @pytest.mark.parametrize("kind", ["scales", "late", "late_tiny", "late_large", "jump", "zero", "subnormal", "huge"])
-def test_rows_of_other_magnitudes(mw, op, kind):
-    M, N, K = 640, 704, 320
+def test_rows_of_other_magnitudes(mw, op, M, N, K, kind):
     rng, A, B = operands(7, M, N, K)
     rows = rng.choice(M, 60, replace=False)
     if kind == "scales":           # rows of A and B apart by many powers of two
@@ -122,23 +127,24 @@ def along_k(kind, M, N, K):
     return A, B
 
 
-@pytest.mark.parametrize("op", [NT, NN, TN])
+@pytest.mark.parametrize("op,M,N,K", SIZES)
 @pytest.mark.parametrize("kind", ["leading", "column", "reciprocal", "far_reciprocal", "samples"])
-def test_magnitudes_that_differ_along_k(mw, op, kind):
+def test_magnitudes_that_differ_along_k(mw, op, M, N, K, kind):
     """Also against fp32 instructions on the same data: the largest error beside sum|a||b| is no more than twice theirs,
     or a rounding of the operands where they have none."""
-    A, B = along_k(kind, 640, 704, 320)
+    A, B = along_k(kind, M, N, K)
     ref = A.astype(np.float64) @ B.astype(np.float64).T
     size = np.abs(A).astype(np.float64) @ np.abs(B).astype(np.float64).T + 2.0 ** -149
     split, f32 = ((np.abs(product(mw, op, A, B, tile=t) - ref) / size).max() for t in (0, mw.TILE_64))
     print("%s op=%d error beside sum|a||b|: split %.3g, fp32 instructions %.3g" % (kind, op, split, f32), flush=True)
-    assert split <= 2 * f32 + 2.0 ** -24 and split <= 320 * 2.0 ** -24
+    assert split <= 2 * f32 + 2.0 ** -24 and split <= K * 2.0 ** -24
 
 
-@pytest.mark.parametrize("op", [NT, NN, TN])
-def test_a_single_term_is_exact(mw, op):
+@pytest.mark.parametrize("op,M,N", [(NT, 1000, 1000), (NT, 1536, 1536), (NN, 1000, 1000), (NN, 1536, 1536), (TN, 1000, 1000),
+                                    (TN, 2304, 2304)])
+def test_a_single_term_is_exact(mw, op, M, N):
     """Products with one term each return the values as they are, all 24 bits of them, over fp32's range."""
-    M = N = K = 640
+    K = N
     rng, A, _ = operands(3, M, N, K)
     A *= (2.0 ** rng.integers(-120, 60, (M, K))).astype(np.float32)
     perm = rng.permutation(K)
@@ -147,13 +153,12 @@ def test_a_single_term_is_exact(mw, op):
     assert np.array_equal(product(mw, op, A, B), A[:, perm])
 
 
-@pytest.mark.parametrize("op", [NT, NN, TN])
-def test_values_that_do_not_fit(mw, op):
+@pytest.mark.parametrize("op,M,N,K", SIZES)
+def test_values_that_do_not_fit(mw, op, M, N, K):
     """Infinities and NaN reach exactly the results they belong to; a value next to fp32's largest stays finite."""
-    M, N, K = 640, 704, 320
     _, A, B = operands(11, M, N, K)
     clean = product(mw, op, A, B)
-    A[3, 200], A[65, 5], A[130, 319], A[200, 77], B[40, 300] = np.inf, -np.inf, np.nan, 3e38, 1e30
+    A[3, 200], A[65, 5], A[130, K - 1], A[200, 77], B[40, 250] = np.inf, -np.inf, np.nan, 3e38, 1e30
     got = product(mw, op, A, B)
     with np.errstate(all="ignore"):
         ref = A.astype(np.float64) @ B.astype(np.float64).T
@@ -168,11 +173,12 @@ def test_values_that_do_not_fit(mw, op):
 
 
 @pytest.mark.parametrize("op", [NT, NN, TN])
-@pytest.mark.parametrize("K", [128, 512, 2048])
-def test_no_less_precise_than_fp32_instructions(mw, op, K):
-    _, A, B = operands(K, 1024, 768, K)
+@pytest.mark.parametrize("M,K", [(1024, 512), (1024, 2048), (1536, 256), (1536, 1024)])
+def test_no_less_precise_than_fp32_instructions(mw, op, M, K):
+    _, A, B = operands(K, M, M, K)
+    f32_tile = mw.TILE_64K2 if K >= 1024 else mw.TILE_64
     ref = A.astype(np.float64) @ B.astype(np.float64).T
-    split, f32 = (np.linalg.norm(product(mw, op, A, B, tile=t) - ref) / np.linalg.norm(ref) for t in (0, mw.TILE_64))
+    split, f32 = (np.linalg.norm(product(mw, op, A, B, tile=t) - ref) / np.linalg.norm(ref) for t in (0, f32_tile))
     print("K=%d normwise error: split %.3g, fp32 instructions %.3g" % (K, split, f32), flush=True)
     assert split <= f32
 
@@ -182,7 +188,7 @@ def test_no_less_precise_than_fp32_instructions(mw, op, K):
     ((1029, 1027, 1025), (0.3, 0.3)),               # element-wise loads: every product in a launch of its own
     ((96, 96), (0.3,)),                             # all of it below
     ((1088, 1056, 1024), (0.0, 0.0)),               # the fragment store restored in the cotangent's launch
-    ((2176, 2112), (0.3,)),                         # 128 x 128 tiles
+    ((2560, 2432), (0.3,)),                         # 128 x 128 tiles
 ])
 def test_phase3_in_two_launches(mw, widths, alphas):
     """The activation and the cotangent of a layer in launches of their own: against the oracle on the same signs, and
