@@ -277,8 +277,21 @@ struct SplitKTnTask {
     else a += (int64_t)k_lo * lda;
     EpiStore es{part + (int64_t)slice * M * N, N, 1.f, 0.f, nullptr};
     EpiStore::Dev ed(es, M, N);
-    split_product<Cfg, RCONTIG, RCONTIG, true, false>(a, lda, B + (int64_t)k_lo * ldb, ldb, M, N, k_n, m0, n0, lds, xd, ed, nullptr,
-                                                      0.f, 0.f);
+    if constexpr (is_split<Cfg>()) {
+      split_product<Cfg, RCONTIG, RCONTIG, true, false>(a, lda, B + (int64_t)k_lo * ldb, ldb, M, N, k_n, m0, n0, lds, xd, ed, nullptr,
+                                                        0.f, 0.f);
+    } else {
+      f32x16 acc[1][Cfg::NACC];
+      float asum[Cfg::WTM];
+#pragma unroll
+      for (int t = 0; t < Cfg::NACC; ++t)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[0][t][i] = 0.f;
+#pragma unroll
+      for (int t = 0; t < Cfg::WTM; ++t) asum[t] = 0.f;
+      gemm_mainloop<Cfg, RCONTIG, RCONTIG, true, false>(a, lda, B + (int64_t)k_lo * ldb, ldb, M, N, k_n, m0, n0, lds, xd, acc[0], asum);
+      reduce_and_finish<Cfg, 1>(lds, M, N, m0, n0, acc, asum, ed);
+    }
   }
 };
 

@@ -127,22 +127,37 @@ struct DwPlan {
   int tile, slices, k_per;
 };
 
+// One slice is too short for split tiles below 128 rows (us with fp32 tiles and split: 25 rows 9.7 and 11.7, 81 rows
+// 12.0 and 12.3, 162 rows 15.6 and 14.9, 243 rows 18.1 and 15.7).
+constexpr int64_t DW_SPLIT_MIN_ROWS = 128;
+
 DwPlan plan_dw(int K1, int Cout, int64_t rows) {
   DwPlan p;
-  // 128 x 128 where that fills the chip with slices of 256 rows (us for 3264 rows, 288 x 96: 128 x 128 16.0 in 39
-  // workgroups, 64 x 64 on fp32 instructions 11.1)
-  const int64_t tiles128 = (int64_t)ceil_div(K1, 128) * ceil_div(Cout, 128);
-  const int t = (K1 > 64 && Cout > 64 && rows * tiles128 >= 256 * 256) ? 128 : 64;
-  p.tile = t == 128 ? TILE_S128 : TILE_S64;
-  const int64_t tiles = (int64_t)ceil_div(K1, t) * ceil_div(Cout, t);
-  // one round of workgroups (two of the small tile) when the rows allow it, never a few more than that (they would
-  // run on their own after all the others), and at least 256 rows per slice
-  const int64_t room = t == 128 ? 256 : 512;
+  int bm, bn, room, step;
+  if (rows >= DW_SPLIT_MIN_ROWS) {
+    // 128 x 128 where that fills the chip with slices of 256 rows; one round of workgroups (two of the small tile)
+    const int64_t tiles128 = (int64_t)ceil_div(K1, 128) * ceil_div(Cout, 128);
+    const bool large = K1 > 64 && Cout > 64 && rows * tiles128 >= 256 * 256;
+    p.tile = large ? TILE_S128 : TILE_S64;
+    bm = bn = large ? 128 : 64;
+    room = large ? 256 : 512;
+    step = 64;
+  } else {
+    // four workgroups per CU
+    if (K1 >= 128 && Cout >= 128) { p.tile = TILE_128W8; bm = 128; bn = 128; }
+    else if (Cout >= 128) { p.tile = TILE_64X128; bm = 64; bn = 128; }
+    else { p.tile = TILE_64; bm = 64; bn = 64; }
+    room = 1024;
+    step = 32;
+  }
+  const int64_t tiles = (int64_t)ceil_div(K1, bm) * ceil_div(Cout, bn);
+  // when the rows allow it, never a few workgroups more than that (they would run on their own after all the others), and
+  // at least 256 rows per slice
   int64_t want = tiles >= room ? 1 : room / tiles;
   if (want > CONV_DW_MAX_SLICES) want = CONV_DW_MAX_SLICES;
   int64_t k_per = (rows + want - 1) / want;
   if (k_per < 256) k_per = 256;
-  k_per = (k_per + 63) / 64 * 64;
+  k_per = (k_per + step - 1) / step * step;
   p.k_per = (int)k_per;
   p.slices = (int)((rows + k_per - 1) / k_per);
   if (p.slices < 1) p.slices = 1;
@@ -360,8 +375,14 @@ hipError_t conv_dw(const ConvGeom& g, int n_img, const float* x, const float* ct
   if (n_img <= 0) return hipSuccess;
   const int K1 = g.taps() * g.C;
   const DwPlan p = plan_dw(K1, Cout, (int64_t)n_img * g.Ho * g.Wo);
-  const hipError_t e = p.tile == TILE_S128 ? dw_t<Split128>(g, n_img, x, ctz, Cout, p, part, stream)
-                                           : dw_t<Split64>(g, n_img, x, ctz, Cout, p, part, stream);
+  hipError_t e;
+  switch (p.tile) {
+    case TILE_S128: e = dw_t<Split128>(g, n_img, x, ctz, Cout, p, part, stream); break;
+    case TILE_S64: e = dw_t<Split64>(g, n_img, x, ctz, Cout, p, part, stream); break;
+    case TILE_128W8: e = dw_t<Tile128W8>(g, n_img, x, ctz, Cout, p, part, stream); break;
+    case TILE_64X128: e = dw_t<Tile64x128>(g, n_img, x, ctz, Cout, p, part, stream); break;
+    default: e = dw_t<Tile64>(g, n_img, x, ctz, Cout, p, part, stream); break;
+  }
   if (e != hipSuccess) return e;
   return ew_reduce_slices(part, p.slices, (int64_t)K1 * Cout, scale, beta, dW, stream);
 }
