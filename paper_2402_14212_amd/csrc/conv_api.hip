@@ -142,7 +142,7 @@ int build_from_weights(mw_conv_handle* h, hipStream_t s) {
         for (int kx = 0; kx < n1; ++kx) {
           if (ky == l.reach && kx == l.reach) continue;
           const int u = l.p + (l.reach - ky) * l.s, v = l.p + (l.reach - kx) * l.s;
-          CV_HIP(gemm_plain(OP_NN, TILE_AUTO, l.Cout, l.Cout, l.Cout, 1.f, l.Tinv, l.Cout,
+          CV_HIP(gemm_plain(OP_NN, pick_tile_f32(l.Cout, l.Cout, l.Cout), l.Cout, l.Cout, l.Cout, 1.f, l.Tinv, l.Cout,
                             l.w + ((size_t)(u * l.k + v) * l.Cin) * l.Cout, l.Cout, 0.f,
                             l.Asweep + (size_t)(ky * n1 + kx) * l.Cout, Ktot, nullptr, s));
         }
@@ -150,7 +150,7 @@ int build_from_weights(mw_conv_handle* h, hipStream_t s) {
     // fragmental layers: the recurrence matrices T^{-1} w[u][:Cout] side by side, u = k - 1 .. 1, in the
     // order of the positions j - k + 1 .. j - 1 they multiply: one [Cout][(k - 1) Cout] matrix
     for (int u = 1; l.Arec && u < l.k; ++u)
-      CV_HIP(gemm_plain(OP_NN, TILE_AUTO, l.Cout, l.Cout, l.Cout, 1.f, l.Tinv, l.Cout, l.w + (size_t)u * l.Cin * l.Cout, l.Cout, 0.f,
+      CV_HIP(gemm_plain(OP_NN, pick_tile_f32(l.Cout, l.Cout, l.Cout), l.Cout, l.Cout, l.Cout, 1.f, l.Tinv, l.Cout, l.w + (size_t)u * l.Cin * l.Cout, l.Cout, 0.f,
                         l.Arec + (size_t)(l.k - 1 - u) * l.Cout, (int64_t)(l.k - 1) * l.Cout, nullptr, s));
   }
   int32_t bad = 0;
@@ -158,6 +158,10 @@ int build_from_weights(mw_conv_handle* h, hipStream_t s) {
   CV_HIP(hipMemcpy(&bad, flag, sizeof(bad), hipMemcpyDeviceToHost));
   return bad ? MW_ERR_NOT_SUBMERSIVE : MW_OK;
 }
+
+// The tile of a product that may take split operands. A training step's do not: its gradients become weights, whose
+// every bit decides the signs of pre-activations next to zero in the next step (see pick_tile_f32).
+int plain_tile(bool split, int M, int N, int K) { return split ? TILE_AUTO : pick_tile_f32(M, N, K); }
 
 // z (rows [r0, r0 + R) of the layer's output, bias added) = patches(x) w, through the patch buffer
 int conv_rows(mw_conv_handle* h, const ConvLayer& l, const float* xin, int64_t r0, int64_t R, float* zout, hipStream_t s) {
@@ -172,7 +176,7 @@ int conv_rows(mw_conv_handle* h, const ConvLayer& l, const float* xin, int64_t r
 // with ct_out) = h; ct_out (may be NULL) = h times the slope selected by the previous layer's mask.
 // Returns through *fused whether ct_out was written (only the gathered kernel can do that).
 int conv_input_grad(mw_conv_handle* h, const ConvLayer& l, const float* ctz, float* hout, float* ct_out,
-                    const ConvLayer* prev, bool* fused, hipStream_t s) {
+                    const ConvLayer* prev, bool* fused, bool split, hipStream_t s) {
   if (fused) *fused = false;
   if (l.gather_rev) {
     // the mask of an image chunk must start on a 32-bit word
@@ -184,7 +188,7 @@ int conv_input_grad(mw_conv_handle* h, const ConvLayer& l, const float* ctz, flo
       CV_HIP(conv_input_cotangent(l.geom(), n_img, l.Cout, ctz + img0 * l.out_img(), l.wrev, hout ? hout + o : nullptr,
                                   fuse ? ct_out + o : nullptr,
                                   fuse ? reinterpret_cast<const uint32_t*>(prev->mask) + o / 32 : nullptr,
-                                  fuse ? prev->alpha : 1.f, s));
+                                  fuse ? prev->alpha : 1.f, split, s));
     }
     if (fused) *fused = fuse;
     return MW_OK;
@@ -195,7 +199,7 @@ int conv_input_grad(mw_conv_handle* h, const ConvLayer& l, const float* ctz, flo
     const int64_t n_img = (img0 + l.chunk_images <= h->B) ? l.chunk_images : h->B - img0;
     const int64_t r0 = img0 * per_img, R = n_img * per_img;
     // patch cotangents = ct_z w^T: (R x Cout) (K x Cout)^T
-    CV_HIP(gemm_plain(OP_NT, TILE_AUTO, (int)R, l.K, l.Cout, 1.f, ctz + r0 * l.Cout, l.Cout, l.w, l.Cout, 0.f, h->patches, l.K,
+    CV_HIP(gemm_plain(OP_NT, plain_tile(split, (int)R, l.K, l.Cout), (int)R, l.K, l.Cout, 1.f, ctz + r0 * l.Cout, l.Cout, l.w, l.Cout, 0.f, h->patches, l.K,
                       nullptr, s));
     CV_HIP(cv_col2im(h->patches, l.Hin, l.Win, l.Cin, l.Ho, l.Wo, l.k, l.s, l.p, img0, n_img, hout, s));
   }
@@ -205,14 +209,14 @@ int conv_input_grad(mw_conv_handle* h, const ConvLayer& l, const float* ctz, flo
 // The part of the layer's input cotangent its own vijp reads, sub(h)[:, :Cout] (the strided positions,
 // the first Cout channels), straight from ct_z: in the fully parallel case only the tap at (p, p)
 // reaches those entries, so it is ct_z T^T with T the first Cout rows of that tap (Alg. 2 read backwards).
-int conv_kept_cotangent(mw_conv_handle* h, const ConvLayer& l, const float* ctz, float* kept, hipStream_t s) {
+int conv_kept_cotangent(mw_conv_handle* h, const ConvLayer& l, const float* ctz, float* kept, bool split, hipStream_t s) {
   const float* tap = l.tri_tap();  // [Cin][Cout]; rows c < Cout are T
   const int64_t per_img = (int64_t)l.Ho * l.Wo;
   for (int64_t img0 = 0; img0 < h->B; img0 += l.gchunk) {
     const int64_t n_img = (img0 + l.gchunk <= h->B) ? l.gchunk : h->B - img0;
     const int64_t r0 = img0 * per_img, R = n_img * per_img;
-    CV_HIP(gemm_plain(OP_NT, TILE_AUTO, (int)R, l.Cout, l.Cout, 1.f, ctz + r0 * l.Cout, l.Cout, tap, l.Cout, 0.f,
-                      kept + r0 * l.Cout, l.Cout, nullptr, s));
+    CV_HIP(gemm_plain(OP_NT, plain_tile(split, (int)R, l.Cout, l.Cout), (int)R, l.Cout, l.Cout, 1.f, ctz + r0 * l.Cout, l.Cout,
+                      tap, l.Cout, 0.f, kept + r0 * l.Cout, l.Cout, nullptr, s));
   }
   return MW_OK;
 }
@@ -281,13 +285,13 @@ int conv_forward_layer(mw_conv_handle* h, const ConvLayer& l, const float* xin, 
 // dW (+ db) of one layer from its input activation and ct_z, both for the whole batch
 // dW = scale * (parameter vjp) + beta0 * dW, likewise db (db may be NULL: not wanted)
 int conv_weight_grad(mw_conv_handle* h, const ConvLayer& l, const float* xin, const float* ctz, float scale, float* dW,
-                     float* db, hipStream_t s, float beta0 = 0.f) {
+                     float* db, bool split, hipStream_t s, float beta0 = 0.f) {
   bool first = true;
   if (l.gather) {
     for (int64_t img0 = 0; img0 < h->B; img0 += l.gchunk) {
       const int n_img = (int)((img0 + l.gchunk <= h->B) ? l.gchunk : h->B - img0);
       CV_HIP(conv_dw(l.geom(), n_img, xin + img0 * l.in_img(), ctz + img0 * l.out_img(), l.Cout, scale, first ? beta0 : 1.f, dW,
-                     h->dw_part, s));
+                     h->dw_part, split, s));
       first = false;
     }
   } else {
@@ -296,7 +300,7 @@ int conv_weight_grad(mw_conv_handle* h, const ConvLayer& l, const float* xin, co
       const int64_t n_img = (img0 + l.chunk_images <= h->B) ? l.chunk_images : h->B - img0;
       const int64_t r0 = img0 * per_img, R = n_img * per_img;
       CV_HIP(cv_im2col(xin, l.Hin, l.Win, l.Cin, l.Ho, l.Wo, l.k, l.s, l.p, r0, R, h->patches, s));
-      CV_HIP(gemm_plain(OP_TN, TILE_AUTO, l.K, l.Cout, (int)R, scale, h->patches, l.K, ctz + r0 * l.Cout, l.Cout,
+      CV_HIP(gemm_plain(OP_TN, plain_tile(split, l.K, l.Cout, (int)R), l.K, l.Cout, (int)R, scale, h->patches, l.K, ctz + r0 * l.Cout, l.Cout,
                         first ? beta0 : 1.f, dW, l.Cout, nullptr, s));
       first = false;
     }
@@ -432,8 +436,10 @@ int moonwalk_conv_setup(mw_conv_handle_t** out, const mw_conv_layer_t* layers, i
     l.gather = cfg->kernels == MW_CONV_KERNELS_AUTO && conv_gather_ok(g, l.Cout, nullptr, l.w);
     l.gather_rev = l.gather && conv_rev_ok(g, l.Cout);
     if (l.gather) {
-      const size_t part = conv_dw_part_floats(g, l.gchunk, l.Cout);
-      if (part > max_part) max_part = part;
+      for (const bool split : {false, true}) {
+        const size_t part = conv_dw_part_floats(g, l.gchunk, l.Cout, split);
+        if (part > max_part) max_part = part;
+      }
     } else {
       any_patch_layer = true;
     }
@@ -604,7 +610,7 @@ int run_conv_moonwalk(mw_conv_handle* h, const float* x, const float* target, fl
       const bool whole = l.whole_h();
       float* kept = prev ? prev->ckpt : (h->h0_full ? nullptr : h->h0);
       if (kept && !whole) {
-        int rc = conv_kept_cotangent(h, l, ct, kept, s);
+        int rc = conv_kept_cotangent(h, l, ct, kept, !apply, s);
         if (rc != MW_OK) return rc;
       }
       if (!prev && !h->h0_full) break;  // nothing else reads h_0
@@ -614,7 +620,7 @@ int run_conv_moonwalk(mw_conv_handle* h, const float* x, const float* target, fl
       const bool can_fuse = l.gather_rev && prev && l.Cin % 32 == 0;
       float* raw = prev ? (can_fuse ? nullptr : h->ha) : h->h0;
       if (whole && kept) raw = kept;  // such a layer reads every position of its input cotangent
-      int rc = conv_input_grad(h, l, ct, raw, ct_next, prev, &fused, s);
+      int rc = conv_input_grad(h, l, ct, raw, ct_next, prev, &fused, !apply, s);
       if (rc != MW_OK) return rc;
       if (prev && !fused) CV_HIP(ew_rev_scale(raw, prev->mask, prev->n_out, prev->alpha, ct_next, s));
     }
@@ -655,8 +661,8 @@ int run_conv_moonwalk(mw_conv_handle* h, const float* x, const float* target, fl
         const float* xc = xin + img0 * l.in_img();
         if (l.whole_h()) {
           if (!frag1d) {
-            CV_HIP(conv_sub_solve(l.geom(), n_img, l.Cout, hin + img0 * l.in_img(), l.Tinv, h->ctz + o, s));
-            CV_HIP(conv_vijp_sweep(l.Ho, l.Wo, l.Cout, n_img, l.reach, h->ctz + o, l.Asweep, s));
+            CV_HIP(conv_sub_solve(l.geom(), n_img, l.Cout, hin + img0 * l.in_img(), l.Tinv, h->ctz + o, !apply, s));
+            CV_HIP(conv_vijp_sweep(l.Ho, l.Wo, l.Cout, n_img, l.reach, h->ctz + o, l.Asweep, !apply, s));
           }
           CV_HIP(conv_vijp_given(l.geom(), n_img, xc, l.w, l.b, l.alpha, l.Cout, h->ctz + o, mask32, xout + o, hout + o,
                                  mismatches, s));
@@ -667,7 +673,7 @@ int run_conv_moonwalk(mw_conv_handle* h, const float* x, const float* target, fl
         }
       }
       int rc = conv_weight_grad(h, l, xin, h->ctz, g_scale, apply ? const_cast<float*>(l.w) : grads_out + l.dW_off,
-                                apply ? const_cast<float*>(l.b) : grads_out + l.db_off, s, g_beta);
+                                apply ? const_cast<float*>(l.b) : grads_out + l.db_off, !apply, s, g_beta);
       if (rc != MW_OK) return rc;
     } else {
       if (apply) return MW_ERR_NOT_PLANNED;
@@ -735,14 +741,14 @@ int backprop_conv_grad(mw_conv_handle_t* h, const float* x, const float* target,
     const float* xprev = (i == 0) ? x : h->layers[i - 1].act;
     CV_HIP(ew_scale_by_act_slope(hcur, l.act, l.n_out, l.alpha, h->ctz, s));
     {
-      int rc = conv_weight_grad(h, l, xprev, h->ctz, inv_scale, grads_out + l.dW_off, grads_out + l.db_off, s);
+      int rc = conv_weight_grad(h, l, xprev, h->ctz, inv_scale, grads_out + l.dW_off, grads_out + l.db_off, true, s);
       if (rc != MW_OK) return rc;
     }
     if (i > 0 || h->h0_full) {
       // the cotangent at the output of layer j < L - 1 lives in hbuf[j % 2] (hb is sized for the odd layers
       // only); h_L was in ha and has gone into ct_z by now, so ha may be written even when it held h_L
       float* hout = i > 0 ? hbuf[(i - 1) & 1] : h->h0;
-      int rc = conv_input_grad(h, l, h->ctz, hout, nullptr, nullptr, nullptr, s);
+      int rc = conv_input_grad(h, l, h->ctz, hout, nullptr, nullptr, nullptr, true, s);
       if (rc != MW_OK) return rc;
       hcur = hout;
     }
@@ -861,14 +867,14 @@ int mw_conv_input_cotangent(const mw_conv_shape_t* shape, const float* ctz, cons
   if (!conv_rev_ok(g, shape->channels_out)) return MW_ERR_INVALID_ARG;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   CV_HIP(cv_pack_rev_weights(w, g.kh, g.kw, g.s, g.C, shape->channels_out, work, s));
-  CV_HIP(conv_input_cotangent(g, shape->batch, shape->channels_out, ctz, work, h, nullptr, nullptr, 1.f, s));
+  CV_HIP(conv_input_cotangent(g, shape->batch, shape->channels_out, ctz, work, h, nullptr, nullptr, 1.f, true, s));
   return MW_OK;
 }
 
 size_t mw_conv_weight_grad_work_floats(const mw_conv_shape_t* shape) {
   ConvGeom g;
   if (!shape_geom(shape, &g)) return 0;
-  return conv_dw_part_floats(g, shape->batch, shape->channels_out) + (size_t)COLSUM_MAX_SLICES * shape->channels_out;
+  return conv_dw_part_floats(g, shape->batch, shape->channels_out, true) + (size_t)COLSUM_MAX_SLICES * shape->channels_out;
 }
 
 int mw_conv_weight_grad(const mw_conv_shape_t* shape, const float* x, const float* ctz, float scale, float* dw, float* db,
@@ -877,8 +883,8 @@ int mw_conv_weight_grad(const mw_conv_shape_t* shape, const float* x, const floa
   if (!shape_geom(shape, &g) || !x || !ctz || !dw || !db || !work || !al16(x) || !al16(ctz) || !al16(work) || !al16(dw))
     return MW_ERR_INVALID_ARG;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  const size_t part = conv_dw_part_floats(g, shape->batch, shape->channels_out);
-  CV_HIP(conv_dw(g, shape->batch, x, ctz, shape->channels_out, scale, 0.f, dw, work, s));
+  const size_t part = conv_dw_part_floats(g, shape->batch, shape->channels_out, true);
+  CV_HIP(conv_dw(g, shape->batch, x, ctz, shape->channels_out, scale, 0.f, dw, work, true, s));
   CV_HIP(ew_colsum_wide(ctz, (int64_t)shape->batch * g.Ho * g.Wo, shape->channels_out, scale, 0.f, db, work + part, s));
   return MW_OK;
 }

@@ -131,10 +131,10 @@ struct DwPlan {
 // 12.0 and 12.3, 162 rows 15.6 and 14.9, 243 rows 18.1 and 15.7).
 constexpr int64_t DW_SPLIT_MIN_ROWS = 128;
 
-DwPlan plan_dw(int K1, int Cout, int64_t rows) {
+DwPlan plan_dw(int K1, int Cout, int64_t rows, bool split) {
   DwPlan p;
   int bm, bn, room, step;
-  if (rows >= DW_SPLIT_MIN_ROWS) {
+  if (split && rows >= DW_SPLIT_MIN_ROWS) {
     // 128 x 128 where that fills the chip with slices of 256 rows; one round of workgroups (two of the small tile)
     const int64_t tiles128 = (int64_t)ceil_div(K1, 128) * ceil_div(Cout, 128);
     const bool large = K1 > 64 && Cout > 64 && rows * tiles128 >= 256 * 256;
@@ -190,9 +190,9 @@ int gather_tile_f32(int M, int N, int K, int csel_a, int csel_b) {
 // 25392 rows of 96 to 128 channels, 5 x 5 183 and 119. Several rounds of 64 x 64 tiles, and channels that are no
 // multiple of 64, take four wavefronts and a K tile of 32, three workgroups to a CU (240000 rows of 64 channels: 173
 // against 207, fp32 320; 40368 rows of 32 channels, 5 x 5: 54, fp32 91).
-int gather_tile(int M, int N, int K, int csel, int sets, int k_sum) {
+int gather_tile(int M, int N, int K, int csel, int sets, int k_sum, bool split) {
   const int64_t t64 = (int64_t)sets * ceil_div(M, 64) * ceil_div(N, 64);
-  if (k_sum / sets < 256 || t64 < 96) return gather_tile_f32(M, N, K, csel, csel);
+  if (!split || k_sum / sets < 256 || t64 < 96) return gather_tile_f32(M, N, K, csel, csel);
   if (N > 64 && pick_split_tile(sets, M, N, false) == TILE_S128) return TILE_S128;
   if (t64 <= 256 && csel % Split64::BK == 0) return TILE_S64;
   return t64 >= 256 ? TILE_S64Q : gather_tile_f32(M, N, K, csel, csel);
@@ -270,12 +270,14 @@ hipError_t sub_solve_t(const ConvGeom& g, int n_img, int Cout, const float* hin,
   return launch_task<Cfg::NT>(t, stream);
 }
 
-hipError_t conv_sub_solve(const ConvGeom& g, int n_img, int Cout, const float* hin, const float* Tinv, float* ct, hipStream_t stream) {
+hipError_t conv_sub_solve(const ConvGeom& g, int n_img, int Cout, const float* hin, const float* Tinv, float* ct, bool split,
+                          hipStream_t stream) {
   if (n_img <= 0) return hipSuccess;
   const int M = n_img * g.Ho * g.Wo;
-  switch (gather_tile(M, Cout, Cout, Cout, 1, Cout)) {
+  switch (gather_tile(M, Cout, Cout, Cout, 1, Cout, split)) {
     case TILE_128W8: return sub_solve_t<Tile128W8>(g, n_img, Cout, hin, Tinv, ct, stream);
     case TILE_64X128: return sub_solve_t<Tile64x128>(g, n_img, Cout, hin, Tinv, ct, stream);
+    case TILE_64K2: return sub_solve_t<Tile64K2>(g, n_img, Cout, hin, Tinv, ct, stream);
     case TILE_S128: return sub_solve_t<Split128>(g, n_img, Cout, hin, Tinv, ct, stream);
     case TILE_S64: return sub_solve_t<Split64>(g, n_img, Cout, hin, Tinv, ct, stream);
     case TILE_S64Q: return sub_solve_t<Split64Q>(g, n_img, Cout, hin, Tinv, ct, stream);
@@ -312,7 +314,8 @@ hipError_t sweep_t(int Ho, int Wo, int Cout, int n_img, int d, int reach, float*
   return launch_task<Cfg::NT>(t, stream);
 }
 
-hipError_t conv_vijp_sweep(int Ho, int Wo, int Cout, int n_img, int reach, float* ct, const float* Asweep, hipStream_t stream) {
+hipError_t conv_vijp_sweep(int Ho, int Wo, int Cout, int n_img, int reach, float* ct, const float* Asweep, bool split,
+                           hipStream_t stream) {
   if (n_img <= 0 || reach <= 0) return hipSuccess;
   const int K = ((reach + 1) * (reach + 1) - 1) * Cout;
   for (int d = 1; d <= Ho + Wo - 2; ++d) {  // diagonal 0 has no earlier position
@@ -321,11 +324,12 @@ hipError_t conv_vijp_sweep(int Ho, int Wo, int Cout, int n_img, int reach, float
     hipError_t e;
     // a diagonal is one round of few workgroups: the shorter chain of the split 64 x 64 tile counts (us a diagonal of
     // eight 32 x 32 images, K = 192: 6.5 against 7.1)
-    int tile = gather_tile(M, Cout, K, Cout, 1, K);
-    if (tile == TILE_64 && K >= 128 && Cout % Split64::BK == 0) tile = TILE_S64;
+    int tile = gather_tile(M, Cout, K, Cout, 1, K, split);
+    if (split && tile == TILE_64 && K >= 128 && Cout % Split64::BK == 0) tile = TILE_S64;
     switch (tile) {
       case TILE_128W8: e = sweep_t<Tile128W8>(Ho, Wo, Cout, n_img, d, reach, ct, Asweep, stream); break;
       case TILE_64X128: e = sweep_t<Tile64x128>(Ho, Wo, Cout, n_img, d, reach, ct, Asweep, stream); break;
+      case TILE_64K2: e = sweep_t<Tile64K2>(Ho, Wo, Cout, n_img, d, reach, ct, Asweep, stream); break;
       case TILE_S128: e = sweep_t<Split128>(Ho, Wo, Cout, n_img, d, reach, ct, Asweep, stream); break;
       case TILE_S64: e = sweep_t<Split64>(Ho, Wo, Cout, n_img, d, reach, ct, Asweep, stream); break;
       case TILE_S64Q: e = sweep_t<Split64Q>(Ho, Wo, Cout, n_img, d, reach, ct, Asweep, stream); break;
@@ -342,15 +346,16 @@ bool conv_rev_ok(const ConvGeom& g, int Cout) {
 }
 
 hipError_t conv_input_cotangent(const ConvGeom& g, int n_img, int Cout, const float* ctz, const float* wrev, float* raw,
-                                float* ct, const uint32_t* mask32, float alpha, hipStream_t stream) {
+                                float* ct, const uint32_t* mask32, float alpha, bool split, hipStream_t stream) {
   if (n_img <= 0) return hipSuccess;
   EpiConvRev epi{raw, ct, mask32, alpha, g.H, g.W, g.s, (uint32_t)((int64_t)n_img * g.H * g.W * g.C * 4)};
   // the tile for the largest class: about a quarter of the input pixels, all taps of that class
   const int M = n_img * ((g.H + g.s - 1) / g.s) * ((g.W + g.s - 1) / g.s);
   const int K = class_taps(g.kh, g.s, 0) * class_taps(g.kw, g.s, 0) * Cout;
-  switch (gather_tile(M, g.C, K, Cout, g.s * g.s, g.taps() * Cout)) {
+  switch (gather_tile(M, g.C, K, Cout, g.s * g.s, g.taps() * Cout, split)) {
     case TILE_128W8: return rev_t<Tile128W8>(g, n_img, Cout, ctz, wrev, epi, stream);
     case TILE_64X128: return rev_t<Tile64x128>(g, n_img, Cout, ctz, wrev, epi, stream);
+    case TILE_64K2: return rev_t<Tile64K2>(g, n_img, Cout, ctz, wrev, epi, stream);
     case TILE_S128: return rev_t<Split128>(g, n_img, Cout, ctz, wrev, epi, stream);
     case TILE_S64: return rev_t<Split64>(g, n_img, Cout, ctz, wrev, epi, stream);
     case TILE_S64Q: return rev_t<Split64Q>(g, n_img, Cout, ctz, wrev, epi, stream);
@@ -359,22 +364,22 @@ hipError_t conv_input_cotangent(const ConvGeom& g, int n_img, int Cout, const fl
   }
 }
 
-size_t conv_dw_part_floats(const ConvGeom& g, int n_img, int Cout) {
+size_t conv_dw_part_floats(const ConvGeom& g, int n_img, int Cout, bool split) {
   // the most slices any chunk of at most n_img images is split into
   const int K1 = g.taps() * g.C;
   int most = 1;
   for (int n = 1; n <= n_img; ++n) {
-    const int sl = plan_dw(K1, Cout, (int64_t)n * g.Ho * g.Wo).slices;
+    const int sl = plan_dw(K1, Cout, (int64_t)n * g.Ho * g.Wo, split).slices;
     if (sl > most) most = sl;
   }
   return (size_t)most * K1 * Cout;
 }
 
 hipError_t conv_dw(const ConvGeom& g, int n_img, const float* x, const float* ctz, int Cout, float scale, float beta,
-                   float* dW, float* part, hipStream_t stream) {
+                   float* dW, float* part, bool split, hipStream_t stream) {
   if (n_img <= 0) return hipSuccess;
   const int K1 = g.taps() * g.C;
-  const DwPlan p = plan_dw(K1, Cout, (int64_t)n_img * g.Ho * g.Wo);
+  const DwPlan p = plan_dw(K1, Cout, (int64_t)n_img * g.Ho * g.Wo, split);
   hipError_t e;
   switch (p.tile) {
     case TILE_S128: e = dw_t<Split128>(g, n_img, x, ctz, Cout, p, part, stream); break;

@@ -257,24 +257,27 @@ hipError_t conv_vijp_layer(const ConvGeom& g, int n_img, const float* x, const f
                            const float* hin, int hin_as_read, const float* Tinv, const uint32_t* mask32, float* xout, float* hout, float* ctz,
                            unsigned long long* mismatches, hipStream_t stream);
 // dW[K1][Cout] = scale * patches(x)^T ct_z + beta * dW, the patch rows split into slices whose partial
-// products (part: conv_dw_part_floats floats) are added in slice order
+// products (part: conv_dw_part_floats floats) are added in slice order. split, here and below: whether large products
+// take split operands (gemm_split.h); a training step's do not (Step::split).
 constexpr int CONV_DW_MAX_SLICES = 256;
-size_t conv_dw_part_floats(const ConvGeom& g, int n_img, int Cout);
+size_t conv_dw_part_floats(const ConvGeom& g, int n_img, int Cout, bool split);
 hipError_t conv_dw(const ConvGeom& g, int n_img, const float* x, const float* ctz, int Cout, float scale, float beta,
-                   float* dW, float* part, hipStream_t stream);
+                   float* dW, float* part, bool split, hipStream_t stream);
 
 // ct [rows][Cout] = sub(hin) Tinv^T: hin [n_img][H][W][C] at the strided positions, first Cout channels
-hipError_t conv_sub_solve(const ConvGeom& g, int n_img, int Cout, const float* hin, const float* Tinv, float* ct, hipStream_t stream);
+hipError_t conv_sub_solve(const ConvGeom& g, int n_img, int Cout, const float* hin, const float* Tinv, float* ct, bool split,
+                          hipStream_t stream);
 // the general vijp's sweep over the anti-diagonals of the output grid, in place on ct (which holds sub(h) Tinv^T);
 // Asweep: [Cout][((reach + 1)^2 - 1) Cout], slot (ky, kx) = T^{-1} w[p + (reach - ky) s][p + (reach - kx) s][:Cout]
-hipError_t conv_vijp_sweep(int Ho, int Wo, int Cout, int n_img, int reach, float* ct, const float* Asweep, hipStream_t stream);
+hipError_t conv_vijp_sweep(int Ho, int Wo, int Cout, int n_img, int reach, float* ct, const float* Asweep, bool split,
+                           hipStream_t stream);
 // whether conv_input_cotangent can be used (stride classes fit the task, channels in fours)
 bool conv_rev_ok(const ConvGeom& g, int Cout);
 // input cotangent of the layer for n_img images from ct_z [n_img][Ho][Wo][Cout]: raw (may be NULL) = h,
 // ct (may be NULL; needs C % 32 == 0) = h times the slope the previous layer's sign bits (mask32, flat
 // index of the input element) select: 1 or alpha. wrev: weights packed by cv_pack_rev_weights.
 hipError_t conv_input_cotangent(const ConvGeom& g, int n_img, int Cout, const float* ctz, const float* wrev, float* raw,
-                                float* ct, const uint32_t* mask32, float alpha, hipStream_t stream);
+                                float* ct, const uint32_t* mask32, float alpha, bool split, hipStream_t stream);
 // wrev (kh kw Cin Cout floats) = the per-stride-class transposed taps conv_input_cotangent multiplies with
 hipError_t cv_pack_rev_weights(const float* w, int kh, int kw, int s, int Cin, int Cout, float* wrev, hipStream_t stream);
 // rows x width floats from src (row stride src_ld) to dst (row stride dst_ld); all three multiples of 4, 16-byte aligned

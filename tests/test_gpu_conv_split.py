@@ -27,6 +27,10 @@ def draw(shape, seed):
     return rng, x, w, ct
 
 
+def cuda(*arrays):
+    return [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in arrays]
+
+
 def weight_gradient(mw, shape, x, ct):
     k, s, p = shape[5:]
     dw, _ = mw.conv_weight_grad(torch.from_numpy(x).cuda(), torch.from_numpy(ct).cuda(), k, k, s, p, p)
@@ -52,3 +56,22 @@ def test_weight_gradient_of_few_rows(mw, rows, Ci, Co):
         shape = (1, 1 if k == 1 else rows, rows if k == 1 else 1, Ci, Co, k, 1, (k - 1) // 2)
         _, x, _, ct = draw(shape, rows)
         check_weight_gradient(mw, shape, x, ct)
+
+
+def test_a_training_step_keeps_fp32_instructions(mw):
+    """A layer whose one tap is the identity: ct_z is the output cotangent and the update of the entries below the diagonal
+    is -lr x^T ct_z, bit for bit the product on fp32 instructions."""
+    B, side, C, alpha, lr = 4, 8, 64, 0.25, 0.5
+    rng = np.random.default_rng(2)
+    x, t = cuda(*(rng.standard_normal((B, side, side, C)).astype(np.float32) for _ in range(2)))
+    w, b = cuda(np.eye(C, dtype=np.float32)[None, None], np.zeros(C, np.float32))
+    net = mw.ConvMoonwalkNet([w], [b], [alpha], B, side, side, 1, 0, plan=mw.PLAN_MOONWALK)
+    net.sgd_step(x, t, lr)
+    torch.cuda.synchronize()
+    y, rows = torch.where(x > 0, x, alpha * x), B * side * side
+    h, _ = mw.loss_grad(y.reshape(B, -1), t.reshape(B, -1), 1.0)
+    ct = torch.where(x > 0, h.reshape(x.shape), alpha * h.reshape(x.shape))
+    raw = mw.gemm_f32(mw.GEMM_TN, x.reshape(rows, C), ct.reshape(rows, C), tile=mw.TILE_64)
+    below = torch.tril(torch.ones(C, C, device="cuda"), -1).bool()
+    assert torch.equal(net.ws[0].reshape(C, C)[below], (-lr * raw)[below])
+    net.close()
