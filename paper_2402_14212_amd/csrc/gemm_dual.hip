@@ -77,7 +77,9 @@ static hipError_t apart_d(int tile_d, int M, int N, int K, const VijpArgs& a, co
 }
 
 template <bool RELU>
-static hipError_t phase3_apart(int tile_v, int tile_d, const VijpArgs& a, int M, int N, int K, const DwArgs* d, hipStream_t stream) {
+static hipError_t phase3_apart(int tile_v, int tile_d, const VijpArgs& a, int M, int N, int K, const DwArgs* d, hipStream_t stream,
+                               uint64_t* more) {
+  *more += 1;
   hipError_t e = gemm_fwd_again(pick_tile_f32(M, N, K), M, N, K, a.X, a.W, a.bias, a.alpha, a.Xout, a.mask, a.mismatches, stream);
   if (e != hipSuccess) return e;
   const EpiCotangent<RELU> epi{a.alpha > 0.f ? 1.0f / a.alpha : 0.f, a.mask, a.offsets, a.frag, a.frag_base, a.frag_capacity, a.Hout, a.CTZ};
@@ -92,13 +94,15 @@ static hipError_t phase3_apart(int tile_v, int tile_d, const VijpArgs& a, int M,
                           : launch_gemm<Split64, KCONTIG, KCONTIG, ANone, EpiCotangent<RELU>, false>(M, N, K, a.Hin, K, a.P, K, ANone{}, epi, true,
                                                                                                     nullptr, 0.f, stream, 0.f);
   if (e != hipSuccess || !d) return e;
+  *more += 1;
   return gemm_dw(tile_d, d->M, d->N, d->K, d->CTZ, d->X, d->scale, d->dW, d->db, stream, d->beta);
 }
 
-hipError_t gemm_phase3_pair(int tile_v, const VijpArgs* v, int M, int N, int K, const DwArgs* d, int tile_d, hipStream_t stream) {
+hipError_t gemm_phase3_pair(int tile_v, const VijpArgs* v, int M, int N, int K, const DwArgs* d, int tile_d, hipStream_t stream,
+                            uint64_t* more) {
   if (v && tile_is_split(tile_v))
-    return v->alpha == 0.f ? phase3_apart<true>(tile_v, tile_d, *v, M, N, K, d, stream)
-                           : phase3_apart<false>(tile_v, tile_d, *v, M, N, K, d, stream);
+    return v->alpha == 0.f ? phase3_apart<true>(tile_v, tile_d, *v, M, N, K, d, stream, more)
+                           : phase3_apart<false>(tile_v, tile_d, *v, M, N, K, d, stream, more);
   if (v && d && !tile_is_split(tile_d) && tile_has_8_waves(tile_v) == tile_has_8_waves(tile_d) && M > 0 && N > 0 && d->M > 0 && d->N > 0 &&
       d->db) {
     const bool shapes_ok = extent_ok(M, K, K) && extent_ok(N, K, K) && extent_ok(M, N, N) &&
@@ -112,6 +116,7 @@ hipError_t gemm_phase3_pair(int tile_v, const VijpArgs* v, int M, int N, int K, 
   if (v) {
     hipError_t e = gemm_vijp_dual(tile_v, M, N, K, *v, stream);
     if (e != hipSuccess) return e;
+    if (d) *more += 1;
   }
   if (d) return gemm_dw(tile_d, d->M, d->N, d->K, d->CTZ, d->X, d->scale, d->dW, d->db, stream, d->beta);
   return hipSuccess;
@@ -240,7 +245,7 @@ static hipError_t bp_pair_r(int tile_r, int tile_d, const BpLayerArgs& a, hipStr
   }
 }
 
-hipError_t gemm_bp_layer(const BpLayerArgs& a, hipStream_t stream) {
+hipError_t gemm_bp_layer(const BpLayerArgs& a, hipStream_t stream, uint64_t* more) {
   const int tile_r = a.Hout ? pick_tile(a.batch, a.d_in, a.d_out) : TILE_AUTO;
   const int tile_d = bp_dw_tile(a.d_out, a.d_in, a.batch, tile_r);
   if (a.Hout && a.batch > 0 && a.d_in > 0 && a.d_out > 0) {
@@ -253,6 +258,7 @@ hipError_t gemm_bp_layer(const BpLayerArgs& a, hipStream_t stream) {
   }
   hipError_t e = gemm_dw_act(tile_d, a.d_out, a.d_in, a.batch, a.Hy, a.act, a.alpha, a.Xprev, a.scale, a.dW, a.db, stream);
   if (e != hipSuccess || !a.Hout) return e;
+  *more += 1;
   return gemm_rev_act(tile_r, a.batch, a.d_in, a.d_out, a.Hy, a.act, a.alpha, a.W, a.Hout, stream);
 }
 

@@ -838,18 +838,20 @@ int phase3_range(const Step& c, int lo, int hi, const float* xin, const float* h
         d.db = c.grads_out + l.db_off;
       }
       if (paired) {
-        MW_LAUNCH(h, s, MW_KCLASS_PHASE3, gemm_phase3_pair(phase3_tile(B, l.d_out, l.d_in, c.split()), &a, B, l.d_out, l.d_in, have_pending ? &pending : nullptr, pending_tile, s));
+        MW_LAUNCH(h, s, MW_KCLASS_PHASE3, gemm_phase3_pair(phase3_tile(B, l.d_out, l.d_in, c.split()), &a, B, l.d_out, l.d_in,
+                                                           have_pending ? &pending : nullptr, pending_tile, s, &h->launches[MW_KCLASS_PHASE3]));
         pending = d;
         pending_tile = tile_d;
         have_pending = true;
       } else {
-        MW_LAUNCH(h, s, MW_KCLASS_VIJP, gemm_phase3_pair(phase3_tile(B, l.d_out, l.d_in, c.split()), &a, B, l.d_out, l.d_in, nullptr, TILE_AUTO, s));
+        MW_LAUNCH(h, s, MW_KCLASS_VIJP, gemm_phase3_pair(phase3_tile(B, l.d_out, l.d_in, c.split()), &a, B, l.d_out, l.d_in,
+                                                         nullptr, TILE_AUTO, s, &h->launches[MW_KCLASS_VIJP]));
         MW_LAUNCH(h, s, MW_KCLASS_DW, gemm_dw(tile_d, d.M, d.N, d.K, d.CTZ, d.X, d.scale, d.dW, d.db, s, d.beta));
       }
       xin = xout;
       hin = hout;
     }
-    if (have_pending) MW_LAUNCH(h, s, MW_KCLASS_PHASE3, gemm_phase3_pair(TILE_AUTO, nullptr, 0, 0, 0, &pending, pending_tile, s));
+    if (have_pending) MW_LAUNCH(h, s, MW_KCLASS_PHASE3, gemm_phase3_pair(TILE_AUTO, nullptr, 0, 0, 0, &pending, pending_tile, s, &h->launches[MW_KCLASS_PHASE3]));
   } else {
     for (int i = lo; i < hi; ++i) {
       Layer& l = h->layers[i];
@@ -1239,7 +1241,7 @@ int backprop_grad(mw_handle_t* h, const float* x, const float* target, float* gr
     BpLayerArgs a{B, l.d_out, l.d_in, hbuf[sel], l.act, l.alpha, xprev, l.W, inv_scale,
                   grads_out + l.dW_off, grads_out + l.db_off, i > 0 ? hbuf[sel ^ 1] : nullptr};
     if (h->class_filter < 0) {
-      MW_LAUNCH(h, s, MW_KCLASS_PHASE3, gemm_bp_layer(a, s));
+      MW_LAUNCH(h, s, MW_KCLASS_PHASE3, gemm_bp_layer(a, s, &h->launches[MW_KCLASS_PHASE3]));
     } else {
       const int tile_r = (i > 0) ? pick_tile(B, l.d_in, l.d_out) : TILE_AUTO;
       MW_LAUNCH(h, s, MW_KCLASS_DW, gemm_dw_act(bp_dw_tile(l.d_out, l.d_in, B, tile_r), l.d_out, l.d_in, B, a.Hy, a.act, a.alpha,

@@ -121,8 +121,9 @@ struct DwArgs {
   float* db;            // [M] or NULL
   float beta = 0.f;     // dW = scale * product + beta * dW (same for db): 1 applies an update in place
 };
-// tile_v, tile_d: phase3_tile's and phase3_dw_tile's.
-hipError_t gemm_phase3_pair(int tile_v, const VijpArgs* v, int M, int N, int K, const DwArgs* d, int tile_d, hipStream_t stream);
+// tile_v, tile_d: phase3_tile's and phase3_dw_tile's. *more, here and below: grows by the kernels launched beyond the first.
+hipError_t gemm_phase3_pair(int tile_v, const VijpArgs* v, int M, int N, int K, const DwArgs* d, int tile_d, hipStream_t stream,
+                            uint64_t* more);
 
 // Phase III for several independent stretches of the network in one launch: n_v layer kernels of one shape
 // (M x N x K each, the same alpha) and n_d weight-gradient products of one shape (the same scale and beta; a
@@ -148,7 +149,7 @@ struct BpLayerArgs {
   float* db;
   float* Hout;         // [B][d_in] or NULL
 };
-hipError_t gemm_bp_layer(const BpLayerArgs& a, hipStream_t stream);
+hipError_t gemm_bp_layer(const BpLayerArgs& a, hipStream_t stream, uint64_t* more);
 
 // ---- elementwise / integer kernels (elementwise.hip) ----
 hipError_t ew_bias_act_mask(const float* zin, const float* bias, int64_t rows, int d, float alpha, float* x,

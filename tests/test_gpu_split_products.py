@@ -203,3 +203,17 @@ def test_phase3_in_two_launches(mw, widths, alphas):
         assert O.normwise_rel_err(res[0].db[i].cpu().numpy(), res[1].db[i].cpu().numpy()) < 1e-5
     for net in nets:
         net.close()
+
+
+@pytest.mark.parametrize("widths,kernels", [
+    ((1152, 1024, 1024), 5),     # activation and cotangent twice (the second with the first weight gradient), one left
+    ((1029, 1027, 1025), 6),     # every product by itself
+    ((96, 96, 96), 3),           # one kernel for both products
+])
+def test_every_phase3_kernel_is_counted(mw, widths, kernels):
+    wl = make_mlp(list(widths), 776, [0.3, 0.3], seed=3, reseed_interval=0, name="split")
+    net = mw.MoonwalkNet.from_workload(wl)
+    net.moonwalk_grad(net.x, net.t)
+    torch.cuda.synchronize()
+    assert net.profile_launches()["phase3"] == kernels
+    net.close()
