@@ -18,6 +18,14 @@
 // products at a time. Normwise error against fp64 for N(0, 1) operands, K = 128 / 512 / 2048:
 // 1.1e-7 / 2.4e-7 / 4.9e-7, with the fp32 instruction 2.0e-7 / 4.1e-7 / 8.1e-7 (5.7e-7 with K split in two).
 //
+// Sign. The bf16 unit brings the products of an instruction and the running sum to one exponent and rounds what falls
+// off downwards, whatever its sign (measured: the error has the same mean for A B and -A B). Products of lower parts
+// have bits there, so that every result came out low by 1.5e-7 of the results' rms (K = 4096), a fifth of its rounding
+// error. A weight gradient, a sum over samples, averages rounding errors but not that: 2.2e-4 off, four layers after a
+// re-seed at width 4096 (fp32 instructions 1.4e-4). So one half of K is summed with A negated: the running sum changes
+// its sign every SPLIT_TURN K tiles, and the K groups have opposite ones. The means of the two halves cancel (3e-10
+// is left, and the gradient is 1.3e-4 off); it costs 1 % of the time.
+//
 // Range. bf16 has fp32's exponents, but the lower parts of values below 2^-110 would fall under its subnormals. So both
 // operands are multiplied by 2^SPLIT_UP on their way (exact; the least part of the least subnormal is then a normal
 // bf16) and the result is scaled back. Values from 2^(127 - SPLIT_UP) on, infinities, NaN and sums beyond
@@ -64,6 +72,8 @@ template <class Cfg>
 constexpr bool is_split() { return Cfg::PREC == 2; }
 
 constexpr int SPLIT_UP = 24;   // see `Range` above
+constexpr int SPLIT_TURN = 4;  // see `Sign` above: K tiles in a row of one sign (even)
+__device__ __forceinline__ float split_up(bool negative) { return negative ? -(float)(1 << SPLIT_UP) : (float)(1 << SPLIT_UP); }
 
 // Byte address of the 8-k chunk c of a row inside a plane of rows of BK halves. The xor (and for 64-byte rows the
 // exchange of neighbouring rows) spreads the rows that a wavefront reads (32 rows, one chunk) or writes (eight
@@ -84,10 +94,10 @@ __device__ __forceinline__ uint32_t bf16_pair(float x, float y) {
   asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(d) : "v"(x), "v"(y));
   return d;
 }
-__device__ __forceinline__ SplitPair split_pair(float x, float y, float& top) {
+__device__ __forceinline__ SplitPair split_pair(float x, float y, float up, float& top) {
   SplitPair p;
-  x *= (float)(1 << SPLIT_UP);
-  y *= (float)(1 << SPLIT_UP);
+  x *= up;
+  y *= up;
   top = fmaxf(fmaxf(fabsf(x), fabsf(y)), top);
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
@@ -151,16 +161,20 @@ struct SplitLoader {
   static __device__ __forceinline__ int row_of(int j) { return LAYOUT == KCONTIG ? Map::row(j) : Map::row((j / 4) * KP) + (j & 3); }
 };
 
-// Split the staged values of `ld` into the planes of an LDS stage (`base`: this operand's rows of the first plane).
-template <int PLANE, bool COLSUM, int NT, int BK, class Ld, class XfDev>
+// Split the staged values of `ld` into the planes of an LDS stage (`base`: this operand's rows of the first plane). SIGNED:
+// operand A, negated if `negative` and, once more, where the second K group reads it.
+template <class Cfg, bool SIGNED, bool COLSUM, class Ld, class XfDev>
 __device__ __forceinline__ void split_store(const Ld& ld, const XfDev& xf, char* __restrict__ base, float* __restrict__ csum,
-                                            float& top) {
+                                            float& top, bool negative) {
   using Map = typename Ld::Map;
+  constexpr int BK = Cfg::BK, NT = Cfg::NT, PLANE = Cfg::PLANE;
+  // (k: the same 16-k step for all of a chunk)
+  auto up = [&](int k) { return split_up(SIGNED && (negative != (Cfg::WK == 2 && ((k >> 4) & 1)))); };
   if constexpr (Ld::KP == 1) {
 #pragma unroll
     for (int i = 0; i < Ld::NV; ++i) {
       const float4 w = xf.apply(ld.v[i], ld.aux[i]);
-      const SplitPair a = split_pair(w.x, w.y, top), b = split_pair(w.z, w.w, top);
+      const SplitPair a = split_pair(w.x, w.y, up(Map::k(0)), top), b = split_pair(w.z, w.w, up(Map::k(0)), top);
       // a thread's chunks are the same k of rows so far apart that they have the same pattern of chunks
       static_assert(NT * 4 / BK % (BK == 32 ? 32 : 16) == 0, "see split_addr");
       char* p = base + split_addr<BK>(Map::row(0), Map::k(0) >> 3) + (Map::k(0) & 4) * 2 + i * (NT * 4 / BK) * BK * 2;
@@ -192,7 +206,7 @@ __device__ __forceinline__ void split_store(const Ld& ld, const XfDev& xf, char*
         for (int h = 0; h < Ld::KP / 2; ++h) {
           const float x = e[q][2 * h], y = e[q][2 * h + 1];
           if (COLSUM) csum[4 * j + q] += x + y;
-          s[h] = split_pair(x, y, top);
+          s[h] = split_pair(x, y, up(k), top);
         }
         char* p = base + split_addr<BK>(row + q, k >> 3) + (k & 7) * 2;
 #pragma unroll
@@ -279,42 +293,46 @@ struct SplitProduct {
     MW_REQUEST(1, 1);
     if (threadIdx.x < 3) flag[threadIdx.x] = 0;
 
-#define MW_TO_LDS(slot, stage)                                                                                            \
+    // idx: the K tile
+#define MW_TO_LDS(slot, stage, idx)                                                                                       \
   do {                                                                                                                    \
-    split_store<Cfg::PLANE, COLSUM, NT, BK>(a[slot], xf, lds + (stage) * Cfg::STAGE, csum, top_a);                        \
-    split_store<Cfg::PLANE, false, NT, BK>(b[slot], none, lds + (stage) * Cfg::STAGE + BM * BK * 2, (float*)nullptr, top_b); \
+    split_store<Cfg, true, COLSUM>(a[slot], xf, lds + (stage) * Cfg::STAGE, csum, top_a, ((idx) / SPLIT_TURN) & 1);        \
+    split_store<Cfg, false, false>(b[slot], none, lds + (stage) * Cfg::STAGE + BM * BK * 2, (float*)nullptr, top_b, false); \
   } while (0)
 #define MW_MULTIPLY(stage) multiply(lds + (stage) * Cfg::STAGE, wm, wn, wk, r, g, acc)
-    MW_TO_LDS(0, 0);
+    MW_TO_LDS(0, 0, 0);
     MW_REQUEST(0, 2);
     __syncthreads();
     // tile t is in LDS stage t % 2, the registers hold tiles t + 1 and t + 2. The last tile is peeled off: after it
     // nothing is staged.
-#define MW_STEP(u)                        \
-  do {                                    \
-    MW_MULTIPLY(u);                       \
-    MW_TO_LDS(1 - (u), 1 - (u));          \
-    MW_REQUEST(1 - (u), t + (u) + 3);     \
-    __syncthreads();                      \
+#define MW_STEP(u)                                   \
+  do {                                               \
+    MW_MULTIPLY(u);                                  \
+    MW_TO_LDS(1 - (u), 1 - (u), t + (u) + 1);        \
+    MW_REQUEST(1 - (u), t + (u) + 3);                \
+    __syncthreads();                                 \
   } while (0)
     int t = 0;
     for (; t + 2 < nkt; t += 2) {
+      turn(t, acc);
       MW_STEP(0);
       MW_STEP(1);
     }
+    turn(t, acc);
     if (t + 1 < nkt) {   // two tiles are left, or one
       MW_STEP(0);
       MW_MULTIPLY(1);
     } else {
       MW_MULTIPLY(0);
     }
+    if ((t / SPLIT_TURN) & 1) negate(acc);
 #undef MW_STEP
 #undef MW_TO_LDS
 #undef MW_MULTIPLY
 #undef MW_REQUEST
     // Add the K groups. A wavefront keeps CNT registers of every tile and hands the others over through LDS.
     __syncthreads();   // the stages are free
-    finish(lds_f, acc, out, wm, wn, wk, lane);
+    finish<true>(lds_f, acc, out, wm, wn, wk, lane);
     bool finite = true;
 #pragma unroll
     for (int i = 0; i < Cfg::NACC; ++i)
@@ -336,6 +354,18 @@ struct SplitProduct {
     top_b = __uint_as_float(flag[2]);
     if (top_a < 0x1p126f && top_b < 0x1p126f && top_a * top_b * (float)K < 0x1p126f) return;
     repeat_f32(ra, lda, rb, ldb, M, N, K, m0, n0, lds_f, xf, out, nkt, wm, wn, wk, r, g, lane);
+  }
+
+  static __device__ __forceinline__ void negate(f32x16 (&acc)[Cfg::NACC]) {
+#pragma unroll
+    for (int i = 0; i < Cfg::NACC; ++i)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) acc[i][j] = -acc[i][j];
+  }
+  // before K tile t (even) is multiplied
+  static __device__ __forceinline__ void turn(int t, f32x16 (&acc)[Cfg::NACC]) {
+    static_assert(Cfg::WK <= 2 && SPLIT_TURN % 2 == 0, "one sign or two");
+    if (t > 0 && t % SPLIT_TURN == 0) negate(acc);
   }
 
   __device__ __forceinline__ void multiply(const char* __restrict__ st, int wm, int wn, int wk, int r, int g,
@@ -410,7 +440,7 @@ struct SplitProduct {
     }
     __syncthreads();
     float again[Cfg::NACC][Cfg::CNT];
-    finish(lds, acc, again, wm, wn, wk, lane);
+    finish<false>(lds, acc, again, wm, wn, wk, lane);
 #pragma unroll
     for (int i = 0; i < Cfg::NACC; ++i)
 #pragma unroll
@@ -418,8 +448,10 @@ struct SplitProduct {
         if (!(fabsf(out[i][j]) < __builtin_inff())) out[i][j] = again[i][j];
   }
 
-  // Sums of one accumulator register over the K groups, in the order of the groups. Entered with the LDS stages free;
+  // Sums of one accumulator register over the K groups, in the order of the groups (SIGNED: the second group's taken away,
+  // see `Sign` above). Entered with the LDS stages free;
   // the caller's next use of LDS follows a barrier of its own.
+  template <bool SIGNED>
   __device__ __forceinline__ void finish(float* __restrict__ lds, const f32x16 (&acc)[Cfg::NACC],
                                          float (&out)[Cfg::NACC][Cfg::CNT], int wm, int wn, int wk, int lane) const {
     constexpr int CNT = Cfg::CNT, WK = Cfg::WK, NACC = Cfg::NACC;
@@ -451,7 +483,7 @@ struct SplitProduct {
           for (int w = 0; w < WK; ++w) {
             const float other = base[slot(wk, w, t, j)];
             const float part = w == wk ? own : other;
-            sum = w == 0 ? part : sum + part;
+            sum = w == 0 ? part : (SIGNED ? sum - part : sum + part);
           }
           out[t][j] = sum;
         }

@@ -183,6 +183,17 @@ def test_no_less_precise_than_fp32_instructions(mw, op, M, K):
     assert split <= f32
 
 
+@pytest.mark.parametrize("op,M,N,K", SIZES + [(NT, 1024, 1024, 2048), (NN, 1536, 1536, 2048), (TN, 2304, 2304, 1024)])
+def test_errors_have_no_common_sign(mw, op, M, N, K):
+    """The mean error of a million results or more. Independent errors leave about a thousandth of their rms, of one sign
+    a fifth of it; sums over samples would keep that."""
+    _, A, B = operands(K, M, N, K)
+    err = product(mw, op, A, B) - A.astype(np.float64) @ B.astype(np.float64).T
+    rms = np.sqrt(np.mean(err * err))
+    print("op=%d K=%d: mean error %.2g of its rms" % (op, K, err.mean() / rms), flush=True)
+    assert abs(err.mean()) <= 0.03 * rms
+
+
 @pytest.mark.parametrize("widths,alphas", [
     ((1152, 1024, 1024, 192), (0.3, 0.3, 0.3)),     # 64 x 64 tiles; the last layer is too small for split operands
     ((1029, 1027, 1025), (0.3, 0.3)),               # element-wise loads: every product in a launch of its own
