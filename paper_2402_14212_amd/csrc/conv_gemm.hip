@@ -135,12 +135,14 @@ DwPlan plan_dw(int K1, int Cout, int64_t rows, bool split) {
   DwPlan p;
   int bm, bn, room, step;
   if (split && rows >= DW_SPLIT_MIN_ROWS) {
-    // 128 x 128 where that fills the chip with slices of 256 rows; one round of workgroups (two of the small tile)
+    // 128 x 128 where that fills the chip with slices of 256 rows; one round of workgroups, of which a CU holds one (us with
+    // two rounds of the small tile and with one: 2904 rows, 1152 x 128 31.3 and 25.2; 16000 rows, 576 x 64 43.5 and 31.9;
+    // 57624 rows, 1600 x 32 130 and 122)
     const int64_t tiles128 = (int64_t)ceil_div(K1, 128) * ceil_div(Cout, 128);
     const bool large = K1 > 64 && Cout > 64 && rows * tiles128 >= 256 * 256;
     p.tile = large ? TILE_S128 : TILE_S64;
     bm = bn = large ? 128 : 64;
-    room = large ? 256 : 512;
+    room = 256;
     step = 64;
   } else {
     // four workgroups per CU
