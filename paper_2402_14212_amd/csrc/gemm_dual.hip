@@ -246,7 +246,7 @@ static hipError_t bp_pair_r(int tile_r, int tile_d, const BpLayerArgs& a, hipStr
 }
 
 hipError_t gemm_bp_layer(const BpLayerArgs& a, hipStream_t stream, uint64_t* more) {
-  const int tile_r = a.Hout ? pick_tile(a.batch, a.d_in, a.d_out) : TILE_AUTO;
+  const int tile_r = a.Hout ? bp_rev_tile(a.d_out, a.d_in, a.batch) : TILE_AUTO;
   const int tile_d = bp_dw_tile(a.d_out, a.d_in, a.batch, tile_r);
   if (a.Hout && a.batch > 0 && a.d_in > 0 && a.d_out > 0) {
     const bool shapes_ok = extent_ok(a.batch, a.d_out, a.d_out) && extent_ok(a.batch, a.d_in, a.d_in) &&

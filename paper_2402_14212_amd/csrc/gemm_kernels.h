@@ -789,7 +789,7 @@ inline bool extent_ok(int64_t n_outer, int64_t n_inner, int64_t ld) {
   return n_outer <= 0 || n_inner <= 0 || ((n_outer - 1) * ld + n_inner) * 4 < (int64_t)0x7FFFFFFF;
 }
 
-// Kernels here use up to ~130 KiB of dynamic LDS (the CU has 160 KiB); anything above the
+// Kernels here use up to 145 KiB of dynamic LDS (the CU has 160 KiB); anything above the
 // default limit needs it raised once per kernel.
 template <class KernelT>
 inline hipError_t ensure_lds(KernelT kernel, int bytes) {

@@ -63,14 +63,17 @@ int pick_tile_f32(int M, int N, int K) {
 }
 
 // Split operands where they are faster than the fp32 tile of the same product, measured over NT, NN and TN (us, fp32
-// against split): from half a round of 128 x 128 tiles (132 of them, 1408 x 1536: K = 256 17.8 and 15.4, 1024 57 and
-// 41; 128 of them, 1024 x 2048: K = 256 14.3 and 16.0, 1024 44.1 and 44.2, 2048 74.5 and 70.2; two rounds, 2176 x
-// 2176: K = 128 18.6 and 20.5, 512 53 and 47), and where 64 x 64 tiles make one round that is nearly full (1024 x 1024: K = 512 14.5
-// and 11.7, 1024 23.8 and 22.5; 512 x 2048 x 2048 46 and 42). Fewer are better spread over 32 x 32 fp32 tiles (512 x 1024 x 1024:
-// 16.4 and 20.1), more 64 x 64 tiles are a second round.
+// against split): from an output of half a round of 128 x 128 tiles (1408 x 1536, 132 of them: K = 256 17.8 and 15.4,
+// 1024 57 and 41; 1024 x 2048, 128: K = 256 14.3 and 16.0, 1024 44.1 and 44.2, 2048 74.5 and 70.2; 2176 x 2176, two
+// rounds: K = 128 18.6 and 20.5, 512 53 and 47), by its size, since as many tiles of a narrow one are mostly padding
+// (130 x 8448 x 300 14.9 and 16.7, 32 x 40960 x 512 30 and 34), and where 64 x 64 tiles make one round that is
+// nearly full (1024 x 1024: K = 512 14.5 and 11.7, 1024 23.8 and 22.5; from 2048 of K the K-split fp32 tile is as fast,
+// 512 x 2048 46 and 42 to 46, by how far the card clocks down). Fewer are better spread over 32 x 32 fp32 tiles (512 x
+// 1024 x 1024: 16.4 and 20.1), more 64 x 64 tiles are a second round.
 bool split_pays(int64_t sets, int M, int N, int K) {
-  const int64_t t64 = sets * tiles_of(M, N, 64, 64), t128 = sets * tiles_of(M, N, 128, 128);
-  return (K >= SPLIT_MIN_K && t128 > (K >= 1024 ? 127 : 128)) || (K >= 512 && t64 >= 192 && t64 <= 256);
+  const int64_t t64 = sets * tiles_of(M, N, 64, 64), size = sets * M * N, half_a_round = 128 * 128 * 128;
+  return (K >= SPLIT_MIN_K && (K >= 1024 ? size >= half_a_round : size > half_a_round)) ||
+         (K >= 512 && K < 2048 && t64 >= 192 && t64 <= 256);
 }
 
 int pick_tile(int M, int N, int K) {
@@ -81,12 +84,12 @@ int pick_tile_tn(int M, int N, int K) {
   return split_pays(1, M, N, K) ? pick_split_tile(1, M, N, true) : pick_tile_f32(M, N, K);
 }
 
-// Where the cotangent product of Phase III takes split operands, it goes by itself (whole gradients, us, in one fp32
-// kernel and apart: eight layers of 1024 x 1024 x 1024 1146 and 819 to 862; six of 4096 x 4096, batch 1024, 7770 and
-// 6330 to 6700; eight of 2048 x 2048, batch 512, 1500 and 1430 to 1530, by how far the card clocks down).
-// Smaller layers keep the one kernel for both products, whose launches are fewer and can be grouped over stretches.
+// Where a layer's cotangent product and its weight gradient both take split operands, the activation is recomputed by a
+// launch of its own (whole gradients, us, in one fp32 kernel and apart: eight layers of 1024 x 1024 x 1024 1146 and 819
+// to 862; six of 4096 x 4096, batch 1024, 7770 and 6330 to 6640). Other layers keep the one kernel for both products,
+// whose launches are fewer and can be grouped over stretches.
 int phase3_tile(int M, int N, int K, bool split) {
-  return split && split_pays(1, M, N, K) ? pick_split_tile(1, M, N, false) : pick_tile_f32(M, N, K);
+  return split && split_pays(1, M, N, K) && split_pays(1, N, K, M) ? pick_split_tile(1, M, N, false) : pick_tile_f32(M, N, K);
 }
 
 int pick_tile_dw_f32(int M, int N, int partner, bool phase3) {
@@ -104,6 +107,10 @@ int phase3_dw_tile(int B, int d_out, int d_in, int next_out, bool split) {
   if (tile_is_split(phase3_tile(B, d_out, d_in, split)) || (d_in < SPLIT_MIN_K && tile_is_split(partner)))
     return pick_split_tile(1, d_out, d_in, true);
   return pick_tile_dw_f32(d_out, d_in, partner, true);
+}
+
+int bp_rev_tile(int d_out, int d_in, int B) {
+  return split_pays(1, B, d_in, d_out) && split_pays(1, d_out, d_in, B) ? pick_split_tile(1, B, d_in, false) : pick_tile_f32(B, d_in, d_out);
 }
 
 int bp_dw_tile(int d_out, int d_in, int B, int partner) {
@@ -1243,7 +1250,7 @@ int backprop_grad(mw_handle_t* h, const float* x, const float* target, float* gr
     if (h->class_filter < 0) {
       MW_LAUNCH(h, s, MW_KCLASS_PHASE3, gemm_bp_layer(a, s, &h->launches[MW_KCLASS_PHASE3]));
     } else {
-      const int tile_r = (i > 0) ? pick_tile(B, l.d_in, l.d_out) : TILE_AUTO;
+      const int tile_r = (i > 0) ? bp_rev_tile(l.d_out, l.d_in, B) : TILE_AUTO;
       MW_LAUNCH(h, s, MW_KCLASS_DW, gemm_dw_act(bp_dw_tile(l.d_out, l.d_in, B, tile_r), l.d_out, l.d_in, B, a.Hy, a.act, a.alpha,
                                                 a.Xprev, a.scale, a.dW, a.db, s));
       if (i > 0) MW_LAUNCH(h, s, MW_KCLASS_REV, gemm_rev_act(tile_r, B, l.d_in, l.d_out, a.Hy, a.act, a.alpha, a.W, a.Hout, s));

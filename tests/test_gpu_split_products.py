@@ -68,6 +68,9 @@ SIZES = [(NT, 900, 1020, 520), (NT, 1436, 1500, 264), (NN, 900, 1020, 520), (NN,
     (1501, 1433, 259, 0),    # odd
     (1500, 1412, 300, 1),    # an unaligned leading dimension
     (1024, 2048, 1024, 0),   # 128 tiles: from this K on
+    (1024, 1024, 2044, 0),   # one round of 64 x 64 tiles up to this K
+    (1024, 1024, 2048, 0),
+    (130, 8448, 300, 0),     # as many tiles, mostly padding: fp32 tiles
     (2177, 2304, 256, 0),    # one row more than the tiles; TN: 256 x 128 tiles
 ])
 def test_tile_edges(mw, op, M, N, K, pad):
@@ -173,7 +176,7 @@ def test_values_that_do_not_fit(mw, op, M, N, K):
 
 
 @pytest.mark.parametrize("op", [NT, NN, TN])
-@pytest.mark.parametrize("M,K", [(1024, 512), (1024, 2048), (1536, 256), (1536, 1024)])
+@pytest.mark.parametrize("M,K", [(1024, 512), (1024, 1920), (1536, 256), (1536, 2048)])
 def test_no_less_precise_than_fp32_instructions(mw, op, M, K):
     _, A, B = operands(K, M, M, K)
     f32_tile = mw.TILE_64K2 if K >= 1024 else mw.TILE_64
@@ -183,7 +186,7 @@ def test_no_less_precise_than_fp32_instructions(mw, op, M, K):
     assert split <= f32
 
 
-@pytest.mark.parametrize("op,M,N,K", SIZES + [(NT, 1024, 1024, 2048), (NN, 1536, 1536, 2048), (TN, 2304, 2304, 1024)])
+@pytest.mark.parametrize("op,M,N,K", SIZES + [(NT, 1024, 1024, 1920), (NN, 1536, 1536, 2048), (TN, 2304, 2304, 1024)])
 def test_errors_have_no_common_sign(mw, op, M, N, K):
     """The mean error of a million results or more. Independent errors leave about a thousandth of their rms, of one sign
     a fifth of it; sums over samples would keep that."""
@@ -195,11 +198,11 @@ def test_errors_have_no_common_sign(mw, op, M, N, K):
 
 
 @pytest.mark.parametrize("widths,alphas", [
-    ((1152, 1024, 1024, 192), (0.3, 0.3, 0.3)),     # 64 x 64 tiles; the last layer is too small for split operands
-    ((1029, 1027, 1025), (0.3, 0.3)),               # element-wise loads: every product in a launch of its own
+    ((1024, 1024, 1024, 192), (0.3, 0.3, 0.3)),     # 64 x 64 tiles; the last layer is too small for split operands
+    ((1023, 1022, 1021), (0.3, 0.3)),               # element-wise loads: every product in a launch of its own
     ((96, 96), (0.3,)),                             # all of it below
-    ((1088, 1056, 1024), (0.0, 0.0)),               # the fragment store restored in the cotangent's launch
-    ((2560, 2432), (0.3,)),                         # 128 x 128 tiles
+    ((1024, 1008, 992), (0.0, 0.0)),               # the fragment store restored in the cotangent's launch
+    ((2816, 2752), (0.3,)),                         # 128 x 128 tiles
 ])
 def test_phase3_in_two_launches(mw, widths, alphas):
     """The activation and the cotangent of a layer in launches of their own: against the oracle on the same signs, and
@@ -217,8 +220,8 @@ def test_phase3_in_two_launches(mw, widths, alphas):
 
 
 @pytest.mark.parametrize("widths,kernels", [
-    ((1152, 1024, 1024), 5),     # activation and cotangent twice (the second with the first weight gradient), one left
-    ((1029, 1027, 1025), 6),     # every product by itself
+    ((1024, 1024, 1024), 5),     # activation and cotangent twice (the second with the first weight gradient), one left
+    ((1023, 1022, 1021), 6),     # every product by itself
     ((96, 96, 96), 3),           # one kernel for both products
 ])
 def test_every_phase3_kernel_is_counted(mw, widths, kernels):
