@@ -95,7 +95,8 @@ typedef struct {
                                waits for them at the end of the call, so the call still looks asynchronous on
                                hip_stream alone. 0: everything on hip_stream, Phase III after Phase II.           */
   int32_t refresh_precision; /* moonwalk_refresh_incremental / moonwalk_sgd_step. 0: every product of a Schulz iteration in
-                               fp32. 1: the residual R = I - P W^T in fp32 (that difference is where digits are lost),
+                               fp32 (as mw_gemm_f32 with MW_TILE_AUTO forms it, below). 1: the residual R = I - P W^T
+                               like that (the difference is where digits are lost),
                                the correction R P that is then added to P with its operands rounded to bf16 (to nearest
                                even) in front of the matrix unit, sums and the addition in fp32: the correction is
                                ||R|| times the size of P, so its 2^-8 relative error is 2^-8 ||R|| of P, and the next
@@ -418,7 +419,10 @@ const char* moonwalk_strerror(int code);
 #define MW_TILE_64K2 5  /* 64x64 workgroup tile, K split over two groups of four wavefronts */
 #define MW_TILE_128W8 6 /* 128x128 workgroup tile, eight wavefronts                     */
 #define MW_TILE_64X128 7 /* 64x128 workgroup tile, eight wavefronts                     */
-/* fp32 MFMA GEMM with LDS-staged tiles; lda/ldb/ldc are row strides in floats. */
+/* fp32 GEMM on matrix instructions with LDS-staged tiles; lda/ldb/ldc are row strides in floats. The named tiles use fp32
+   instructions. MW_TILE_AUTO takes one of them, or for large products bf16 instructions on operands that are split
+   into three bf16 parts each (all 24 bits of a value; what is left out of a product a b is at most 2^-24 |a b|), summed
+   in fp32: |C - A B| <= K 2^-24 sum |a b| either way, infinities and NaN as fp32 instructions give them. */
 int mw_gemm_f32(int32_t op, int32_t tile, int32_t M, int32_t N, int32_t K, float alpha,
                 const float* A, int32_t lda, const float* B, int32_t ldb, float beta,
                 float* C, int32_t ldc, void* hip_stream);
