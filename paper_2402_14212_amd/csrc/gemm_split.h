@@ -58,15 +58,15 @@ struct SplitCfg {
   static constexpr int LDS_BYTES = MAIN + 16;   // + a flag
   static_assert((BM + BN) * (BK + 4) * 4 <= 2 * STAGE, "the fp32 repeat stages its tile in the same memory");
 };
-// Shapes that were fastest over the layer sizes in use (us at M x N x K; 512 threads each):
+// Shapes that were fastest over the layer sizes in use (us at M x N x K; 512 threads each, one workgroup to a CU):
 //   Split256  4096 x 4096 x 1024 (TN): 188 (128 x 128: 200)
 //   Split128  2048 x 2048 x 2048: 94 (64 x 64: 150), 2048 x 2048 x 512 (TN): 30 (64 x 64: 51)
-//   Split64   512 x 2048 x 2048: 42 (128 x 128: 71)
+//   Split64   1024 x 1024 x 1024: 22.5 (128 x 128: 38.6)
 using Split256 = SplitCfg<2, 2, 4, 2, 1, 2>;  // 256 x 128, K tile 32
 using Split128 = SplitCfg<2, 2, 2, 2, 2, 1>;  // 128 x 128, K tile 32, K split over two groups of four wavefronts
 using Split64 = SplitCfg<1, 1, 2, 2, 2, 2>;   //  64 x  64, K tile 64, likewise
 
-using Split64Q = SplitCfg<1, 1, 2, 2, 1, 2>;  // 64 x 64, K tile 32, four wavefronts: gathers of 32 channels and odd multiples
+using Split64Q = SplitCfg<1, 1, 2, 2, 1, 2>;  // 64 x 64, K tile 32, four wavefronts, three to a CU: gathers, see gather_tile
 
 template <class Cfg>
 constexpr bool is_split() { return Cfg::PREC == 2; }

@@ -28,8 +28,8 @@ static int64_t tiles_of(int m, int n, int tm, int tn) { return (int64_t)((m + tm
 
 // The split tile with the least time for `sets` outputs of M x N. One workgroup of each runs on a CU at a time, so
 // the time is the number of rounds of 256 workgroups times a round's length; relative lengths measured at K = 1024
-// (us a round): 256 x 128 94, 128 x 128 50, 64 x 64 26 (21 alone). For example 512 x 2048 x 2048: 256 tiles of 64 x 64
-// in 42 us against 64 of 128 x 128 in 71; 2048 x 2048 x 2048: 150 us against 94.
+// (us a round): 256 x 128 94, 128 x 128 50, 64 x 64 26 (21 alone). For example 1024 x 1024 x 1024: 256 tiles of 64 x 64
+// in 22.5 us against 64 of 128 x 128 in 38.6; 2048 x 2048 x 2048: 150 us against 94.
 int pick_split_tile(int64_t sets, int M, int N, bool s256) {
   struct { int tile, tm, tn; double cost; bool allowed; } const c[] = {
       {TILE_S256, 256, 128, 1.88, s256}, {TILE_S128, 128, 128, 1.0, true}, {TILE_S64, 64, 64, 0.52, true}};
