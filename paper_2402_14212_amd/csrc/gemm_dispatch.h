@@ -6,8 +6,8 @@
 namespace mw {
 
 // Which tiles a launcher can be asked for (each one is a kernel): every tile (the kernel-level entry point takes fp32
-// tiles by name), those of pick_tile_f32 and pick_tile, those of weight gradients.
-enum TileSet { TILES_ALL, TILES_LAYER, TILES_DW };
+// tiles by name), those of pick_tile_z, those of pick_tile_f32 and pick_tile, those of weight gradients.
+enum TileSet { TILES_ALL, TILES_Z, TILES_LAYER, TILES_DW };
 
 template <int LA, int LB, bool COLSUM, TileSet SET, class Xf, class Epi>
 inline hipError_t dispatch_gemm(int tile, int M, int N, int K, const float* A, int64_t lda, const float* B,
@@ -28,7 +28,8 @@ inline hipError_t dispatch_gemm(int tile, int M, int N, int K, const float* A, i
     if (tile == TILE_FINE_K4) MW_LAUNCH_TILE(FineK4Cfg);
   }
   if (tile == TILE_S128) MW_LAUNCH_TILE(Split128);
-  if (tile == TILE_S64) MW_LAUNCH_TILE(Split64);
+  if constexpr (SET != TILES_Z)
+    if (tile == TILE_S64) MW_LAUNCH_TILE(Split64);
   if constexpr (SET != TILES_DW) {
     if (tile == TILE_32K4) MW_LAUNCH_TILE(Tile32K4);
     if (tile == TILE_64K2) MW_LAUNCH_TILE(Tile64K2);

@@ -14,10 +14,10 @@ hipError_t gemm_fwd_act(int tile, int M, int N, int K, const float* X, const flo
   if (mask) {
     if (N % 32 != 0) return hipErrorInvalidValue;
     EpiFwdAct<true> epi{Xout, bias, alpha, reinterpret_cast<uint32_t*>(mask), Zkeep};
-    return dispatch_gemm<KCONTIG, KCONTIG, false, TILES_LAYER>(tile, M, N, K, X, K, W, K, ANone{}, epi, nullptr, 0.f, stream);
+    return dispatch_gemm<KCONTIG, KCONTIG, false, TILES_Z>(tile, M, N, K, X, K, W, K, ANone{}, epi, nullptr, 0.f, stream);
   }
   EpiFwdAct<false> epi{Xout, bias, alpha, nullptr, Zkeep};
-  return dispatch_gemm<KCONTIG, KCONTIG, false, TILES_LAYER>(tile, M, N, K, X, K, W, K, ANone{}, epi, nullptr, 0.f, stream);
+  return dispatch_gemm<KCONTIG, KCONTIG, false, TILES_Z>(tile, M, N, K, X, K, W, K, ANone{}, epi, nullptr, 0.f, stream);
 }
 
 namespace {
@@ -54,7 +54,7 @@ hipError_t gemm_fwd_act_and_mask(int tile, int M, int N, int K, const float* X, 
 hipError_t gemm_fwd_again(int tile, int M, int N, int K, const float* X, const float* W, const float* bias, float alpha, float* Xout,
                           const uint64_t* mask, unsigned long long* mismatches, hipStream_t stream) {
   EpiFwdAgain epi{Xout, bias, alpha, reinterpret_cast<const uint32_t*>(mask), mismatches};
-  return dispatch_gemm<KCONTIG, KCONTIG, false, TILES_LAYER>(tile, M, N, K, X, K, W, K, ANone{}, epi, nullptr, 0.f, stream);
+  return dispatch_gemm<KCONTIG, KCONTIG, false, TILES_Z>(tile, M, N, K, X, K, W, K, ANone{}, epi, nullptr, 0.f, stream);
 }
 
 }  // namespace mw
