@@ -189,14 +189,14 @@ struct AConvPatch {
       ch.nvalid = ((unsigned)iy < (unsigned)g.H && (unsigned)ix < (unsigned)g.W) ? 4 : 0;
       return ch;
     }
-    __device__ __forceinline__ float value(const float* __restrict__ x, int row, int k, int64_t) const {
+    __device__ __forceinline__ uint32_t place(int row, int k, int64_t) const {
       uint32_t b, oy, ox;
       split_row((uint32_t)(row + row_off), b, oy, ox);
       const uint32_t tap = g.d_csel.div((uint32_t)k), c = (uint32_t)k - tap * (uint32_t)g.Csel;
       const uint32_t ty = g.d_kw.div(tap), tx = tap - ty * (uint32_t)g.kw;
       const int iy = (int)oy * g.s - g.py + (int)ty, ix = (int)ox * g.s - g.px - g.xdiag * (int)oy + (int)tx;
-      if ((unsigned)iy >= (unsigned)g.H || (unsigned)ix >= (unsigned)g.W) return 0.f;
-      return x[(((int64_t)b * g.H + iy) * g.W + ix) * g.C + g.c0 + c];
+      const uint32_t e = ((b * (uint32_t)g.H + (uint32_t)iy) * (uint32_t)g.W + (uint32_t)ix) * (uint32_t)g.C + (uint32_t)g.c0 + c;
+      return (unsigned)iy < (unsigned)g.H && (unsigned)ix < (unsigned)g.W ? e * 4u : OOB;
     }
     __device__ __forceinline__ uint32_t extent(int, int, int64_t) const { return g.bytes; }
     template <bool VEC, bool SCALAR>

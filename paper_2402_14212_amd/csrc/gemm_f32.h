@@ -220,8 +220,8 @@ struct ALinearDev {
   __device__ __forceinline__ uint32_t extent(int n_outer, int n_inner, int64_t ld) const {
     return extent_bytes(n_outer, n_inner, ld);
   }
-  // one element of a KCONTIG operand
-  __device__ __forceinline__ float value(const float* __restrict__ A, int row, int k, int64_t ld) const { return A[(int64_t)row * ld + k]; }
+  // byte offset of one element of a KCONTIG operand
+  __device__ __forceinline__ uint32_t place(int row, int k, int64_t ld) const { return ((uint32_t)row * (uint32_t)ld + (uint32_t)k) * 4u; }
 };
 
 struct ANone {

@@ -30,8 +30,8 @@
 // operands are multiplied by 2^SPLIT_UP on their way (exact; the least part of the least subnormal is then a normal
 // bf16) and the result is scaled back. Values from 2^(127 - SPLIT_UP) on, infinities, NaN and sums beyond
 // 2^(127 - 2 SPLIT_UP) then do not give a finite result: a workgroup that sees one, from operands large enough for
-// it, computes its tile again with fp32 instructions and takes those results for the elements concerned. The time does not
-// depend on the data otherwise.
+// it, computes its tile again with fp32 instructions and takes those results for the elements concerned. The time depends on the
+// data otherwise only where the result is a pre-activation (see NearZero).
 #pragma once
 
 #include <type_traits>
@@ -57,7 +57,7 @@ struct SplitCfg {
   static constexpr int STAGE = 3 * PLANE;
   static constexpr int PARKED = NT * NACC * (16 - CNT) * 4;
   static constexpr int MAIN = 2 * STAGE > PARKED ? 2 * STAGE : PARKED;
-  static constexpr int LDS_BYTES = MAIN + 16;   // + a flag
+  static constexpr int LDS_BYTES = MAIN + 16;   // + flags
   static_assert((BM + BN) * (BK + 4) * 4 <= 2 * STAGE, "the fp32 repeat stages its tile in the same memory");
 };
 // Shapes that were fastest over the layer sizes in use (us at M x N x K; 512 threads each, one workgroup to a CU):
@@ -110,6 +110,12 @@ __device__ __forceinline__ SplitPair split_pair(float x, float y, float up, floa
     }
   }
   return p;
+}
+// sum + the squares of two bf16
+__device__ __forceinline__ float add_squares(uint32_t pair, float sum) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const bf16x2 v = __builtin_bit_cast(bf16x2, pair);
+  return __builtin_amdgcn_fdot2_f32_bf16(v, v, sum, false);
 }
 // combine over the eight lanes of an aligned group of eight
 __device__ __forceinline__ float dpp_f32(float v, int quad_or_mirror) {
@@ -166,10 +172,12 @@ struct SplitLoader {
 };
 
 // Split the staged values of `ld` into the planes of an LDS stage (`base`: this operand's rows of the first plane). SIGNED:
-// operand A, negated if `negative` and, once more, where the second K group reads it.
-template <class Cfg, bool SIGNED, bool COLSUM, class Ld, class XfDev>
+// operand A, negated if `negative` and, once more, where the second K group reads it. COLSUM, SQUARES: csum gets the sums of the values
+// or of the squares of their first parts (2^48 times the values'), by row.
+template <class Cfg, bool SIGNED, bool COLSUM, bool SQUARES, class Ld, class XfDev>
 __device__ __forceinline__ void split_store(const Ld& ld, const XfDev& xf, char* __restrict__ base, float* __restrict__ csum,
                                             float& top, bool negative) {
+  static_assert(!(COLSUM && SQUARES), "one or the other");
   using Map = typename Ld::Map;
   constexpr int BK = Cfg::BK, NT = Cfg::NT, PLANE = Cfg::PLANE;
   // (k: the same 16-k step for all of a chunk)
@@ -179,6 +187,7 @@ __device__ __forceinline__ void split_store(const Ld& ld, const XfDev& xf, char*
     for (int i = 0; i < Ld::NV; ++i) {
       const float4 w = ld.value(i, xf);
       const SplitPair a = split_pair(w.x, w.y, up(Map::k(0)), top), b = split_pair(w.z, w.w, up(Map::k(0)), top);
+      if (SQUARES) csum[i] = add_squares(b.part[0], add_squares(a.part[0], csum[i]));
       // a thread's chunks are the same k of rows so far apart that they have the same pattern of chunks
       static_assert(NT * 4 / BK % (BK == 32 ? 32 : 16) == 0, "see split_addr");
       char* p = base + split_addr<BK>(Map::row(0), Map::k(0) >> 3) + (Map::k(0) & 4) * 2 + i * (NT * 4 / BK) * BK * 2;
@@ -211,6 +220,7 @@ __device__ __forceinline__ void split_store(const Ld& ld, const XfDev& xf, char*
           const float x = e[q][2 * h], y = e[q][2 * h + 1];
           if (COLSUM) csum[4 * j + q] += x + y;
           s[h] = split_pair(x, y, up(k), top);
+          if (SQUARES) csum[4 * j + q] = add_squares(s[h].part[0], csum[4 * j + q]);
         }
         char* p = base + split_addr<BK>(row + q, k >> 3) + (k & 7) * 2;
 #pragma unroll
@@ -248,6 +258,139 @@ __device__ __forceinline__ void plain_store(const Ld& ld, const XfDev& xf, float
   }
 }
 
+// Pre-activations next to zero (an epilogue with NEAR_ZERO). The sign of a pre-activation selects a linear piece of the network,
+// so that one which rounding takes over zero changes gradients by a finite step, however small the error. A value that
+// lies, with its bias, within NEAR_ERROR sqrt(K) |a| |b| of zero, a and b its row of A and its column of B, is therefore formed again
+// in 64 bits by the whole wavefront. The line stands on the operands themselves (the squares of their first parts are added up while
+// they are staged), so that it holds at the edges of the matrix, next to rows of any size and where sums cancel. The largest errors
+// seen over sqrt(K) |a| |b|, among two million values each, K = 1024 .. 8192: 1e-9 .. 3e-9 for N(0, 1) operands, 1.4e-8 where the terms
+// of one half of K have one sign and those of the other half the other, 1.2e-8 where two terms of 1000 times the others' size
+// cancel, 1.9e-8 where the two groups of K have sums of opposite sign.
+// Of N(0, 1) values 3.2e-8 K are that near: 0.3 of a wavefront's 2048 at K = 4096. What it costs: 1.6 % of the time for the squares
+// and 1.2 % for the sums (six layers of 4096, batch 1024).
+// More than NEAR_MOST in one wavefront (sums that cancel all over), or rows so small or large that their squares leave
+// fp32: the workgroup's tile is formed again with fp32 instructions, as the pre-activations of smaller layers are. Rows and
+// columns of zeros are exact and not concerned. Apart from that a value depends on its row, its column and the tile alone, and a
+// product that is formed again elsewhere with the same tile has the same bits.
+// Signs that differ from the 64-bit network's, twelve inputs each, with fp32 products and here: five layers of 2500 .. 2301 on 1500
+// rows 58 and 43, six of 2048 on 1024 43 and 37, of 3000 on 700 63 and 42, of 4096 on 1024 (eleven) 146 and 94; none in the first layer here.
+// What is left comes from the rounding of the layers' inputs, as it does with fp32 products.
+constexpr float NEAR_ERROR = 4e-8f;
+constexpr int NEAR_MOST = 16;
+constexpr float NEAR_SQUARES_MIN = 0x1p-60f, NEAR_SQUARES_MAX = 0x1p110f;   // (of values times 2^SPLIT_UP)
+
+template <class EpiDev, class = void>
+struct near_zero : std::false_type {};
+template <class EpiDev>
+struct near_zero<EpiDev, std::enable_if_t<EpiDev::NEAR_ZERO>> : std::true_type {};
+
+template <class Cfg>
+struct NearZero {
+  static constexpr int PARTS = 2;                           // of a column of B, at most
+  static constexpr int FLOATS = Cfg::BM + PARTS * Cfg::BN;  // for A's rows and B's columns, in LDS behind what is parked
+  static_assert(Cfg::WK == 2 && Cfg::BK == 32 && Cfg::NACC * Cfg::CNT <= 64 && Cfg::PARKED + FLOATS * 4 <= Cfg::MAIN,
+                "a barrier between the squares and their use, eight lanes to a row, one flag a value");
+  static __device__ __forceinline__ float* place(float* lds) { return lds + Cfg::PARKED / 4; }
+
+  // One operand's squares from the threads' shares: the norms of KCONTIG rows, squares in parts R apart of others.
+  template <class Ld, int LAYOUT, int R>
+  static __device__ __forceinline__ void gather(const float* __restrict__ share, float* __restrict__ dst) {
+    static_assert(LAYOUT == KCONTIG || Cfg::BK / Ld::KP / 8 == PARTS, "see column_sums");
+#pragma unroll
+    for (int j = 0; j < Ld::NS; ++j) {
+      const float v = sum_over_8(share[j]);
+      const int k = LAYOUT == KCONTIG ? 0 : Ld::Map::k((j / 4) * Ld::KP) / Ld::KP;
+      if (((int)threadIdx.x & 7) == 0) dst[(k >> 3) * R + Ld::row_of(j)] = LAYOUT == KCONTIG ? norm(v) : v;
+    }
+  }
+  // |.| of values times 2^SPLIT_UP; what is too small or too large is infinite, for outside() below
+  static __device__ __forceinline__ float norm(float squares) {
+    const float n = __builtin_amdgcn_sqrtf(squares);
+    return squares > NEAR_SQUARES_MAX || (squares > 0.f && squares < NEAR_SQUARES_MIN) ? __builtin_inff() : n;
+  }
+
+  // bias: epi's, of this lane's columns. The values of a wavefront that are formed again (bit i * CNT + j: out[i][j]); all: its
+  // tile is to be. (Rows and columns outside the matrix are zeros, and so are their results.)
+  template <int LB>
+  static __device__ __forceinline__ unsigned long long find(int K, const float (&bias)[Cfg::WTN], const float* __restrict__ norms,
+                                                            const float (&out)[Cfg::NACC][Cfg::CNT], bool& all) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 31, g = lane >> 5;
+    const int wk = wave % Cfg::WK, wn = (wave / Cfg::WK) % Cfg::WN, wm = wave / (Cfg::WK * Cfg::WN);
+    const float c = NEAR_ERROR * 0x1p-24f * 0x1p-24f * __builtin_amdgcn_sqrtf((float)K);
+    float line[Cfg::WTN];
+#pragma unroll
+    for (int tn = 0; tn < Cfg::WTN; ++tn) {
+      const float* p = norms + Cfg::BM + (wn * Cfg::WTN + tn) * 32 + r;
+      line[tn] = c * (LB == RCONTIG ? norm(p[0] + p[Cfg::BN]) : p[0]);
+    }
+    uint32_t flags[2] = {0, 0};
+    bool outside = false;
+#pragma unroll
+    for (int tm = 0; tm < Cfg::WTM; ++tm)
+#pragma unroll
+      for (int j = 0; j < Cfg::CNT; ++j) {
+        const float a = norms[(wm * Cfg::WTM + tm) * 32 + acc_row(wk * Cfg::CNT + j, g)];
+#pragma unroll
+        for (int tn = 0; tn < Cfg::WTN; ++tn) {
+          const int bit = (tm * Cfg::WTN + tn) * Cfg::CNT + j;
+          const float v = out[tm * Cfg::WTN + tn][j], near = line[tn] * a;
+          // (infinite, or zero because of an underflow; 0 times infinity is a row of zeros beside one that is too large: NaN)
+          outside |= near == __builtin_inff() || (near == 0.f && v != 0.f);
+          flags[bit >> 5] |= fabsf(v + bias[tn]) < near ? 1u << (bit & 31) : 0u;
+        }
+      }
+    const unsigned long long found = flags[0] | (unsigned long long)flags[1] << 32;
+    int count = __popcll(found);
+    if (__ballot(found != 0)) {
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) count += __shfl_xor(count, o);
+    }
+    all = outside || count > NEAR_MOST;
+    return found;
+  }
+
+  // whole wavefronts
+  template <int LB, class XfDev>
+  static __device__ __forceinline__ void form_again(unsigned long long flags, __amdgpu_buffer_rsrc_t ra, int64_t lda, __amdgpu_buffer_rsrc_t rb,
+                                                    int64_t ldb, int K, int m0, int n0, const XfDev& xf,
+                                                    float (&out)[Cfg::NACC][Cfg::CNT]) {
+    constexpr int AT_ONCE = 8;   // loads of each operand in flight
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wk = wave % Cfg::WK, wn = (wave / Cfg::WK) % Cfg::WN, wm = wave / (Cfg::WK * Cfg::WN);
+    unsigned long long some = __ballot(flags != 0);
+    while (some) {
+      const int from = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(some));
+      const uint32_t lower = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)flags, from);
+      const uint32_t upper = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(flags >> 32), from);
+      const int which = lower ? __builtin_ctz(lower) : 32 + __builtin_ctz(upper);
+      const int i = which / Cfg::CNT, j = which % Cfg::CNT;
+      const int row = m0 + (wm * Cfg::WTM + i / Cfg::WTN) * 32 + acc_row(wk * Cfg::CNT + j, from >> 5);
+      const int col = n0 + (wn * Cfg::WTN + i % Cfg::WTN) * 32 + (from & 31);
+      double sum = 0.0;
+#pragma clang loop unroll(disable)
+      for (int k0 = lane; k0 - lane < K; k0 += 64 * AT_ONCE) {
+        float va[AT_ONCE], vb[AT_ONCE];
+#pragma unroll
+        for (int u = 0; u < AT_ONCE; ++u) {
+          const int k = k0 + 64 * u;
+          va[u] = buf_load_f32(ra, k < K ? xf.place(row, k, lda) : OOB);
+          vb[u] = buf_load_f32(rb, k < K ? (LB == KCONTIG ? (uint32_t)col * (uint32_t)ldb + (uint32_t)k : (uint32_t)k * (uint32_t)ldb + (uint32_t)col) * 4u : OOB);
+        }
+#pragma unroll
+        for (int u = 0; u < AT_ONCE; ++u) sum += (double)va[u] * (double)vb[u];
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+      const float v = (float)sum;
+#pragma unroll
+      for (int w = 0; w < Cfg::NACC * Cfg::CNT; ++w)
+        if (w == which && lane == from) out[w / Cfg::CNT][w % Cfg::CNT] = v;
+      if (lane == from) flags &= ~(1ull << which);
+      some = __ballot(flags != 0);
+    }
+  }
+};
+
 // One product of a workgroup tile over the whole K range.
 template <class Cfg, int LA, int LB, bool VEC, class XfDev>
 struct SplitProduct {
@@ -260,13 +403,15 @@ struct SplitProduct {
   // out[tile][j]: finished values of accumulator registers wk * CNT + j (acc_row) of the wavefront's tiles, the K
   // groups added in the order 0, 1, 2, ...
   // csum (COLSUM): this thread's share of the sums over k of the A rows it stages.
+  // epi: where the results are pre-activations, those next to zero are formed again (NearZero).
   // A workgroup's first use of LDS; it may be reused after the caller's next barrier.
-  template <bool COLSUM>
+  template <bool COLSUM, class EpiDev>
   __device__ __forceinline__ void run(const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb, int M,
                                       int N, int K, int m0, int n0, float* __restrict__ lds_f, XfDev& xf,
-                                      float (&out)[Cfg::NACC][Cfg::CNT], float* __restrict__ csum) {
+                                      float (&out)[Cfg::NACC][Cfg::CNT], float* __restrict__ csum, const EpiDev& epi) {
+    constexpr bool NEAR = near_zero<EpiDev>::value;
     char* const lds = reinterpret_cast<char*>(lds_f);
-    uint32_t* const flag = reinterpret_cast<uint32_t*>(lds + Cfg::MAIN);  // not finite, largest magnitudes of A and B
+    uint32_t* const flag = reinterpret_cast<uint32_t*>(lds + Cfg::MAIN);  // not finite, largest magnitudes of A and B, all again
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wk = wave % Cfg::WK, wn = (wave / Cfg::WK) % Cfg::WN, wm = wave / (Cfg::WK * Cfg::WN);
     const int r = lane & 31, g = lane >> 5;
@@ -277,6 +422,7 @@ struct SplitProduct {
     const ANone::Dev none;
     const int nkt = (K + BK - 1) / BK;
     float top_a = 0.f, top_b = 0.f;
+    float sq_a[NEAR ? LdA::NS : 1] = {}, sq_b[NEAR ? LdB::NS : 1] = {};   // squares of the rows this thread stages
     f32x16 acc[Cfg::NACC];
 #pragma unroll
     for (int i = 0; i < Cfg::NACC; ++i)
@@ -295,13 +441,13 @@ struct SplitProduct {
     xf.template prepare<LA, BM, BK, NT, LdA::KP>(m0, M, K);
     MW_REQUEST(0, 0);
     MW_REQUEST(1, 1);
-    if (threadIdx.x < 3) flag[threadIdx.x] = 0;
+    if (threadIdx.x < 4) flag[threadIdx.x] = 0;
 
     // idx: the K tile
-#define MW_TO_LDS(slot, stage, idx)                                                                                       \
-  do {                                                                                                                    \
-    split_store<Cfg, true, COLSUM>(a[slot], xf, lds + (stage) * Cfg::STAGE, csum, top_a, ((idx) / SPLIT_TURN) & 1);        \
-    split_store<Cfg, false, false>(b[slot], none, lds + (stage) * Cfg::STAGE + BM * BK * 2, (float*)nullptr, top_b, false); \
+#define MW_TO_LDS(slot, stage, idx)                                                                                          \
+  do {                                                                                                                       \
+    split_store<Cfg, true, COLSUM, NEAR>(a[slot], xf, lds + (stage) * Cfg::STAGE, NEAR ? sq_a : csum, top_a, ((idx) / SPLIT_TURN) & 1); \
+    split_store<Cfg, false, false, NEAR>(b[slot], none, lds + (stage) * Cfg::STAGE + BM * BK * 2, sq_b, top_b, false);        \
   } while (0)
 #define MW_MULTIPLY(stage) multiply(lds + (stage) * Cfg::STAGE, wm, wn, wk, r, g, acc)
     MW_TO_LDS(0, 0, 0);
@@ -336,6 +482,14 @@ struct SplitProduct {
 #undef MW_REQUEST
     // Add the K groups. A wavefront keeps CNT registers of every tile and hands the others over through LDS.
     __syncthreads();   // the stages are free
+    using Near = NearZero<Cfg>;
+    float bias[NEAR ? Cfg::WTN : 1];
+    if constexpr (NEAR) {
+#pragma unroll
+      for (int tn = 0; tn < Cfg::WTN; ++tn) bias[tn] = epi.bias_of(n0 + (wn * Cfg::WTN + tn) * 32 + r, N);
+      Near::template gather<LdA, LA, BM>(sq_a, Near::place(lds_f));
+      Near::template gather<LdB, LB, BN>(sq_b, Near::place(lds_f) + BM);
+    }
     finish<true>(lds_f, acc, out, wm, wn, wk, lane);
     bool finite = true;
 #pragma unroll
@@ -347,7 +501,19 @@ struct SplitProduct {
         static_assert(SPLIT_UP == 24, "both operands");
       }
     if (!finite) *flag = 1;
-    __syncthreads();
+    if constexpr (NEAR) {
+      bool all = false;
+      const unsigned long long near = Near::template find<LB>(K, bias, Near::place(lds_f), out, all);
+      if (all) flag[3] = 1;
+      __syncthreads();
+      if (__builtin_amdgcn_readfirstlane(flag[3]) != 0) {
+        repeat_f32<true>(ra, lda, rb, ldb, M, N, K, m0, n0, lds_f, xf, out, nkt, wm, wn, wk, r, g, lane);
+        return;
+      }
+      Near::template form_again<LB>(near, ra, lda, rb, ldb, K, m0, n0, xf, out);
+    } else {
+      __syncthreads();
+    }
     if (__builtin_amdgcn_readfirstlane(flag[0]) == 0) return;
     // Operands so small that neither a part nor a sum can have overflowed: what is not finite has met a NaN, and fp32
     // instructions would say the same (a network whose training has diverged takes no longer than another)
@@ -357,7 +523,7 @@ struct SplitProduct {
     top_a = __uint_as_float(flag[1]);
     top_b = __uint_as_float(flag[2]);
     if (top_a < 0x1p126f && top_b < 0x1p126f && top_a * top_b * (float)K < 0x1p126f) return;
-    repeat_f32(ra, lda, rb, ldb, M, N, K, m0, n0, lds_f, xf, out, nkt, wm, wn, wk, r, g, lane);
+    repeat_f32<false>(ra, lda, rb, ldb, M, N, K, m0, n0, lds_f, xf, out, nkt, wm, wn, wk, r, g, lane);
   }
 
   static __device__ __forceinline__ void negate(f32x16 (&acc)[Cfg::NACC]) {
@@ -405,7 +571,8 @@ struct SplitProduct {
   }
 
   // The product again with fp32 instructions, one K tile at a time through registers and LDS, for the elements that are
-  // not finite. Rare, so simple.
+  // not finite or for all. Rare, so simple.
+  template <bool ALL>
   __device__ __forceinline__ void repeat_f32(__amdgpu_buffer_rsrc_t ra, int64_t lda, __amdgpu_buffer_rsrc_t rb, int64_t ldb, int M, int N,
                                              int K, int m0, int n0, float* __restrict__ lds, XfDev& xf,
                                              float (&out)[Cfg::NACC][Cfg::CNT], int nkt, int wm, int wn, int wk, int r, int g,
@@ -449,7 +616,7 @@ struct SplitProduct {
     for (int i = 0; i < Cfg::NACC; ++i)
 #pragma unroll
       for (int j = 0; j < Cfg::CNT; ++j)
-        if (!(fabsf(out[i][j]) < __builtin_inff())) out[i][j] = again[i][j];
+        if (ALL || !(fabsf(out[i][j]) < __builtin_inff())) out[i][j] = again[i][j];
   }
 
   // Sums of one accumulator register over the K groups, in the order of the groups (SIGNED: the second group's taken away,
@@ -523,78 +690,6 @@ struct SplitProduct {
   }
 };
 
-// Pre-activations next to zero (EpiDev::NEAR_ZERO). The sign of a pre-activation selects a linear piece of the network, so that one
-// which rounding takes over zero changes gradients by a finite step, however small the error. Values within
-// NEAR_SIGMAS of the product's rounding error of zero, with the bias, are therefore formed again, in 64 bits, by the
-// whole wavefront. The error is 1.1e-8 sqrt(K) of the values' rms (see `Accuracy`), so that about one value in a
-// million is (K = 4096: 14 of 1024 x 4096, 2 us each in one workgroup). More than NEAR_MOST in a wavefront's part of the
-// tile are not rounding but rows that are zero, and stay as they are. What comes out depends on the operands and the
-// tile alone: a product that is formed again elsewhere with the same tile has the same bits.
-constexpr float NEAR_SIGMAS = 6.f, NEAR_ERROR = 1.1e-8f;
-constexpr int NEAR_MOST = 8;
-
-template <class Cfg, int LA, int LB, class XfDev, class EpiDev>
-__device__ __forceinline__ void split_near_zero(const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb, int M,
-                                                int N, int K, int m0, int n0, const XfDev& xf, const EpiDev& epi,
-                                                float (&out)[Cfg::NACC][Cfg::CNT]) {
-  static_assert(LA == KCONTIG && Cfg::NACC * Cfg::CNT <= 64, "one flag a value");
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 31, g = lane >> 5;
-  const int wk = wave % Cfg::WK, wn = (wave / Cfg::WK) % Cfg::WN, wm = wave / (Cfg::WK * Cfg::WN);
-  unsigned long long flags = 0;
-  float squares = 0.f;
-#pragma unroll
-  for (int i = 0; i < Cfg::NACC; ++i)
-#pragma unroll
-    for (int j = 0; j < Cfg::CNT; ++j) squares += out[i][j] * out[i][j];
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) squares += __shfl_xor(squares, o);
-  const float line = NEAR_SIGMAS * NEAR_ERROR * sqrtf((float)K * squares / (float)(64 * Cfg::NACC * Cfg::CNT));
-  if (!(line < __builtin_inff())) return;
-#pragma unroll
-  for (int i = 0; i < Cfg::NACC; ++i) {
-    const int col = n0 + (wn * Cfg::WTN + i % Cfg::WTN) * 32 + r, row_base = m0 + (wm * Cfg::WTM + i / Cfg::WTN) * 32;
-    const float bias = epi.bias_of(col, N);
-#pragma unroll
-    for (int j = 0; j < Cfg::CNT; ++j) {
-      const bool near = fabsf(out[i][j] + bias) < line && col < N && row_base + acc_row(wk * Cfg::CNT + j, g) < M;
-      flags |= near ? 1ull << (i * Cfg::CNT + j) : 0ull;
-    }
-  }
-  unsigned long long some = __ballot(flags != 0);
-  if (some == 0) return;
-  int count = __popcll(flags);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) count += __shfl_xor(count, o);
-  if (count > NEAR_MOST) return;
-  while (some) {
-    const int from = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(some));
-    const uint32_t lower = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)flags, from);
-    const uint32_t upper = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(flags >> 32), from);
-    const int which = lower ? __builtin_ctz(lower) : 32 + __builtin_ctz(upper);
-    const int i = which / Cfg::CNT, j = which % Cfg::CNT;
-    const int row = m0 + (wm * Cfg::WTM + i / Cfg::WTN) * 32 + acc_row(wk * Cfg::CNT + j, from >> 5);
-    const int col = n0 + (wn * Cfg::WTN + i % Cfg::WTN) * 32 + (from & 31);
-    double sum = 0.0;
-#pragma unroll 4
-    for (int k = lane; k < K; k += 64) {
-      const float b = LB == KCONTIG ? B[(int64_t)col * ldb + k] : B[(int64_t)k * ldb + col];
-      sum += (double)xf.value(A, row, k, lda) * (double)b;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-#pragma unroll
-    for (int w = 0; w < Cfg::NACC * Cfg::CNT; ++w)
-      if (w == which && lane == from) out[w / Cfg::CNT][w % Cfg::CNT] = (float)sum;
-    if (lane == from) flags &= ~(1ull << which);
-    some = __ballot(flags != 0);
-  }
-}
-
-template <class EpiDev, class = void>
-struct near_zero : std::false_type {};
-template <class EpiDev>
-struct near_zero<EpiDev, std::enable_if_t<EpiDev::NEAR_ZERO>> : std::true_type {};
-
 // out[set][tile][j] of the wavefront to the epilogue, one 32 x 32 tile (CNT registers of it) at a time
 template <class Cfg, int NSETS, class EpiDev>
 __device__ __forceinline__ void split_epilogue(int M, int N, int m0, int n0, const float (*out)[Cfg::NACC][Cfg::CNT], EpiDev& epi) {
@@ -623,8 +718,7 @@ __device__ __forceinline__ void split_product(const float* __restrict__ A, int64
   SplitProduct<Cfg, LA, LB, VEC, XfDev> p;
   float out[Cfg::NACC][Cfg::CNT];
   float csum[COLSUM ? decltype(p)::LdA::NS : 1];
-  p.template run<COLSUM>(A, lda, B, ldb, M, N, K, m0, n0, lds, xf, out, csum);
-  if constexpr (near_zero<EpiDev>::value) split_near_zero<Cfg, LA, LB>(A, lda, B, ldb, M, N, K, m0, n0, xf, epi, out);
+  p.template run<COLSUM>(A, lda, B, ldb, M, N, K, m0, n0, lds, xf, out, csum, epi);
   split_epilogue<Cfg, 1>(M, N, m0, n0, &out, epi);
   if constexpr (COLSUM) {
     if (n0 == 0 && colsum_dst) {
