@@ -284,6 +284,13 @@ struct near_zero : std::false_type {};
 template <class EpiDev>
 struct near_zero<EpiDev, std::enable_if_t<EpiDev::NEAR_ZERO>> : std::true_type {};
 
+// the float next to v in the direction of the sign
+__device__ __forceinline__ float next_float(float v, bool upwards) {
+  if (v == 0.f) return upwards ? 0x1p-149f : -0x1p-149f;
+  const uint32_t u = __float_as_uint(v);
+  return __uint_as_float((v > 0.f) == upwards ? u + 1 : u - 1);
+}
+
 template <class Cfg>
 struct NearZero {
   static constexpr int PARTS = 2;                           // of a column of B, at most
@@ -352,7 +359,7 @@ struct NearZero {
   // whole wavefronts
   template <int LB, class XfDev>
   static __device__ __forceinline__ void form_again(unsigned long long flags, __amdgpu_buffer_rsrc_t ra, int64_t lda, __amdgpu_buffer_rsrc_t rb,
-                                                    int64_t ldb, int K, int m0, int n0, const XfDev& xf,
+                                                    int64_t ldb, int K, int m0, int n0, const XfDev& xf, const float (&bias)[Cfg::WTN],
                                                     float (&out)[Cfg::NACC][Cfg::CNT]) {
     constexpr int AT_ONCE = 8;   // loads of each operand in flight
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -381,7 +388,14 @@ struct NearZero {
       }
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-      const float v = (float)sum;
+      // the epilogue adds the bias in fp32, exactly where the two are next to each other: the float beside the sum where
+      // the sum's own rounding would change the sign
+      float b = bias[0];
+#pragma unroll
+      for (int tn = 1; tn < Cfg::WTN; ++tn) b = i % Cfg::WTN == tn ? bias[tn] : b;
+      float v = (float)sum;
+      const bool positive = sum + (double)b > 0.0;
+      if ((v + b > 0.f) != positive) v = next_float(v, positive);   // (lane `from` has that column's bias)
 #pragma unroll
       for (int w = 0; w < Cfg::NACC * Cfg::CNT; ++w)
         if (w == which && lane == from) out[w / Cfg::CNT][w % Cfg::CNT] = v;
@@ -510,7 +524,7 @@ struct SplitProduct {
         repeat_f32<true>(ra, lda, rb, ldb, M, N, K, m0, n0, lds_f, xf, out, nkt, wm, wn, wk, r, g, lane);
         return;
       }
-      Near::template form_again<LB>(near, ra, lda, rb, ldb, K, m0, n0, xf, out);
+      Near::template form_again<LB>(near, ra, lda, rb, ldb, K, m0, n0, xf, bias, out);
     } else {
       __syncthreads();
     }

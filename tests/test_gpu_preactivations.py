@@ -182,3 +182,17 @@ def test_last_rows_and_channels_of_a_convolution():
     rows, chans = rows.cpu().numpy(), chans.cpu().numpy()
     assert np.array_equal(got[rows, chans], z[rows, chans] > 0)
     assert np.array_equal(got[z != 0], (z > 0)[z != 0])
+
+
+def test_signs_below_the_rounding_of_the_sum():
+    """Biases that are the rounded sum itself, negated: what is left is less than half a unit in the last place of the sum."""
+    gen = generator(8)
+    W = orthonormal(K, N, gen)
+    x = torch.randn(ROWS, K, device="cuda", generator=gen)
+    cols = torch.arange(N, device="cuda")
+    rows = cols * 199 + 3
+    s = (x[rows].double() * W.double()).sum(1)
+    b = -s.float()
+    _, got = by_row(x, W.t().contiguous(), b)
+    rows, cols, left = rows.cpu().numpy(), cols.cpu().numpy(), (s + b.double()).cpu().numpy()
+    assert np.array_equal(got[rows, cols], left > 0)
