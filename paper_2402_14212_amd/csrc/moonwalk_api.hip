@@ -232,7 +232,7 @@ struct mw_handle {
   const uint32_t** count_ptrs = nullptr;  // device array [n_relu]
   FragLayer* frag_layers = nullptr;       // device array [n_relu]: mask, offsets and size of every ReLU layer
   int64_t frag_max_n = 0;                 // largest B * d_out among them
-  uint32_t* status = nullptr;             // [0..1] sign mismatches (u64), [2] fragment overflow, [3] non-finite loss, [4] bad pivot (setup, refresh), in a step the count of ew_loss_step (zero before and after)
+  uint32_t* status = nullptr;             // [0..1] sign mismatches (u64), [2] fragment overflow, [3] non-finite loss, [4] bad pivot, [5] the count of ew_loss_step (zero before and after)
   double* loss_scratch = nullptr;
   float* refresh_work = nullptr;  // incremental refresh of P: allocated on first use
   const float** refresh_tab = nullptr;  // device table of pointers for the grouped products of that refresh:
@@ -350,7 +350,6 @@ int build_right_inverses(mw_handle* h, hipStream_t stream) {
   int32_t bad_host = 0;
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   if (e == hipSuccess) e = hipMemcpy(&bad_host, bad, sizeof(int32_t), hipMemcpyDeviceToHost);
-  if (e == hipSuccess && bad_host) e = ew_fill_u32(h->status + 4, 0u, 1, stream);   // (a step counts in it)
   if (e != hipSuccess) rc = hip_fail(e, "right-inverse setup");
   else if (bad_host) rc = MW_ERR_NOT_SUBMERSIVE;
   h->release(work);
@@ -499,9 +498,9 @@ int moonwalk_setup(mw_handle_t** out, const mw_layer_t* layers, int32_t n_layers
     return code;
   };
   mw_memstats_t& st = h->st;
-  bool ok = alloc_t(h, &h->status, 5, &st.bytes_mw_scratch);
+  bool ok = alloc_t(h, &h->status, 6, &st.bytes_mw_scratch);
   if (!ok) return fail(MW_ERR_OOM);
-  hipError_t e = ew_fill_u32(h->status, 0u, 5, stream);
+  hipError_t e = ew_fill_u32(h->status, 0u, 6, stream);
   if (e != hipSuccess) return fail(hip_fail(e, "status init"));
 
   if (h->plan & MW_PLAN_MOONWALK) {
@@ -1121,7 +1120,7 @@ int run_moonwalk(mw_handle* h, const float* x, const float* target, float* grads
     c.top_scaled = one_launch;
     if (one_launch)
       MW_LAUNCH(h, s, MW_KCLASS_EW, ew_loss_step(x_L, target, B, top.d_out, h->loss_scale, top.alpha, h->ha, loss_out, h->loss_scratch,
-                                                 h->status + 4, h->status, h->status + 3, s));
+                                                 h->status + 5, h->status, h->status + 3, s));
     else
       MW_LAUNCH(h, s, MW_KCLASS_EW, ew_loss_grad(x_L, target, B, top.d_out, h->loss_scale, h->ha, loss_out, h->loss_scratch, s, h->status + 3));
     if (h->group_width > 0) return reverse_and_sweep(c);

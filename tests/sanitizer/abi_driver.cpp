@@ -15,6 +15,8 @@
 extern "C" unsigned long long fake_hip_launches();
 extern "C" unsigned long long fake_hip_bad_launches();
 extern "C" int fake_hip_pending_configurations();
+extern "C" void fake_hip_bad_pivot_then_failure();
+extern "C" unsigned fake_hip_loss_count();
 
 static int g_failures = 0;
 #define EXPECT(cond)                                                    \
@@ -156,6 +158,22 @@ static void dense_network(const std::vector<int>& widths, int batch, const std::
   EXPECT(g_live_blocks == 0);
 }
 
+// A refresh that flags a pivot and then fails leaves nothing behind that the next step's loss counts in.
+static void failed_refresh() {
+  const int n = 80, batch = 8;   // (wider than the networks that are one launch)
+  std::vector<float> W((size_t)n * n, 0.f), x((size_t)batch * n), grads((size_t)n * n + n);
+  mw_layer_t layer{n, n, W.data(), nullptr, 0.1f};
+  mw_config_t cfg = base_config(batch);
+  mw_handle_t* h = nullptr;
+  EXPECT(moonwalk_setup(&h, &layer, 1, &cfg, nullptr) == MW_OK);
+  fake_hip_bad_pivot_then_failure();
+  EXPECT(moonwalk_refresh(h, nullptr) != MW_OK);
+  EXPECT(moonwalk_grad(h, x.data(), x.data(), grads.data(), nullptr, nullptr) == MW_OK);
+  EXPECT(fake_hip_loss_count() == 0);
+  moonwalk_destroy(h);
+  EXPECT(g_live_blocks == 0);
+}
+
 static void dense_allocation_failures() {
   // the allocator gives out after n calls, for every n until setup succeeds: everything taken so far must go back
   std::vector<float> W(64 * 64, 0.f);
@@ -257,6 +275,7 @@ int main() {
   dense_network({200, 136, 136, 136, 96, 96, 70, 50}, 9, {0.1f, 0.1f, 0.1f, 0.1f, 0.1f, 0.1f, 0.1f}, 2, 0, 1, 0, MW_PLAN_MOONWALK, 1, 0, 1);
   dense_network(std::vector<int>(12, 1024), 64, std::vector<float>(11, 0.1f), 4, 0, 1, 0, MW_PLAN_MOONWALK, 0, 0, 1);
   dense_allocation_failures();
+  failed_refresh();
   // convolutional chains: gathered kernels and patch buffer, as-read input cotangent, image chunks of 3,
   // a kernel wider than padding + stride (the sweep), 1-D fragmental layers in blocks of 4
   conv_network(MW_CONV_SUBMERSIVE, 32, 3, 2, 1, 32, 32, 8, 3, 2, MW_CONV_KERNELS_AUTO, MW_CONV_H0_FULL, 0, 0);

@@ -21,6 +21,11 @@ struct FreeSymbolsAtExit {
 } g_free_symbols;
 thread_local hipError_t g_last = hipSuccess;
 unsigned long long g_launches = 0, g_bad_launches = 0;
+std::map<const void*, const char*> g_names;  // host handle of a kernel -> its name
+// One failing set-up of right inverses: the next factorisation finds a pivot that is not positive (it is the kernel's last
+// argument that says so), and the launch after it fails.
+int g_bad_pivot = 0;  // 1: waiting for the factorisation, 2: the next launch fails
+uint32_t g_loss_count = 0;
 struct CallConfig {
   dim3 grid, block;
   size_t shmem;
@@ -36,6 +41,9 @@ unsigned long long fake_hip_launches() { return g_launches; }
 unsigned long long fake_hip_bad_launches() { return g_bad_launches; }
 // launch configurations pushed by the calling thread that no launch has taken up (must be 0 between calls)
 int fake_hip_pending_configurations() { return g_cfg_depth; }
+void fake_hip_bad_pivot_then_failure() { g_bad_pivot = 1; }
+// what the workgroup counter of the loss held at the last launch that counts in one
+uint32_t fake_hip_loss_count() { return g_loss_count; }
 
 hipError_t hipMalloc(void** ptr, size_t size) {
   if (!ptr) return hipErrorInvalidValue;
@@ -110,6 +118,16 @@ hipError_t hipLaunchKernel(const void* func, dim3 grid, dim3 block, void** args,
     g_last = hipErrorInvalidConfiguration;
     return g_last;
   }
+  if (g_bad_pivot == 2) {
+    g_bad_pivot = 0;
+    return g_last = hipErrorLaunchFailure;
+  }
+  const char* name = g_names.count(func) ? g_names[func] : "";
+  if (g_bad_pivot == 1 && strstr(name, "k_chol_diag")) {
+    **static_cast<int32_t**>(args[5]) = 1;
+    g_bad_pivot = 2;
+  }
+  if (strstr(name, "k_loss_gradILb1E")) g_loss_count = **static_cast<uint32_t**>(args[7]);   // the first word of its LossStep
   return hipSuccess;
 }
 hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t shmem, hipStream_t stream) {
@@ -130,7 +148,10 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shmem, hip
 static void* g_module_token[1];
 void** __hipRegisterFatBinary(const void*) { return g_module_token; }
 void __hipUnregisterFatBinary(void**) {}
-void __hipRegisterFunction(void**, const void*, char*, const char*, unsigned, void*, void*, void*, void*, int*) {}
+void __hipRegisterFunction(void**, const void* func, char*, const char* name, unsigned, void*, void*, void*, void*, int*) {
+  std::lock_guard<std::mutex> guard(g_lock);
+  g_names[func] = name;
+}
 void __hipRegisterVar(void**, void* var, char*, char*, int, size_t size, int, int) {
   std::lock_guard<std::mutex> guard(g_lock);
   if (!g_symbols.count(var)) {
