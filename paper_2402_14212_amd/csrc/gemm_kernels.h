@@ -996,10 +996,8 @@ inline hipError_t launch_vijp_dual(int M, int N, int K, const float* X, const fl
   if (!extent_ok(M, K, K) || !extent_ok(N, K, K) || !extent_ok(M, N, N)) return hipErrorInvalidValue;
   if (operand_vec_ok(K))
     return launch_task<Cfg::NT>(make_vijp_task<Cfg, true, RELU>(M, N, K, X, W, Hin, P, epi), stream);
-  if constexpr (std::is_same<Cfg, Tile64>::value || is_fine<Cfg>()) {
-    if ((int64_t)(M < N ? M : N) * K < 4)
-      return launch_task<Cfg::NT>(make_vijp_task<TileTiny, false, RELU>(M, N, K, X, W, Hin, P, epi), stream);
-  }
+  if ((int64_t)(M < N ? M : N) * K < 4)   // (load_chunk; from 33000 rows on with the tiles of large outputs)
+    return launch_task<TileTiny::NT>(make_vijp_task<TileTiny, false, RELU>(M, N, K, X, W, Hin, P, epi), stream);
   return launch_task<Cfg::NT>(make_vijp_task<Cfg, false, RELU>(M, N, K, X, W, Hin, P, epi), stream);
 }
 

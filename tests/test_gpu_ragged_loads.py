@@ -80,3 +80,21 @@ def test_signs_packed_beside_the_next_layer(widths, batch, segment, alpha):
     for i in range(len(Ws) if segment == 0 else segment):
         assert np.array_equal(nets[0].fetch_mask(i), nets[1].fetch_mask(i)), i
     nets[0].memory_stats()
+
+
+@pytest.mark.parametrize("widths", [(1, 1), (3, 1), (3, 3, 1), (2, 1, 1)])
+@pytest.mark.parametrize("alpha", [0.0, 0.3])
+def test_weights_of_less_than_a_chunk_on_many_rows(widths, alpha):
+    """Weights of one to three elements where the batch alone asks for the tiles of large outputs. Every weight is one or two in
+    size, so that moonwalk and backprop differ by the rounding of the sums over the batch: 2^-24 sqrt(33000), twice."""
+    batch = 33000
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(sum(widths))
+    Ws = [torch.eye(b, a, device="cuda") * 2 - 0.5 for a, b in zip(widths[:-1], widths[1:])]
+    bs = [torch.full((b,), 0.25, device="cuda") for b in widths[1:]]
+    x, t = torch.randn(batch, widths[0], device="cuda", generator=gen), torch.randn(batch, widths[-1], device="cuda", generator=gen)
+    net = mw.MoonwalkNet(Ws, bs, [alpha] * len(Ws), batch)
+    g = net.moonwalk_grad(x, t).flat.double()
+    h = net.backprop_grad(x, t).flat.double()
+    assert net.memory_stats()["sign_mismatches"] == 0
+    assert torch.isfinite(g).all() and ((g - h).norm() <= 5e-5 * h.norm()).item()
