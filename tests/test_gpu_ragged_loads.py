@@ -41,6 +41,32 @@ def test_product_of_ragged_operands(op, gap):
             assert err <= max(4 * math.sqrt(K) * 2.0 ** -24, 2.0 ** -22), (op, M, N, K, gap, tile, err)
 
 
+@pytest.mark.parametrize("start", [1, 2, 3])
+@pytest.mark.parametrize("op", ["NT", "NN", "TN"])
+def test_operands_that_start_anywhere(op, start):
+    """Rows of a multiple of four and not, every operand (and the result) `start` floats after a 16-byte boundary: the bits of
+    aligned ones."""
+    code = {"NT": mw.GEMM_NT, "NN": mw.GEMM_NN, "TN": mw.GEMM_TN}[op]
+
+    def moved(t, gap):
+        r, c = t.shape
+        flat = torch.full((start + r * (c + gap),), float("nan"), device="cuda")
+        view = flat[start:].reshape(r, c + gap)[:, :c]
+        view.copy_(t)
+        assert view.data_ptr() % 16 == 4 * start
+        return view
+
+    for M, N, K in [(3, 2, 2), (64, 64, 32), (33, 35, 257), (100, 388, 700), (129, 132, 64), (200, 1201, 1403), (1024, 2048, 512)]:
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(M + 1000 * N + K)
+        A = torch.randn((K, M) if op == "TN" else (M, K), device="cuda", generator=gen)
+        B = torch.randn((N, K) if op == "NT" else (K, N), device="cuda", generator=gen)
+        ref = mw.gemm_f32(code, A, B)
+        for gap in (0, 4):
+            got = mw.gemm_f32(code, moved(A, gap), moved(B, gap), C_out=moved(torch.zeros_like(ref), gap))
+            assert torch.equal(got, ref), (op, start, M, N, K, gap)
+
+
 @pytest.mark.parametrize("widths,batch", [((5, 3, 2, 1), 1), ((9, 7, 7), 3), ((66, 65, 35), 31), ((301, 299, 257), 33), ((515, 515, 259), 70)])
 @pytest.mark.parametrize("alpha", [0.0, 0.3])
 def test_ragged_network(widths, batch, alpha):
