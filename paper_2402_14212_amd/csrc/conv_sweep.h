@@ -42,9 +42,6 @@ struct SweepImages {
 // Magnitudes up to which neither a part nor a sum of the three products of parts can overflow; see the repeat below.
 constexpr float SWEEP_BIG_H = 0x1p40f, SWEEP_BIG_A = 0x1p20f;
 
-// A barrier of the workgroup that orders LDS only: stores and loads of memory stay in flight.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 template <int C>
 __global__ void __launch_bounds__(SweepCfg<C>::NT) sweep_images_kernel(SweepImages p) {
   using Cfg = SweepCfg<C>;
@@ -140,9 +137,8 @@ __global__ void __launch_bounds__(SweepCfg<C>::NT) sweep_images_kernel(SweepImag
       }
 #pragma unroll
       for (int i = 0; i < 16; ++i) park[wave * (Cfg::PARK / 4) + acc_row(i, g) * 36 + r] = acc[i];
-      // (what the repeat reads from memory was written before the last barrier but one)
-      if (*big) __syncthreads();
-      else lds_barrier();
+      // (what the repeat reads from memory was stored by this workgroup before an earlier barrier; *big is up to date here)
+      __syncthreads();
       float top = 0.f;
 #pragma unroll
       for (int u = 0; u < Cfg::QUADS; ++u) {
@@ -187,7 +183,7 @@ __global__ void __launch_bounds__(SweepCfg<C>::NT) sweep_images_kernel(SweepImag
         }
       }
       if (top >= SWEEP_BIG_H * split_up(false)) *big = 1;
-      lds_barrier();   // the sums are read, the diagonal is written
+      __syncthreads();   // the sums are read, the diagonal is written
     }
   }
 }

@@ -17,8 +17,6 @@ namespace {
 constexpr int NT = 512, WAVES = NT / 64;
 constexpr int KS = SMALL_NET_MAX_WIDTH / 32;   // slices of 32 k
 
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // place of column n in a row of an LDS buffer: inside a slice of 32 in the order in which a lane reads its eight k
 // (gemm_fine.h: lane group q has k = 16 (q & 1) + (q >> 1) + 0, 2, .. 14)
 __device__ __forceinline__ int place(int n) { return (n & ~31) + (((n >> 4) & 1) + 2 * (n & 1)) * 8 + ((n & 15) >> 1); }
@@ -134,7 +132,7 @@ __global__ void __launch_bounds__(NT) k_small_net(SmallNet p) {
     for (int row = wave; row < B; row += WAVES)
       for (int n = lane; n < d; n += 64) X[row * pitch + place(n)] = p.x[(int64_t)row * d + n];
   }
-  lds_barrier();
+  __syncthreads();
   asm volatile("" ::"v"(touched));
 
   // ---- Phase I
@@ -171,7 +169,7 @@ __global__ void __launch_bounds__(NT) k_small_net(SmallNet p) {
     }
     w = next;
     xi = xo;
-    lds_barrier();
+    __syncthreads();
   }
 
   // ---- loss, the cotangent of the output and of its pre-activations
@@ -188,7 +186,7 @@ __global__ void __launch_bounds__(NT) k_small_net(SmallNet p) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
     if (lane == 0) red[wave] = sum;
-    lds_barrier();
+    __syncthreads();
     if (threadIdx.x == 0) {
       double t = 0.0;
       for (int i = 0; i < WAVES; ++i) t += red[i];
@@ -240,7 +238,7 @@ __global__ void __launch_bounds__(NT) k_small_net(SmallNet p) {
     }
     w = next;
     ci = 1 - ci;
-    lds_barrier();
+    __syncthreads();
   }
   __syncthreads();   // checkpoints are read back below
 
@@ -338,7 +336,7 @@ __global__ void __launch_bounds__(NT) k_small_net(SmallNet p) {
     if (i < L) {
       w = next;
       pw = next_pw;
-      lds_barrier();
+      __syncthreads();
       xi = xi == 2 ? 0 : xi + 1;
       hi = 1 - hi;
       ci = 1 - ci;
