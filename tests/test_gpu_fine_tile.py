@@ -24,10 +24,26 @@ def test_bits_of_the_64_tile(op, K):
         assert torch.equal(got, ref), (op, M, N, K)
 
 
+@pytest.mark.parametrize("K", [256, 257, 287, 300, 383, 384, 385, 511, 513, 640, 767, 769, 1000, 1023, 1024])
+@pytest.mark.parametrize("op", ["NT", "NN", "TN"])
+def test_bits_of_the_tile_that_splits_k(op, K):
+    """From K = 256 to 1024, up to 128 tiles of 32 x 32, the automatic choice is the 16 x 16 tile with K split over four
+    wavefronts: the bits of the 32 x 32 tile with that split."""
+    for M, N in [(1, 4), (15, 17), (16, 16), (33, 65), (100, 389), (128, 1024), (129, 31)]:
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(M * N + K)
+        A = torch.randn((K, M) if op == "TN" else (M, K), device="cuda", generator=gen)
+        B = torch.randn((N, K) if op == "NT" else (K, N), device="cuda", generator=gen)
+        A = A * torch.exp2(torch.randint(-10, 11, A.shape, device="cuda", generator=gen).float())
+        got, ref = mw.gemm_f32(OPS[op], A, B), mw.gemm_f32(OPS[op], A, B, tile=mw.TILE_32K4)
+        assert torch.equal(got, ref), (op, M, N, K)
+
+
 @pytest.mark.parametrize("side,c_in,c_out,k,stride", [(9, 32, 32, 1, 1), (17, 96, 64, 3, 2), (23, 64, 96, 5, 2), (12, 128, 32, 3, 1)])
 def test_layer_of_a_small_batch(side, c_in, c_out, k, stride):
     """A layer of few images takes the small tile, many copies of them the large ones: the same image, the same bits. Only where
-    neither splits K (channels that are no multiple of 128), and for the forward product, which is fp32 in every tile."""
+    neither splits K (channels that are no multiple of 128), and for the forward product of up to 64 channels, or up to 191
+    tiles of 128 x 128, which is fp32 in every tile."""
     gen = torch.Generator(device="cuda")
     gen.manual_seed(side)
     x = torch.randn(2, side, side, c_in, device="cuda", generator=gen)
@@ -35,6 +51,7 @@ def test_layer_of_a_small_batch(side, c_in, c_out, k, stride):
     b = torch.randn(c_out, device="cuda", generator=gen)
     y, mask = mw.conv_forward(x, w, b, stride, 0, 0, alpha=0.2, want_mask=True)
     many = 200 * 64 * 64 // y[0].numel() + 1
+    assert c_out <= 64 or 2 * many * y[0].numel() // c_out < 191 * 128      # (else split operands)
     big, _ = mw.conv_forward(x.repeat(many, 1, 1, 1), w, b, stride, 0, 0, alpha=0.2, want_mask=True)
     if c_in % 64 or c_out % 64:      # (else the large batch may take a tile that splits K)
         assert torch.equal(big[:2], y) and torch.equal(big[-2:], y)
