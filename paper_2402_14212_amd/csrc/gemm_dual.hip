@@ -265,7 +265,6 @@ static hipError_t bp_pair_r(int tile_r, int tile_d, const BpLayerArgs& a, hipStr
     case TILE_64X128: return bp_pair_d<Tile64x128>(tile_d, a, stream);
     case TILE_64K2: return bp_pair_d<Tile64K2>(tile_d, a, stream);
     case TILE_FINE_K4: return bp_pair_d<FineK4Cfg>(tile_d, a, stream);
-    case TILE_FINE: return bp_pair_d<FineCfg>(tile_d, a, stream);
     case TILE_64: return bp_pair_d<Tile64>(tile_d, a, stream);
     default: return bp_pair_d<Tile32K4>(tile_d, a, stream);
   }
@@ -285,7 +284,6 @@ hipError_t gemm_bp_layer(const BpLayerArgs& a, hipStream_t stream, uint64_t* mor
         (int64_t)a.batch * a.d_out >= 4) {
       if (tile_r == TILE_32K4) return bp_pair_d<Tile32K4, false>(tile_d, a, stream);
       if (tile_r == TILE_FINE_K4) return bp_pair_d<FineK4Cfg, false>(tile_d, a, stream);
-      if (tile_r == TILE_FINE) return bp_pair_d<FineCfg, false>(tile_d, a, stream);
       return bp_pair_d<Tile64, false>(tile_d, a, stream);
     }
   }

@@ -121,8 +121,16 @@ int phase3_dw_tile(int B, int d_out, int d_in, int next_out, bool split) {
   return pick_tile_dw_f32(d_out, d_in, partner, true);
 }
 
+// Beside a weight gradient the reverse product is not alone on the chip, and the traffic of small tiles counts: TILE_FINE not at all
+// (six layers, backprop, us with TILE_64 and with it: 128 wide on 1000 rows 202 and 220, on 300 95 and 99, 240 on 700 162 and 175, 131 ..
+// 129 on 1000 260 and 261, 96 on 60 70 and 69), TILE_FINE_K4 up to 128 rows and while it leaves some of 128 places free (with TILE_32K4
+// and with it: 384 wide on 200 89 and 98, 448 on 250 105 and 113, 256 on 256 89 and 95, four of 1000 on 100 96 and 100; 512 on
+// 64 82 and 70, 411 on 60 88 and 70, 700 on 100 125 and 111, four of 900 on 120 94 and 93). The same bits.
 int bp_rev_tile(int d_out, int d_in, int B) {
-  return split_pays(1, B, d_in, d_out) && split_pays(1, d_out, d_in, B) ? pick_split_tile(1, B, d_in, false) : pick_tile_f32(B, d_in, d_out);
+  if (split_pays(1, B, d_in, d_out) && split_pays(1, d_out, d_in, B)) return pick_split_tile(1, B, d_in, false);
+  const int t = pick_tile_f32(B, d_in, d_out);
+  if (t == TILE_FINE) return TILE_64;
+  return t == TILE_FINE_K4 && (B > 128 || tiles_of(B, d_in, 32, 32) >= 128) ? TILE_32K4 : t;
 }
 
 int bp_dw_tile(int d_out, int d_in, int B, int partner) {

@@ -124,3 +124,32 @@ def test_weights_of_less_than_a_chunk_on_many_rows(widths, alpha):
     h = net.backprop_grad(x, t).flat.double()
     assert net.memory_stats()["sign_mismatches"] == 0
     assert torch.isfinite(g).all() and ((g - h).norm() <= 5e-5 * h.norm()).item()
+
+
+@pytest.mark.parametrize("d,batch", [(512, 128), (512, 129), (1000, 97), (992, 100), (991, 128), (1024, 100), (200, 140), (129, 300)])
+def test_backprop_where_its_reverse_tile_changes(d, batch):
+    """Both sides of the lines of the reverse product beside a weight gradient (rows, tiles, K), against
+    the gradient in 64 bits with the signs of the handle's own pre-activations. Bound: sums of d or batch terms, four times."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d + batch)
+    Ws = [torch.linalg.qr(torch.randn(d, d, device="cuda", generator=gen))[0].contiguous() for _ in range(2)]
+    bs = [0.1 * torch.randn(d, device="cuda", generator=gen) for _ in range(2)]
+    x, t = torch.randn(batch, d, device="cuda", generator=gen), torch.randn(batch, d, device="cuda", generator=gen)
+    net = mw.MoonwalkNet(Ws, bs, [0.3, 0.3], batch)
+    net.moonwalk_grad(x, t)
+    got = net.backprop_grad(x, t)
+    ref, acts, slopes = [], [x.double()], []
+    for i, (W, b) in enumerate(zip(Ws, bs)):
+        words = net.fetch_mask(i)
+        e = np.arange(batch * d)
+        bits = torch.tensor(((words[e // 64] >> (e % 64).astype(np.uint64)) & np.uint64(1)).astype(bool), device="cuda").reshape(batch, d)
+        slopes.append(torch.where(bits, 1.0, 0.3).double())
+        acts.append((acts[-1] @ W.double().t().contiguous() + b.double()) * slopes[-1])
+    h = (acts[-1] - t.double()) / batch
+    for i in (1, 0):
+        h = h * slopes[i]
+        ref = [(h.t().contiguous() @ acts[i]).reshape(-1), h.sum(0)] + ref
+        h = h @ Ws[i].double()
+    ref = torch.cat(ref)
+    bound = 4 * math.sqrt(max(d, batch)) * 2.0 ** -24
+    assert ((got.flat.double() - ref).norm() <= bound * ref.norm()).item()
