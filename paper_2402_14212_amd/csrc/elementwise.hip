@@ -739,8 +739,11 @@ __global__ void __launch_bounds__(EW_THREADS) k_reduce_slices(ReduceTask a, Redu
 constexpr int LOSS_UNROLL = 4;
 // What one launch can do beyond the output cotangent and the partial sums (LossStep::done != NULL): the loss itself, by the
 // workgroup that finishes last; the cotangent of the pre-activations (alpha < 1) from the activation's own sign (x > 0 <=> z > 0
-// for alpha > 0); and the status words cleared for the rest of the step. Three launches less in every step of a leaky network (us:
-// six layers of 380 on 109 rows 128 and 123, of 701 .. 389 on 100 186 and 181).
+// for alpha > 0); and the status words cleared for the rest of the step. Three launches less in every step of a leaky network whose output is
+// small. Every workgroup writes its cache back before it counts, so that from some size on this costs more than the launches: up to
+// 128 workgroups (ew_loss_step_pays; whole steps in launches of their own and in one, us: 300 x 100 46.3 and 43.0, 512 x 256 68.1
+// and 64.5, 512 x 1024, 128 workgroups, 132.1 and 130.4, 512 x 2048, 256 of them, 208.2 and 210.1, 1024 x 1024 213.6 and 215.3,
+// 512 x 4096 375 and 386, 256 x 65536 2041 and 2310).
 struct LossStep {
   uint32_t* done;        // workgroups that have finished: zero between launches (the last one wraps it round)
   uint32_t* clear;       // three words to clear, or NULL
@@ -1333,6 +1336,10 @@ hipError_t ew_loss_grad(const float* xL, const float* t, int64_t rows, int d, fl
     e = hipGetLastError();
   }
   return e;
+}
+
+bool ew_loss_step_pays(const float* xL, const float* t, const float* hL, int64_t rows, int d) {
+  return plan_loss(xL, t, hL, rows, rows * d, 1.f).blocks <= 128;
 }
 
 hipError_t ew_loss_step(const float* xL, const float* t, int64_t rows, int d, float scale, float alpha, float* hL, float* loss,

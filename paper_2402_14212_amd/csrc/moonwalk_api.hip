@@ -1117,8 +1117,9 @@ int run_moonwalk(mw_handle* h, const float* x, const float* target, float* grads
   const float* x_L = nullptr;
   const Layer& top = h->layers[L - 1];
   // the loss, the cotangent of the last pre-activations and the status words in one launch; a launch each where the raw output
-  // cotangent is asked for (fragments, debugging) and where kernels are timed by class
-  const bool one_launch = h->S <= 0 && h->fuse && top.alpha > 0.f && !h->debug_keep && h->class_filter < 0;
+  // cotangent is asked for (fragments, debugging), where kernels are timed by class and for large outputs
+  const bool one_launch = h->S <= 0 && h->fuse && top.alpha > 0.f && !h->debug_keep && h->class_filter < 0 &&
+                          ew_loss_step_pays(h->xa, target, h->ha, B, top.d_out);
   if (!one_launch) MW_LAUNCH(h, s, MW_KCLASS_EW, ew_fill_u32(h->status, 0u, 3, s));
 
   if (h->S <= 0) {

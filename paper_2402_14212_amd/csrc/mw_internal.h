@@ -255,6 +255,7 @@ hipError_t ew_loss_grad(const float* xL, const float* t, int64_t rows, int d, fl
 // hL times alpha where xL is not positive (1: as it is; alpha > 0), the three words at `clear` (may be NULL) set to zero
 hipError_t ew_loss_step(const float* xL, const float* t, int64_t rows, int d, float scale, float alpha, float* hL, float* loss,
                         double* scratch, uint32_t* done, uint32_t* clear, uint32_t* nonfinite, hipStream_t stream);
+bool ew_loss_step_pays(const float* xL, const float* t, const float* hL, int64_t rows, int d);
 hipError_t ew_copy(const float* src, float* dst, int64_t n, hipStream_t stream);
 hipError_t ew_fill_u32(uint32_t* p, uint32_t value, int64_t n, hipStream_t stream);
 inline hipError_t ew_fill_f32(float* p, float value, int64_t n, hipStream_t stream) {
