@@ -89,18 +89,19 @@ __device__ __forceinline__ int split_addr(int row, int c) {
   return row * 256 + ((c ^ (row & 15)) << 4);
 }
 
-// The three parts of x and y, two bf16 to a word (x in the lower half); top: the largest magnitude seen, NaN aside
+// The three parts of x and y, two bf16 to a word (x in the lower half); top (TOP): the largest magnitude seen, NaN aside
 struct SplitPair { uint32_t part[3]; };
 __device__ __forceinline__ uint32_t bf16_pair(float x, float y) {
   uint32_t d;
   asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(d) : "v"(x), "v"(y));
   return d;
 }
+template <bool TOP = true>
 __device__ __forceinline__ SplitPair split_pair(float x, float y, float up, float& top) {
   SplitPair p;
   x *= up;
   y *= up;
-  top = fmaxf(fmaxf(fabsf(x), fabsf(y)), top);
+  if (TOP) top = fmaxf(fmaxf(fabsf(x), fabsf(y)), top);
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
     p.part[i] = bf16_pair(x, y);
@@ -111,11 +112,11 @@ __device__ __forceinline__ SplitPair split_pair(float x, float y, float up, floa
   }
   return p;
 }
-// sum + the squares of two bf16
+// sum + the squares of two bf16 (the shifted values are those that split_pair takes away; with v_dot2_f32_bf16 1024 x 4096 x 4096
+// takes 3 us more)
 __device__ __forceinline__ float add_squares(uint32_t pair, float sum) {
-  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-  const bf16x2 v = __builtin_bit_cast(bf16x2, pair);
-  return __builtin_amdgcn_fdot2_f32_bf16(v, v, sum, false);
+  const float x = __uint_as_float(pair << 16), y = __uint_as_float(pair & 0xFFFF0000u);
+  return fmaf(x, x, fmaf(y, y, sum));
 }
 // combine over the eight lanes of an aligned group of eight
 __device__ __forceinline__ float dpp_f32(float v, int quad_or_mirror) {
@@ -173,7 +174,7 @@ struct SplitLoader {
 
 // Split the staged values of `ld` into the planes of an LDS stage (`base`: this operand's rows of the first plane). SIGNED:
 // operand A, negated if `negative` and, once more, where the second K group reads it. COLSUM, SQUARES: csum gets the sums of the values
-// or of the squares of their first parts (2^48 times the values'), by row.
+// or of the squares of their first parts (2^48 times the values'), by row; the latter stand in for the largest magnitude.
 template <class Cfg, bool SIGNED, bool COLSUM, bool SQUARES, class Ld, class XfDev>
 __device__ __forceinline__ void split_store(const Ld& ld, const XfDev& xf, char* __restrict__ base, float* __restrict__ csum,
                                             float& top, bool negative) {
@@ -186,7 +187,7 @@ __device__ __forceinline__ void split_store(const Ld& ld, const XfDev& xf, char*
 #pragma unroll
     for (int i = 0; i < Ld::NV; ++i) {
       const float4 w = ld.value(i, xf);
-      const SplitPair a = split_pair(w.x, w.y, up(Map::k(0)), top), b = split_pair(w.z, w.w, up(Map::k(0)), top);
+      const SplitPair a = split_pair<!SQUARES>(w.x, w.y, up(Map::k(0)), top), b = split_pair<!SQUARES>(w.z, w.w, up(Map::k(0)), top);
       if (SQUARES) csum[i] = add_squares(b.part[0], add_squares(a.part[0], csum[i]));
       // a thread's chunks are the same k of rows so far apart that they have the same pattern of chunks
       static_assert(NT * 4 / BK % (BK == 32 ? 32 : 16) == 0, "see split_addr");
@@ -219,7 +220,7 @@ __device__ __forceinline__ void split_store(const Ld& ld, const XfDev& xf, char*
         for (int h = 0; h < Ld::KP / 2; ++h) {
           const float x = e[q][2 * h], y = e[q][2 * h + 1];
           if (COLSUM) csum[4 * j + q] += x + y;
-          s[h] = split_pair(x, y, up(k), top);
+          s[h] = split_pair<!SQUARES>(x, y, up(k), top);
           if (SQUARES) csum[4 * j + q] = add_squares(s[h].part[0], csum[4 * j + q]);
         }
         char* p = base + split_addr<BK>(row + q, k >> 3) + (k & 7) * 2;
@@ -266,8 +267,8 @@ __device__ __forceinline__ void plain_store(const Ld& ld, const XfDev& xf, float
 // seen over sqrt(K) |a| |b|, among two million values each, K = 1024 .. 8192: 1e-9 .. 3e-9 for N(0, 1) operands, 1.4e-8 where the terms
 // of one half of K have one sign and those of the other half the other, 1.2e-8 where two terms of 1000 times the others' size
 // cancel, 1.9e-8 where the two groups of K have sums of opposite sign.
-// Of N(0, 1) values 3.2e-8 K are that near: 0.3 of a wavefront's 2048 at K = 4096. What it costs: 1.6 % of the time for the squares
-// and 1.2 % for the sums (six layers of 4096, batch 1024).
+// Of N(0, 1) values 3.2e-8 K are that near: 0.3 of a wavefront's 2048 at K = 4096. What it costs: 1024 x
+// 4096 x 4096 206 us instead of 194, about half of it the squares, half the sums; 131072 x 128 x 1152 286 instead of 275.
 // More than NEAR_MOST in one wavefront (sums that cancel all over), or rows so small or large that their squares leave
 // fp32: the workgroup's tile is formed again with fp32 instructions, as the pre-activations of smaller layers are. Rows and
 // columns of zeros are exact and not concerned. Apart from that a value depends on its row, its column and the tile alone, and a
@@ -514,7 +515,6 @@ struct SplitProduct {
         out[i][j] *= 0x1p-24f * 0x1p-24f;
         static_assert(SPLIT_UP == 24, "both operands");
       }
-    if (!finite) *flag = 1;
     if constexpr (NEAR) {
       bool all = false;
       const unsigned long long near = Near::template find<LB>(K, bias, Near::place(lds_f), out, all);
@@ -525,9 +525,10 @@ struct SplitProduct {
         return;
       }
       Near::template form_again<LB>(near, ra, lda, rb, ldb, K, m0, n0, xf, bias, out);
-    } else {
-      __syncthreads();
+      return;   // (no part and no sum can have overflowed: what is not finite has met a NaN)
     }
+    if (!finite) *flag = 1;
+    __syncthreads();
     if (__builtin_amdgcn_readfirstlane(flag[0]) == 0) return;
     // Operands so small that neither a part nor a sum can have overflowed: what is not finite has met a NaN, and fp32
     // instructions would say the same (a network whose training has diverged takes no longer than another)

@@ -34,7 +34,7 @@ int pick_split_tile(int64_t sets, int M, int N, bool s256);
 int pick_tile_f32(int M, int N, int K);
 // the tile of a pre-activation product: the same in Phase I, where Phase III forms it again, and in backprop. Split operands where
 // Phase III recomputes the activation in a launch of its own (phase3_tile) with 128 x 128 tiles (us for 1024 x 4096 x 4096: 298 in
-// fp32, 197 split; with 64 x 64 tiles there is nothing to gain, 1024 x 1024 x 1024 23.8 and 22.5). What comes out next to zero is
+// fp32, 206 split; with 64 x 64 tiles there is nothing to gain, 1024 x 1024 x 1024 23.8 and 22.5). What comes out next to zero is
 // formed again in 64 bits (NearZero).
 int pick_tile_z(int M, int N, int K, bool split);
 // tile of a layer's kernel in Phase III: a split tile (of the cotangent product; the activation is then recomputed by
