@@ -132,6 +132,25 @@ def test_rows_of_any_kind(kind):
     assert np.array_equal(got[rows, at], z[rows, at] > 0)
 
 
+def test_rows_that_leave_the_range_of_the_squares():
+    """Rows of 2^20 to 2^70 of their neighbours' size, infinities and NaN in some: every finite row within an fp32 sum's error of the
+    64-bit one, every other as infinite or NaN as IEEE says, signs those of the values."""
+    gen = generator(9)
+    x = torch.randn(ROWS, K, device="cuda", generator=gen) * torch.exp2(torch.randint(0, 2, (ROWS, 1), device="cuda", generator=gen)
+                                                                        * torch.randint(20, 71, (ROWS, 1), device="cuda", generator=gen).float())
+    w = torch.randn(K, N, device="cuda", generator=gen) * 2.0 ** 20
+    x[100:ROWS // 2:997, 5] = float("inf")
+    x[101:ROWS // 2:1499, 7] = float("nan")
+    y, got = by_row(x, w)
+    odd = ~torch.isfinite(x).all(1)
+    z = x.double() @ w.double()
+    bound = 4 * math.sqrt(K) * 2.0 ** -24 * x.double().norm(dim=1)[:, None] * w.double().norm(dim=0)[None]
+    assert ((y.double() - z).abs() <= bound)[~odd].all()
+    ref = torch.where(torch.isnan(x).any(1)[:, None], float("nan"), float("inf") * torch.sign(w[5])[None].double()).expand(ROWS, N)[odd]
+    assert torch.equal(torch.isnan(y[odd]), torch.isnan(ref)) and torch.equal(torch.nan_to_num(y[odd].double()), torch.nan_to_num(ref))
+    assert np.array_equal(got, (y > 0).cpu().numpy())
+
+
 def test_a_row_does_not_depend_on_the_others():
     gen = generator(5)
     W = orthonormal(K, N, gen)
