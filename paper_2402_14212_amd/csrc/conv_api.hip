@@ -681,7 +681,7 @@ int run_conv_moonwalk(mw_conv_handle* h, const float* x, const float* target, fl
         } else {
           CV_HIP(conv_vijp_layer(l.geom(), n_img, xc, l.w, l.b, l.alpha, l.Cout,
                                  hin + img0 * (hin_as_read ? l.out_img() : l.in_img()), hin_as_read ? 1 : 0, l.Tinv, mask32,
-                                 xout + o, hout + o, h->ctz + o, mismatches, !apply, s));
+                                 xout + o, hout + o, h->ctz + o, mismatches, !apply && l.z_split(), s));
         }
       }
       int rc = conv_weight_grad(h, l, xin, h->ctz, g_scale, apply ? const_cast<float*>(l.w) : grads_out + l.dW_off,

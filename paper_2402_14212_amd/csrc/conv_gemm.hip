@@ -266,7 +266,10 @@ hipError_t conv_vijp_layer(const ConvGeom& g, int n_img, const float* x, const f
                            unsigned long long* mismatches, bool split, hipStream_t stream) {
   if (n_img <= 0) return hipSuccess;
   const int M = n_img * g.Ho * g.Wo, K1 = g.taps() * g.C;
-  if (tile_is_split(z_tile(M, Cout, K1, g.C, Cout, split))) {   // the solve by itself, then the product that takes it
+  // The solve by itself, then the product that takes it. From 256 output channels on the solve then takes split operands too (chains
+  // of three layers of 256 channels, 16 images of 64 x 64, ten inputs: gradients 2.5e-7 to 9.4e-5 from 64 bits with both in one
+  // fp32 kernel, 2.2e-7 to 2.3e-7 and once 8.4e-5 here).
+  if (tile_is_split(z_tile(M, Cout, K1, g.C, Cout, split))) {
     hipError_t e = conv_sub_solve(g, n_img, Cout, hin, hin_as_read, Tinv, ctz, split, stream);
     return e != hipSuccess ? e : conv_vijp_given(g, n_img, x, w, b, alpha, Cout, ctz, mask32, xout, hout, mismatches, split, stream);
   }

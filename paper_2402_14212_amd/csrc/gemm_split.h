@@ -311,7 +311,7 @@ struct NearZero {
       if (((int)threadIdx.x & 7) == 0) dst[(k >> 3) * R + Ld::row_of(j)] = LAYOUT == KCONTIG ? norm(v) : v;
     }
   }
-  // |.| of values times 2^SPLIT_UP; what is too small or too large is infinite, for outside() below
+  // |.| of values times 2^SPLIT_UP; what is too small or too large is infinite, for find() below
   static __device__ __forceinline__ float norm(float squares) {
     const float n = __builtin_amdgcn_sqrtf(squares);
     return squares > NEAR_SQUARES_MAX || (squares > 0.f && squares < NEAR_SQUARES_MIN) ? __builtin_inff() : n;

@@ -64,8 +64,9 @@ int pick_tile_f32(int M, int N, int K) {
   if (tiles_of(M, N, 64, 128) >= 512) return TILE_64X128;
   if (tiles_of(M, N, 64, 64) >= 192) return K >= 1024 ? TILE_64K2 : TILE_64;
   // (TILE_32K4 against TILE_FINE_K4 in us, NT: 32 x 512 x 512 5.8 and 4.0, 100 x 400 x 400 6.0 and 4.1, 100 x 1000 x 1000, 128 tiles of
-  // 32 x 32, 9.6 and 8.9, 200 x 700 x 700, 154 of them, 8.1 and 8.2, 256 x 1024 x 1024 9.7 and 15.9: twice the operand traffic; and
-  // with long rows 17 x 2500 x 2500 19.7 and 30.5)
+  // 32 x 32, 9.6 and 8.9, 200 x 700 x 700, 154 of them, 8.1 and 8.2, 256 x 1024 x 1024 9.7 and 15.9: twice the operand traffic. Longer
+  // K: whole steps of three layers of 2048 on 32 rows 204 and 219, four of 1200 on 96 200 and 201, but four of 1536 on 32 280 and
+  // 264; 17 x 2500 x 2500 19.7 and 30.5, but 32 x 512 x 2048 15.7 and below 9.7.)
   if (K >= 256) return K <= 1024 && tiles_of(M, N, 32, 32) <= 128 ? TILE_FINE_K4 : TILE_32K4;
   return fine_pays(1, M, N) ? TILE_FINE : TILE_64;
 }
@@ -1050,9 +1051,10 @@ int reverse_and_sweep(const Step& c) {
 }
 
 // Whether the whole step goes into one workgroup (small_net.hip). Leaky layers, every buffer in one CU's LDS, nothing kept for
-// debugging or timed by kernel class, and products of at most sixteen slices of 16 x 16 x 32 (layers of 64 on a batch of 32): us layer by
-// layer and here: four layers of 64 on 32 68 and 58, five of 61 .. 49 on 25 104 and 68, nine of 32 on 64 138 and 95; four of 64 on 64, twice the work,
-// 67 to 76 and 76.
+// debugging or timed by kernel class, and products of at most sixteen slices of 16 x 16 x 32. Us layer by layer (from what the kernels take to what a slow host
+// makes of their launches) and here: two slices, three layers of 20 .. 5 on 7, 41 and 17; eight, four of 64 on 16, 62 to 67 and 50; sixteen, four of 64
+// on 32, 54 to 66 and 56, sixteen of 64 on 32 185 to 233 and 219; eighteen, four of 48 on 48, 58 to 73 and 59; 24, four of 64 on 48, 54 to 68 and 67; 32, on
+// 64, 54 to 68 and 76.
 constexpr int64_t SMALL_NET_MAX_WORK = 16;
 bool small_net_ok(const mw_handle* h) {
   const int L = h->L, B = h->B;

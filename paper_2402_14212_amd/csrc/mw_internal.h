@@ -9,11 +9,10 @@ namespace mw {
 
 // tile selectors (same values as MW_TILE_* in the public header)
 constexpr int TILE_AUTO = 0, TILE_128 = 1, TILE_64 = 2, TILE_32K4 = 3, TILE_32K8 = 4, TILE_64K2 = 5, TILE_128W8 = 6, TILE_64X128 = 7;
-// tiles of the products on split operands (gemm_split.h), chosen by the library only; eight wavefronts each (S64Q: four)
-// 32 x 32 tiles of four 16 x 16 wavefronts (gemm_fine.h): TILE_64's bits for small outputs
-constexpr int TILE_FINE = 15;
-// 16 x 16 tiles with K split over four wavefronts: TILE_32K4's bits
-constexpr int TILE_FINE_K4 = 14;
+// Chosen by the library only, as those below. Fp32 tiles for small outputs (gemm_fine.h): 16 x 16 tiles with K split over four
+// wavefronts, TILE_32K4's bits, and 32 x 32 tiles of four 16 x 16 wavefronts, TILE_64's bits.
+constexpr int TILE_FINE_K4 = 14, TILE_FINE = 15;
+// tiles of the products on split operands (gemm_split.h); eight wavefronts each (S64Q: four)
 constexpr int TILE_S256 = 16, TILE_S128 = 17, TILE_S64 = 18, TILE_S64Q = 19;
 inline bool tile_is_split(int tile) { return tile >= TILE_S256; }
 // least K of a product that takes split operands: below it the product is a few K tiles of launch and memory latency
@@ -145,8 +144,8 @@ hipError_t gemm_phase3_pair(int tile_v, const VijpArgs* v, int M, int N, int K, 
 // Phase III for several independent stretches of the network in one launch: n_v layer kernels of one shape
 // (M x N x K each, the same alpha) and n_d weight-gradient products of one shape (the same scale and beta; a
 // NULL db is skipped), either count may be 0, at most 16 each. Every product gets the bits it gets from
-// gemm_phase3_pair. Only for shapes phase3_group_ok accepts and 16-byte aligned operands (else an error,
-// nothing launched).
+// gemm_phase3_pair. Only for shapes phase3_group_ok accepts, weight gradients of widths that are
+// multiples of four, and layers of one alpha (else an error, nothing launched).
 constexpr int MAX_PHASE3_GROUP = 16;
 bool phase3_group_ok(int M, int N, int K);
 hipError_t gemm_phase3_group(int n_v, const VijpArgs* v, int M, int N, int K, int n_d, const DwArgs* d, hipStream_t stream);

@@ -2,8 +2,8 @@
 // activations, cotangents and signs in LDS.
 //
 // A network of four layers of 64 on a batch of 32 is 17 launches of 2 to 6 us, each of them a launch, a memory latency and
-// a few hundred clocks of work: 68 us, 57 here. A product is LDS reads, matrix instructions, epilogue and a barrier that
-// waits for LDS only; its weights are loaded while the product before it runs. What bounds it is that chain on one CU: 2.9 us
+// a few hundred clocks of work: 54 to 68 us, 56 here. A product is LDS reads, matrix instructions, epilogue and a
+// barrier; its weights are loaded while the product before it runs. What bounds it is that chain on one CU: 2.9 us
 // a layer in Phase I (1.0 without loads and matrix instructions, 0.7 for these, 1.0 for the loads, sixteen rows each of them), 2.1
 // in Phase II, 8 in Phase III with two products and a weight gradient. The same products in the same order of k
 // (gemm_fine.h), hence the bits of the launches layer by layer.
