@@ -437,7 +437,6 @@ struct SplitProduct {
     const ANone::Dev none;
     const int nkt = (K + BK - 1) / BK;
     float top_a = 0.f, top_b = 0.f;
-    float sq_a[NEAR ? LdA::NS : 1] = {}, sq_b[NEAR ? LdB::NS : 1] = {};   // squares of the rows this thread stages
     f32x16 acc[Cfg::NACC];
 #pragma unroll
     for (int i = 0; i < Cfg::NACC; ++i)
@@ -446,6 +445,13 @@ struct SplitProduct {
     if (COLSUM) {
 #pragma unroll
       for (int j = 0; j < LdA::NS; ++j) csum[j] = 0.f;
+    }
+    float sq_a[NEAR ? LdA::NS : 1], sq_b[NEAR ? LdB::NS : 1];   // squares of the rows this thread stages
+    if constexpr (NEAR) {
+#pragma unroll
+      for (int j = 0; j < LdA::NS; ++j) sq_a[j] = 0.f;
+#pragma unroll
+      for (int j = 0; j < LdB::NS; ++j) sq_b[j] = 0.f;
     }
 #define MW_REQUEST(slot, idx)                       \
   do {                                              \
@@ -456,13 +462,13 @@ struct SplitProduct {
     xf.template prepare<LA, BM, BK, NT, LdA::KP>(m0, M, K);
     MW_REQUEST(0, 0);
     MW_REQUEST(1, 1);
-    if (threadIdx.x < 4) flag[threadIdx.x] = 0;
+    if (threadIdx.x < (NEAR ? 4 : 3)) flag[threadIdx.x] = 0;
 
     // idx: the K tile
 #define MW_TO_LDS(slot, stage, idx)                                                                                          \
   do {                                                                                                                       \
     split_store<Cfg, true, COLSUM, NEAR>(a[slot], xf, lds + (stage) * Cfg::STAGE, NEAR ? sq_a : csum, top_a, ((idx) / SPLIT_TURN) & 1); \
-    split_store<Cfg, false, false, NEAR>(b[slot], none, lds + (stage) * Cfg::STAGE + BM * BK * 2, sq_b, top_b, false);        \
+    split_store<Cfg, false, false, NEAR>(b[slot], none, lds + (stage) * Cfg::STAGE + BM * BK * 2, NEAR ? sq_b : (float*)nullptr, top_b, false); \
   } while (0)
 #define MW_MULTIPLY(stage) multiply(lds + (stage) * Cfg::STAGE, wm, wn, wk, r, g, acc)
     MW_TO_LDS(0, 0, 0);
