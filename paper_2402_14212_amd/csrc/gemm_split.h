@@ -174,15 +174,15 @@ struct SplitLoader {
 
 // Split the staged values of `ld` into the planes of an LDS stage (`base`: this operand's rows of the first plane). SIGNED:
 // operand A, negated if `negative` and, once more, where the second K group reads it. COLSUM, SQUARES: csum gets the sums of the values
-// or of the squares of their first parts (2^48 times the values'), by row; the latter stand in for the largest magnitude.
+// or of the squares of their first parts, by row; the latter stand in for the largest magnitude. scale: a power of two.
 template <class Cfg, bool SIGNED, bool COLSUM, bool SQUARES, class Ld, class XfDev>
 __device__ __forceinline__ void split_store(const Ld& ld, const XfDev& xf, char* __restrict__ base, float* __restrict__ csum,
-                                            float& top, bool negative) {
+                                            float& top, bool negative, float scale = (float)(1 << SPLIT_UP)) {
   static_assert(!(COLSUM && SQUARES), "one or the other");
   using Map = typename Ld::Map;
   constexpr int BK = Cfg::BK, NT = Cfg::NT, PLANE = Cfg::PLANE;
   // (k: the same 16-k step for all of a chunk)
-  auto up = [&](int k) { return split_up(SIGNED && (negative != (Cfg::WK == 2 && ((k >> 4) & 1)))); };
+  auto up = [&](int k) { return SIGNED && (negative != (Cfg::WK == 2 && ((k >> 4) & 1))) ? -scale : scale; };
   if constexpr (Ld::KP == 1) {
 #pragma unroll
     for (int i = 0; i < Ld::NV; ++i) {
@@ -269,7 +269,8 @@ __device__ __forceinline__ void plain_store(const Ld& ld, const XfDev& xf, float
 // cancel, 1.9e-8 where the two groups of K have sums of opposite sign.
 // Of N(0, 1) values 3.2e-8 K are that near: 0.3 of a wavefront's 2048 at K = 4096. What it costs: 1024 x
 // 4096 x 4096 206 us instead of 194, about half of it the squares, half the sums; 131072 x 128 x 1152 286 instead of 275.
-// More than NEAR_MOST in one wavefront (sums that cancel all over), or rows so small or large that their squares leave
+// More than NEAR_MOST in one wavefront (sums that cancel all over; a column that is near zero in all rows, as in deep networks whose
+// rows have become alike, is 32), or rows so small or large that their squares leave
 // fp32: the workgroup's tile is formed again with fp32 instructions, as the pre-activations of smaller layers are. Rows and
 // columns of zeros are exact and not concerned. Apart from that a value depends on its row, its column and the tile alone, and a
 // product that is formed again elsewhere with the same tile has the same bits.
@@ -277,8 +278,8 @@ __device__ __forceinline__ void plain_store(const Ld& ld, const XfDev& xf, float
 // rows 58 and 43, six of 2048 on 1024 43 and 37, of 3000 on 700 63 and 42, of 4096 on 1024 (eleven) 146 and 94; none in the first layer here.
 // What is left comes from the rounding of the layers' inputs, as it does with fp32 products.
 constexpr float NEAR_ERROR = 4e-8f;
-constexpr int NEAR_MOST = 16;
-constexpr float NEAR_SQUARES_MIN = 0x1p-60f, NEAR_SQUARES_MAX = 0x1p110f;   // (of values times 2^SPLIT_UP)
+constexpr int NEAR_MOST = 64;
+constexpr float NEAR_SQUARES_MIN = 0x1p-60f, NEAR_SQUARES_MAX = 0x1p110f;   // (of the values as they are staged, times a power of two)
 
 template <class EpiDev, class = void>
 struct near_zero : std::false_type {};
@@ -311,20 +312,20 @@ struct NearZero {
       if (((int)threadIdx.x & 7) == 0) dst[(k >> 3) * R + Ld::row_of(j)] = LAYOUT == KCONTIG ? norm(v) : v;
     }
   }
-  // |.| of values times 2^SPLIT_UP; what is too small or too large is infinite, for find() below
+  // |.| of the values as staged; what is too small or too large is infinite, for find() below
   static __device__ __forceinline__ float norm(float squares) {
     const float n = __builtin_amdgcn_sqrtf(squares);
     return squares > NEAR_SQUARES_MAX || (squares > 0.f && squares < NEAR_SQUARES_MIN) ? __builtin_inff() : n;
   }
 
-  // bias: epi's, of this lane's columns. The values of a wavefront that are formed again (bit i * CNT + j: out[i][j]); all: its
+  // out and bias (epi's, of this lane's columns): times the powers of two of both operands. The values of a wavefront that are formed again (bit i * CNT + j: out[i][j]); all: its
   // tile is to be. (Rows and columns outside the matrix are zeros, and so are their results.)
   template <int LB>
   static __device__ __forceinline__ unsigned long long find(int K, const float (&bias)[Cfg::WTN], const float* __restrict__ norms,
                                                             const float (&out)[Cfg::NACC][Cfg::CNT], bool& all) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 31, g = lane >> 5;
     const int wk = wave % Cfg::WK, wn = (wave / Cfg::WK) % Cfg::WN, wm = wave / (Cfg::WK * Cfg::WN);
-    const float c = NEAR_ERROR * 0x1p-24f * 0x1p-24f * __builtin_amdgcn_sqrtf((float)K);
+    const float c = NEAR_ERROR * __builtin_amdgcn_sqrtf((float)K);
     float line[Cfg::WTN];
 #pragma unroll
     for (int tn = 0; tn < Cfg::WTN; ++tn) {
@@ -357,12 +358,25 @@ struct NearZero {
     return found;
   }
 
-  // whole wavefronts
-  template <int LB, class XfDev>
+  template <int Q>
+  static __device__ __forceinline__ void load(float (&v)[Q], __amdgpu_buffer_rsrc_t rs, uint32_t off) {
+    if constexpr (Q == 4) {
+      const float4 w = buf_load_f32x4(rs, off);
+      v[0] = w.x;
+      v[1] = w.y;
+      v[2] = w.z;
+      v[3] = w.w;
+    } else {
+      v[0] = buf_load_f32(rs, off);
+    }
+  }
+
+  // whole wavefronts; VEC: K is a multiple of four
+  template <int LB, bool VEC, class XfDev>
   static __device__ __forceinline__ void form_again(unsigned long long flags, __amdgpu_buffer_rsrc_t ra, int64_t lda, __amdgpu_buffer_rsrc_t rb,
                                                     int64_t ldb, int K, int m0, int n0, const XfDev& xf, const float (&bias)[Cfg::WTN],
                                                     float (&out)[Cfg::NACC][Cfg::CNT]) {
-    constexpr int AT_ONCE = 8;   // loads of each operand in flight
+    constexpr int AT_ONCE = LB == KCONTIG ? 8 : 5;   // in flight: 2048 k, or 1280
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wk = wave % Cfg::WK, wn = (wave / Cfg::WK) % Cfg::WN, wm = wave / (Cfg::WK * Cfg::WN);
     unsigned long long some = __ballot(flags != 0);
@@ -374,18 +388,27 @@ struct NearZero {
       const int i = which / Cfg::CNT, j = which % Cfg::CNT;
       const int row = m0 + (wm * Cfg::WTM + i / Cfg::WTN) * 32 + acc_row(wk * Cfg::CNT + j, from >> 5);
       const int col = n0 + (wn * Cfg::WTN + i % Cfg::WTN) * 32 + (from & 31);
+      // four k a lane; where rows end inside such four, one
+      constexpr int Q = VEC ? 4 : 1, STEP = 64 * Q;
       double sum = 0.0;
 #pragma clang loop unroll(disable)
-      for (int k0 = lane; k0 - lane < K; k0 += 64 * AT_ONCE) {
-        float va[AT_ONCE], vb[AT_ONCE];
+      for (int k0 = Q * lane; k0 - Q * lane < K; k0 += STEP * AT_ONCE) {
+        float va[AT_ONCE][Q], vb[AT_ONCE][Q];
 #pragma unroll
         for (int u = 0; u < AT_ONCE; ++u) {
-          const int k = k0 + 64 * u;
-          va[u] = buf_load_f32(ra, k < K ? xf.place(row, k, lda) : OOB);
-          vb[u] = buf_load_f32(rb, k < K ? (LB == KCONTIG ? (uint32_t)col * (uint32_t)ldb + (uint32_t)k : (uint32_t)k * (uint32_t)ldb + (uint32_t)col) * 4u : OOB);
+          const int k = k0 + STEP * u;
+          load<Q>(va[u], ra, k < K ? xf.place(row, k, lda) : OOB);
+          if (LB == KCONTIG) {
+            load<Q>(vb[u], rb, k < K ? ((uint32_t)col * (uint32_t)ldb + (uint32_t)k) * 4u : OOB);
+          } else {
+#pragma unroll
+            for (int q = 0; q < Q; ++q) vb[u][q] = buf_load_f32(rb, k < K ? ((uint32_t)(k + q) * (uint32_t)ldb + (uint32_t)col) * 4u : OOB);
+          }
         }
 #pragma unroll
-        for (int u = 0; u < AT_ONCE; ++u) sum += (double)va[u] * (double)vb[u];
+        for (int u = 0; u < AT_ONCE; ++u)
+#pragma unroll
+          for (int q = 0; q < Q; ++q) sum += (double)va[u][q] * (double)vb[u][q];
       }
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
@@ -463,11 +486,12 @@ struct SplitProduct {
     MW_REQUEST(0, 0);
     MW_REQUEST(1, 1);
     if (threadIdx.x < (NEAR ? 4 : 3)) flag[threadIdx.x] = 0;
+    const float up_a = NEAR ? near_scale(flag + 1, xf, lane) : (float)(1 << SPLIT_UP);
 
     // idx: the K tile
 #define MW_TO_LDS(slot, stage, idx)                                                                                          \
   do {                                                                                                                       \
-    split_store<Cfg, true, COLSUM, NEAR>(a[slot], xf, lds + (stage) * Cfg::STAGE, NEAR ? sq_a : csum, top_a, ((idx) / SPLIT_TURN) & 1); \
+    split_store<Cfg, true, COLSUM, NEAR>(a[slot], xf, lds + (stage) * Cfg::STAGE, NEAR ? sq_a : csum, top_a, ((idx) / SPLIT_TURN) & 1, up_a); \
     split_store<Cfg, false, false, NEAR>(b[slot], none, lds + (stage) * Cfg::STAGE + BM * BK * 2, NEAR ? sq_b : (float*)nullptr, top_b, false); \
   } while (0)
 #define MW_MULTIPLY(stage) multiply(lds + (stage) * Cfg::STAGE, wm, wn, wk, r, g, acc)
@@ -512,6 +536,27 @@ struct SplitProduct {
       Near::template gather<LdB, LB, BN>(sq_b, Near::place(lds_f) + BM);
     }
     finish<true>(lds_f, acc, out, wm, wn, wk, lane);
+    static_assert(SPLIT_UP == 24, "both operands");
+    if constexpr (NEAR) {
+      bool all = false;
+      float scaled[Cfg::WTN];
+#pragma unroll
+      for (int tn = 0; tn < Cfg::WTN; ++tn) scaled[tn] = bias[tn] * up_a * 0x1p24f;   // (infinite: far from any sum)
+      const unsigned long long near = Near::template find<LB>(K, scaled, Near::place(lds_f), out, all);
+      if (all) flag[3] = 1;
+      __syncthreads();
+      if (__builtin_amdgcn_readfirstlane(flag[3]) != 0) {
+        repeat_f32<true>(ra, lda, rb, ldb, M, N, K, m0, n0, lds_f, xf, out, nkt, wm, wn, wk, r, g, lane);
+        return;
+      }
+      const float down = 1.f / up_a;
+#pragma unroll
+      for (int i = 0; i < Cfg::NACC; ++i)
+#pragma unroll
+        for (int j = 0; j < Cfg::CNT; ++j) out[i][j] = out[i][j] * 0x1p-24f * down;
+      Near::template form_again<LB, VEC>(near, ra, lda, rb, ldb, K, m0, n0, xf, bias, out);
+      return;   // (no part and no sum can have overflowed: what is not finite has met a NaN)
+    }
     bool finite = true;
 #pragma unroll
     for (int i = 0; i < Cfg::NACC; ++i)
@@ -519,20 +564,7 @@ struct SplitProduct {
       for (int j = 0; j < Cfg::CNT; ++j) {
         finite &= fabsf(out[i][j]) < __builtin_inff();
         out[i][j] *= 0x1p-24f * 0x1p-24f;
-        static_assert(SPLIT_UP == 24, "both operands");
       }
-    if constexpr (NEAR) {
-      bool all = false;
-      const unsigned long long near = Near::template find<LB>(K, bias, Near::place(lds_f), out, all);
-      if (all) flag[3] = 1;
-      __syncthreads();
-      if (__builtin_amdgcn_readfirstlane(flag[3]) != 0) {
-        repeat_f32<true>(ra, lda, rb, ldb, M, N, K, m0, n0, lds_f, xf, out, nkt, wm, wn, wk, r, g, lane);
-        return;
-      }
-      Near::template form_again<LB>(near, ra, lda, rb, ldb, K, m0, n0, xf, bias, out);
-      return;   // (no part and no sum can have overflowed: what is not finite has met a NaN)
-    }
     if (!finite) *flag = 1;
     __syncthreads();
     if (__builtin_amdgcn_readfirstlane(flag[0]) == 0) return;
@@ -545,6 +577,26 @@ struct SplitProduct {
     top_b = __uint_as_float(flag[2]);
     if (top_a < 0x1p126f && top_b < 0x1p126f && top_a * top_b * (float)K < 0x1p126f) return;
     repeat_f32<false>(ra, lda, rb, ldb, M, N, K, m0, n0, lds_f, xf, out, nkt, wm, wn, wk, r, g, lane);
+  }
+
+  // The power of two that brings the first K tile of A next to 2^SPLIT_UP (activations of deep networks shrink layer by layer to
+  // where their squares would be zero). peak: a word of LDS that holds zero after the next barrier.
+  __device__ __forceinline__ float near_scale(uint32_t* __restrict__ peak, const XfDev& xf, int lane) const {
+    float m = 0.f;
+#pragma unroll
+    for (int i = 0; i < LdA::NV; ++i) {
+      const float4 w = a[0].value(i, xf);
+      m = fmaxf(fmaxf(fmaxf(fabsf(w.x), fabsf(w.y)), fmaxf(fabsf(w.z), fabsf(w.w))), m);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+    __syncthreads();
+    if (lane == 0) atomicMax(peak, __float_as_uint(m));
+    __syncthreads();
+    const uint32_t u = (uint32_t)__builtin_amdgcn_readfirstlane((int)*peak);
+    int e = SPLIT_UP + 127 - (int)(u >> 23);
+    e = u == 0 || u >= 0x7F800000u ? SPLIT_UP : (e < -100 ? -100 : (e > 120 ? 120 : e));
+    return __uint_as_float((uint32_t)(127 + e) << 23);
   }
 
   static __device__ __forceinline__ void negate(f32x16 (&acc)[Cfg::NACC]) {

@@ -96,9 +96,10 @@ def by_row(x, w, b=None):
 ROWS, K, N = 25600, 1152, 128     # 200 tiles of 128 x 128
 
 
-@pytest.mark.parametrize("kind", ["sizes", "tiny", "common", "ends", "groups"])
+@pytest.mark.parametrize("kind", ["sizes", "tiny", "small", "large", "common", "ends", "groups"])
 def test_rows_of_any_kind(kind):
-    """Row sizes from 2^-20 to 2^20 of their neighbours', or so small that their squares underflow; sums whose halves cancel; two
+    """Row sizes from 2^-20 to 2^20 of their neighbours', or so small beside them that their squares underflow; all of them as small or as large
+    as activations of deep networks become; sums whose halves cancel; two
     terms 30 times the others; 16 k of one sign and 16 of the other in turn (which the two groups of K each add up)."""
     gen = generator(len(kind))
     x = torch.randn(ROWS, K, device="cuda", generator=gen)
@@ -118,6 +119,8 @@ def test_rows_of_any_kind(kind):
         x[rows] = (x[rows].double() - (x[rows].double() * w).sum(1, keepdim=True) * w / w.pow(2).sum(1, keepdim=True)).float()
     if kind == "sizes":
         x *= torch.exp2(torch.randint(-20, 21, (ROWS, 1), device="cuda", generator=gen).float())
+    if kind in ("small", "large"):
+        x *= 2.0 ** (-90 if kind == "small" else 90)
     if kind == "tiny":                      # (tiles with such rows are formed again in fp32, with fp32's own signs)
         x[ROWS // 2::7] *= 2.0 ** -80
         keep = rows < ROWS // 2
