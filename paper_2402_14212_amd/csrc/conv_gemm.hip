@@ -189,8 +189,8 @@ int gather_tile_f32(int M, int N, int K, int csel_a, int csel_b, int sets = 1) {
 
 // The tile of a pre-activation product, in Phase I and where it is formed again. Split operands (with what comes out next to
 // zero formed again: NearZero) from three quarters of a round of 128 x 128 tiles on, where at least two thirds of the
-// rounds are the matrix (us fp32 and split: 131072 x 128 x 1152 366 and 286, with the solve in the same
-// kernel 404 and, apart, 304 + 52; 32768 x 128 x 1152 101 and 76; 32768 x 256 x 768 129 and 99).
+// rounds are the matrix (us fp32 and split: 131072 x 128 x 1152 366 and 283, with the solve in the same
+// kernel 404 and, apart, 291 + 52; 32768 x 128 x 1152 101 and 75; 32768 x 256 x 768 129 and 99).
 int z_tile(int M, int N, int K, int csel, int Cout, bool split) {
   const int64_t tiles = (int64_t)ceil_div(M, 128) * ceil_div(N, 128), rounds = (tiles + 255) / 256;
   if (split && N > 64 && K >= 256 && tiles >= 192 && 3 * (int64_t)M * N >= 2 * rounds * 256 * 128 * 128) return TILE_S128;

@@ -268,7 +268,7 @@ __device__ __forceinline__ void plain_store(const Ld& ld, const XfDev& xf, float
 // of one half of K have one sign and those of the other half the other, 1.2e-8 where two terms of 1000 times the others' size
 // cancel, 1.9e-8 where the two groups of K have sums of opposite sign.
 // Of N(0, 1) values 3.2e-8 K are that near: 0.3 of a wavefront's 2048 at K = 4096. What it costs: 1024 x
-// 4096 x 4096 206 us instead of 194, about half of it the squares, half the sums; 131072 x 128 x 1152 286 instead of 275.
+// 4096 x 4096 206 us instead of 194, about half of it the squares, half the sums; 131072 x 128 x 1152 283 instead of 275.
 // More than NEAR_MOST in one wavefront (sums that cancel all over; a column that is near zero in all rows, as in deep networks whose
 // rows have become alike, is 32), or rows so small or large that their squares leave
 // fp32: the workgroup's tile is formed again with fp32 instructions, as the pre-activations of smaller layers are. Rows and

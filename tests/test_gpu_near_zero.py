@@ -1,5 +1,6 @@
 """Pre-activations of large layers on split operands: what comes out next to zero is formed again in 64 bits, so that its sign
-is that of the 64-bit value, the same in Phase I and Phase III; rows that are zero are left alone.
+is that of the 64-bit value, the same in Phase I and Phase III, beside samples of zeros (which have the bias's sign; without a bias, at the
+edges of the matrix and for rows of other sizes: test_gpu_preactivations.py).
 
 Planted: biases that bring chosen pre-activations to a few units in the last place of the sum, a hundredth of the
 rounding error of a sum of two thousand terms, on either side of zero."""
