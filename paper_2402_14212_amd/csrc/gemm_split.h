@@ -272,7 +272,8 @@ __device__ __forceinline__ void plain_store(const Ld& ld, const XfDev& xf, float
 // More than NEAR_MOST in one wavefront (sums that cancel all over; a column that is near zero in all rows, as in deep networks whose
 // rows have become alike, is 32), or rows so small or large that their squares leave
 // fp32: the workgroup's tile is formed again with fp32 instructions, as the pre-activations of smaller layers are. Rows and
-// columns of zeros are exact and not concerned. Apart from that a value depends on its row, its column and the tile alone, and a
+// columns of zeros are exact and not concerned; nor are values that are exactly zero where a wavefront has more than NEAR_MOST of them,
+// since that is not rounding but operands whose products are zeros (identities, masks, blocks). Apart from that a value depends on its row, its column and the tile alone, and a
 // product that is formed again elsewhere with the same tile has the same bits.
 // Signs that differ from the 64-bit network's, twelve inputs each, with fp32 products and here: five layers of 2500 .. 2301 on 1500
 // rows 58 and 43, six of 2048 on 1024 43 and 37, of 3000 on 700 63 and 42, of 4096 on 1024 (eleven) 146 and 94; none in the first layer here.
@@ -332,7 +333,7 @@ struct NearZero {
       const float* p = norms + Cfg::BM + (wn * Cfg::WTN + tn) * 32 + r;
       line[tn] = c * (LB == RCONTIG ? norm(p[0] + p[Cfg::BN]) : p[0]);
     }
-    uint32_t flags[2] = {0, 0};
+    uint32_t flags[2] = {0, 0}, zeros[2] = {0, 0};
     bool outside = false;
 #pragma unroll
     for (int tm = 0; tm < Cfg::WTM; ++tm)
@@ -346,11 +347,18 @@ struct NearZero {
           // (infinite, or zero because of an underflow; 0 times infinity is a row of zeros beside one that is too large: NaN)
           outside |= near == __builtin_inff() || (near == 0.f && v != 0.f);
           flags[bit >> 5] |= fabsf(v + bias[tn]) < near ? 1u << (bit & 31) : 0u;
+          zeros[bit >> 5] |= v == 0.f ? 1u << (bit & 31) : 0u;
         }
       }
-    const unsigned long long found = flags[0] | (unsigned long long)flags[1] << 32;
-    int count = __popcll(found);
+    unsigned long long found = flags[0] | (unsigned long long)flags[1] << 32;
+    int count = 0;
     if (__ballot(found != 0)) {
+      const unsigned long long zero = found & (zeros[0] | (unsigned long long)zeros[1] << 32);
+      int none = __popcll(zero);
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) none += __shfl_xor(none, o);
+      if (none > NEAR_MOST) found &= ~zero;
+      count = __popcll(found);
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) count += __shfl_xor(count, o);
     }

@@ -169,6 +169,32 @@ def test_a_row_does_not_depend_on_the_others():
         assert torch.equal(by_row(v, w)[0][live], y[live]), change
 
 
+def test_weights_of_mostly_zeros():
+    """Every other column of the weights a unit vector, inputs half zeros: thousands of sums that are exactly zero beside planted ones in
+    dense columns. The former are the inputs themselves, the latter keep the sign of the 64-bit sum (but for one in
+    a hundred that comes out as exactly zero too)."""
+    gen = generator(10)
+    W = orthonormal(K, N, gen)
+    W[::2] = torch.eye(K, device="cuda")[: N // 2]
+    x = torch.relu(torch.randn(ROWS, K, device="cuda", generator=gen))
+    rows = torch.arange(0, ROWS, 7, device="cuda")
+    cols = rows // 7 * 2 % N + 1
+    keep = x[rows][:, : N // 2].clone()
+    V = W.clone()
+    V[:, : N // 2] = 0      # (moved along the part of the column that the unit vectors do not see)
+    for _ in range(3):
+        v = V[cols].double()
+        x[rows] = (x[rows].double() - (x[rows].double() * W[cols].double()).sum(1, keepdim=True) * v / v.pow(2).sum(1, keepdim=True)).float()
+    assert torch.equal(x[rows][:, : N // 2], keep)
+    y, got = by_row(x, W.t().contiguous())
+    assert torch.equal(y[:, ::2], x[:, : N // 2])
+    z = (x[rows].double() * W[cols].double()).sum(1).cpu().numpy()
+    some = (y[rows, cols] != 0).cpu().numpy()
+    assert some.mean() > 0.95
+    assert np.array_equal(got[rows.cpu().numpy(), cols.cpu().numpy()][some], (z > 0)[some])
+    assert np.array_equal(got, (y > 0).cpu().numpy())
+
+
 def test_sums_that_cancel_all_over():
     """Rows at right angles to all of W: every value is next to zero, the tile is formed again in fp32. No worse than that."""
     gen = generator(6)
