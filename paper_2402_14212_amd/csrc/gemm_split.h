@@ -280,7 +280,7 @@ __device__ __forceinline__ void plain_store(const Ld& ld, const XfDev& xf, float
 // What is left comes from the rounding of the layers' inputs, as it does with fp32 products.
 constexpr float NEAR_ERROR = 4e-8f;
 constexpr int NEAR_MOST = 64;
-constexpr float NEAR_SQUARES_MIN = 0x1p-60f, NEAR_SQUARES_MAX = 0x1p110f;   // (of the values as they are staged, times a power of two)
+constexpr float NEAR_SQUARES_MIN = 0x1p-100f, NEAR_SQUARES_MAX = 0x1p120f;   // (of the values as they are staged, times a power of two)
 
 template <class EpiDev, class = void>
 struct near_zero : std::false_type {};
@@ -587,8 +587,8 @@ struct SplitProduct {
     repeat_f32<false>(ra, lda, rb, ldb, M, N, K, m0, n0, lds_f, xf, out, nkt, wm, wn, wk, r, g, lane);
   }
 
-  // The power of two that brings the first K tile of A next to 2^SPLIT_UP (activations of deep networks shrink layer by layer to
-  // where their squares would be zero). peak: a word of LDS that holds zero after the next barrier.
+  // The power of two that brings the first K tile of A next to one (activations of deep networks shrink layer by layer to where
+  // their squares would be zero). Rows may then be 2^50 smaller and values 2^50 larger. peak: a word of LDS that holds zero after the next barrier.
   __device__ __forceinline__ float near_scale(uint32_t* __restrict__ peak, const XfDev& xf, int lane) const {
     float m = 0.f;
 #pragma unroll
@@ -602,8 +602,8 @@ struct SplitProduct {
     if (lane == 0) atomicMax(peak, __float_as_uint(m));
     __syncthreads();
     const uint32_t u = (uint32_t)__builtin_amdgcn_readfirstlane((int)*peak);
-    int e = SPLIT_UP + 127 - (int)(u >> 23);
-    e = u == 0 || u >= 0x7F800000u ? SPLIT_UP : (e < -100 ? -100 : (e > 120 ? 120 : e));
+    int e = 127 - (int)(u >> 23);
+    e = u == 0 || u >= 0x7F800000u ? 0 : (e < -100 ? -100 : (e > 120 ? 120 : e));
     return __uint_as_float((uint32_t)(127 + e) << 23);
   }
 

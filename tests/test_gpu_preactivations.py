@@ -96,10 +96,10 @@ def by_row(x, w, b=None):
 ROWS, K, N = 25600, 1152, 128     # 200 tiles of 128 x 128
 
 
-@pytest.mark.parametrize("kind", ["sizes", "tiny", "small", "large", "common", "ends", "groups"])
+@pytest.mark.parametrize("kind", ["sizes", "tiny", "small", "large", "late", "common", "ends", "groups"])
 def test_rows_of_any_kind(kind):
-    """Row sizes from 2^-20 to 2^20 of their neighbours', or so small beside them that their squares underflow; all of them as small or as large
-    as activations of deep networks become; sums whose halves cancel; two
+    """Row sizes from 2^-20 to 2^20 of their neighbours', or so small beside them that their squares underflow; all of them as small or
+    as large as activations of deep networks become; columns of which the first are 2^40 smaller; sums whose halves cancel; two
     terms 30 times the others; 16 k of one sign and 16 of the other in turn (which the two groups of K each add up)."""
     gen = generator(len(kind))
     x = torch.randn(ROWS, K, device="cuda", generator=gen)
@@ -107,6 +107,8 @@ def test_rows_of_any_kind(kind):
     k = torch.arange(K, device="cuda")
     if kind == "common":
         x, W = 1 + 0.1 * x, torch.where(k < K // 2, 1.0, -1.0) * (1 + 0.1 * W)
+    elif kind == "late":
+        x[:, :40] *= 2.0 ** -40
     elif kind == "ends":
         x[:, 0] = x[:, -1] = 30.0
         W[:, 0], W[:, -1] = 30.0, -30.0
@@ -116,7 +118,8 @@ def test_rows_of_any_kind(kind):
     cols = rows // 5 * 37 % N
     for _ in range(2):                      # next to zero, but for the rounding of x
         w = W[cols].double()
-        x[rows] = (x[rows].double() - (x[rows].double() * w).sum(1, keepdim=True) * w / w.pow(2).sum(1, keepdim=True)).float()
+        v = w * (k >= 40) if kind == "late" else w
+        x[rows] = (x[rows].double() - (x[rows].double() * w).sum(1, keepdim=True) * v / v.pow(2).sum(1, keepdim=True)).float()
     if kind == "sizes":
         x *= torch.exp2(torch.randint(-20, 21, (ROWS, 1), device="cuda", generator=gen).float())
     if kind in ("small", "large"):
